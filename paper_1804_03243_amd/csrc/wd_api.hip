@@ -34,6 +34,7 @@ namespace {
 struct Caps {
   uint64_t frame, arcs, nodes, links, kept, raw, words, win;
   uint64_t prof;  // step-profile words per utterance (WD_FLAG_PHASES)
+  bool chip;      // chip-wide mode
 };
 
 // Execution mode: chip-wide kernels per frame for frames too large for one
@@ -67,6 +68,7 @@ Caps resolve_caps(const wd_graph* g, int32_t max_T, const wd_params* p, const wd
   if (incremental_prune(p))
     r.win = (c && c->window_links > 0) ? (uint64_t)c->window_links : std::max<uint64_t>(r.links / 4, 1);
   r.words = T1 * (g->nlevels + 1) + 1;
+  r.chip = chip_wide_mode(p);
   // (one row per frame, then one for the lattice pass)
   r.prof = (p->flags & WD_FLAG_PHASES) ? (T1 + 1) * (uint64_t)kProfSlots : 0;
   return r;
@@ -82,7 +84,8 @@ struct Regions {
   unsigned long long* slot;
   uint32_t* bitmap;
   uint32_t* used;
-  void* grid;
+  void* grid;    // chip-wide: GridLanes; one-workgroup: the clusters' control blocks
+  uint64_t grid_bytes;
   uint64_t bitmap_words, used_words;
   uint64_t total;
 };
@@ -101,13 +104,18 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   R.desc = (LaneDesc*)take(sizeof(LaneDesc));
   R.info = (LaneInfo*)take(sizeof(LaneInfo));
   R.bad = (uint32_t*)take(sizeof(uint32_t));
-  R.grid = take(grid_lane_bytes());
+  // (one size, so that a workspace does not depend on the mode)
+  R.grid_bytes = align_up(std::max(grid_lane_bytes(), cluster_ctl_bytes()), 256);
+  R.grid = take(R.grid_bytes);
   R.bitmap_words = (S + 31) / 32;
   R.used_words = (c.nodes + 31) / 32 + 1;
   char* slot = take(8 * S);
-  char* idx = take(4 * S);
+  // chip-wide: idx, and the epsilon buckets after the bitmap; one workgroup:
+  // the slots of odd frames
+  char* idx = c.chip ? take(4 * S) : nullptr;
+  char* slot2 = c.chip ? nullptr : take(8 * S);
   char* bitmap = take(4 * R.bitmap_words);
-  char* bucket = take(4 * S);
+  char* bucket = c.chip ? take(4 * S) : nullptr;
   char* touched = take(4 * c.frame);
   char* surv_state = take(4 * c.frame);
   char* surv_pack = take(8 * c.frame);
@@ -164,9 +172,11 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
       L.raw_cap = c.raw;
       L.word_cap = c.words;
       L.slot = (decltype(L.slot))at(slot, 8 * S);
-      L.idx = (decltype(L.idx))at(idx, 4 * S);
+      L.idx = c.chip ? (decltype(L.idx))at(idx, 4 * S) : nullptr;
+      L.slot2 = c.chip ? nullptr : (decltype(L.slot2))at(slot2, 8 * S);
+      L.ctl = c.chip ? nullptr : (decltype(L.ctl))at((char*)R.grid, R.grid_bytes);
       L.bitmap = (decltype(L.bitmap))at(bitmap, 4 * R.bitmap_words);
-      L.bucket = (decltype(L.bucket))at(bucket, 4 * S);
+      L.bucket = c.chip ? (decltype(L.bucket))at(bucket, 4 * S) : nullptr;
       L.touched = (decltype(L.touched))at(touched, 4 * c.frame);
       L.surv_state = (decltype(L.surv_state))at(surv_state, 4 * c.frame);
       L.surv_pack = (decltype(L.surv_pack))at(surv_pack, 8 * c.frame);
@@ -325,8 +335,13 @@ static wd_status run_setup(wd_stream* run, const wd_graph* g, int32_t B, const f
   const uint64_t S = (uint64_t)g->S;
   launch_fill_u32((uint32_t*)R.info, (uint64_t)B * sizeof(LaneInfo) / 4, 0u, s);
   launch_fill_u32(R.bad, (uint64_t)B, 0u, s);
-  launch_fill_u64(R.slot, (uint64_t)B * S, kEmpty, s);
-  launch_fill_u32(R.bitmap, (uint64_t)B * R.bitmap_words, 0u, s);
+  if (chip_wide_mode(p)) {
+    launch_fill_u64(R.slot, (uint64_t)B * S, kEmpty, s);
+    launch_fill_u32(R.bitmap, (uint64_t)B * R.bitmap_words, 0u, s);
+  } else {
+    // (the slots and the bitmap: by a decode's first large frame, if it has one)
+    launch_clear_clusters(R.desc, B, s);
+  }
   launch_fill_u32(R.used, (uint64_t)B * R.used_words, 0u, s);
   if (p->flags & WD_FLAG_TIMING)
     for (auto& e : run->ev)
@@ -710,8 +725,7 @@ extern "C" wd_status wd_decode_noalloc(const wd_graph* g, const float* loglikes,
     return st;
   launch_fill_u32((uint32_t*)R.info, sizeof(LaneInfo) / 4, 0u, s);
   launch_fill_u32(R.bad, 1, 0u, s);
-  launch_fill_u64(R.slot, (uint64_t)g->S, kEmpty, s);
-  launch_fill_u32(R.bitmap, R.bitmap_words, 0u, s);
+  launch_clear_clusters(R.desc, 1, s);
   launch_fill_u32(R.used, R.used_words, 0u, s);
   const Params prm{p->beam, p->max_active, p->lattice_beam, p->flags};
   launch_check_loglikes(R.desc, 1, g->P, R.bad, s);

@@ -12,6 +12,8 @@
 
 namespace wd {
 
+struct ClusterCtl;
+
 constexpr uint64_t kEmpty = ~0ull;          // slot holds no token
 constexpr uint32_t kNoArc = 0xffffffffu;    // predecessor of the start token
 constexpr uint32_t kNoEps = 0xffu;          // class byte: state has no epsilon out-arcs
@@ -144,7 +146,7 @@ struct LaneInfo {
   float best_cost;
   uint32_t tb_fail;            // traceback met an inconsistent predecessor
   uint32_t last_tokens;        // surviving tokens of the last decoded frame
-  uint32_t pad0;
+  uint32_t slots_clean;        // one-workgroup mode: the slot arrays and the bitmap have been emptied
   double Z;                    // total cost of the kept lattice (-log of its path sum)
 };
 
@@ -201,6 +203,11 @@ struct LaneDesc {
   uint64_t win_cap;            // incremental pruning: links of one raw window slot (0: off)
   // per-frame scratch
   WD_GLOBAL unsigned long long* slot;    // [S] packed (cost key, arc id); kEmpty between frames
+  // one-workgroup mode: the slots of odd frames (large frames only; both slot
+  // arrays and the bitmap are emptied when a decode has its first large frame)
+  WD_GLOBAL unsigned long long* slot2;   // [S]
+  WD_GLOBAL struct ClusterCtl* ctl;      // control block of the utterance's workgroup cluster
+  // chip-wide mode
   WD_GLOBAL uint32_t* idx;               // [S] node id of a state in the current frame / scratch
   WD_GLOBAL uint32_t* bitmap;            // [ceil(S/32)] zero between frames
   WD_GLOBAL uint32_t* touched;           // [frame_cap] states touched this frame

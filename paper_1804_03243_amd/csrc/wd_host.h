@@ -30,6 +30,10 @@ void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Param
 // forward pass (all frames at once); before launch_lattice.
 void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, hipStream_t s);
 void launch_lattice(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s);
+// One-workgroup mode: the control block of an utterance's workgroup cluster,
+// of which the first part is zero when a launch of the forward pass starts.
+size_t cluster_ctl_bytes();
+size_t cluster_ctl_clear_bytes();
 size_t grid_lane_bytes();
 // Raw window slots of the link store with incremental pruning.
 uint32_t grid_window_slots();
@@ -62,6 +66,9 @@ void launch_pack_results(const LaneDesc* lanes, int B, void* dst, hipStream_t s)
 // Sets T, t0 and open of lanes[0..B) (streaming) from host values passed as
 // kernel arguments.
 void launch_set_frames(LaneDesc* lanes, int B, const int32_t* T, const int32_t* t0, int32_t open, hipStream_t s);
+// Resets the clusters' control blocks (one-workgroup mode, before a launch of
+// the forward pass; launch_set_frames does it for streams).
+void launch_clear_clusters(const LaneDesc* lanes, int B, hipStream_t s);
 void launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
 

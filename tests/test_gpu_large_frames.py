@@ -1,0 +1,137 @@
+"""Large frames of the one-workgroup mode (frames beyond the LDS token table),
+which the leading workgroup runs together with the launch's helpers: against
+the CPU oracle at the sizes where that can go wrong."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_compare import assert_same
+
+pytestmark = pytest.mark.gpu
+
+
+def graph_of(S, A, P, eps, depth, seed):
+    cfg = dict(index=900 + seed, family="zipf_levels", S=S, A=A, eps_frac=eps, depth=depth, P=P, V=1000, wmean=2.0)
+    rng = np.random.default_rng(seed)
+    return synth._pack(synth._graph_zipf_levels(cfg, rng), S)
+
+
+def flat(T, P, seed, std=1.0):
+    return np.random.default_rng(seed).normal(-8.0, std, (T, P)).astype(np.float32)
+
+
+@pytest.fixture(scope="module")
+def wf():
+    import torch
+    from paper_1804_03243_amd import wfstdec
+    assert torch.cuda.is_available()
+    return wfstdec
+
+
+@pytest.fixture(scope="module")
+def noisy(wf):
+    g = graph_of(60_000, 160_000, 200, 0.25, 5, 1)
+    return g, wf.Graph(g, 200)
+
+
+def check(wf, oracle_mod, g, graph, L, args, mode="workgroup", debug=True):
+    import torch
+    print(f"\n[gpu case] large frames S={g['num_states']} T={L.shape[0]} args={args} mode={mode}", flush=True)
+    r = wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, debug=debug, mode=mode)
+    assert_same(r, oracle_mod.decode(g, L, *args, debug=debug), debug=debug)
+    return r
+
+
+# no limit; a limit no frame reaches; limits around the LDS table (2048 touched
+# states), the tile of 1024 tokens and a cluster's shares; ties at the cutoff
+# are kept, so a frame may hold a few more
+@pytest.mark.parametrize("mode", ["workgroup", "workgroup_levels"])
+@pytest.mark.parametrize("beam,ma", [(14.0, 0), (14.0, 50_000), (12.0, 1023), (12.0, 1025), (13.0, 4097), (9.0, 2047)])
+def test_max_active(wf, oracle_mod, noisy, beam, ma, mode):
+    g, graph = noisy
+    r = check(wf, oracle_mod, g, graph, flat(14, 200, 3), (beam, ma, 6.0), mode)
+    assert r.needed["frame_tokens"] > 2048 and r.stats["max_tokens"] >= 1000
+
+
+def test_in_and_out(wf, oracle_mod, noisy):
+    """Flat stretches (large frames) between peaked ones (LDS frames): runs
+    open and close several times, on frames of either parity."""
+    g, graph = noisy
+    L = flat(60, 200, 4)
+    rng = np.random.default_rng(5)
+    for a, b in ((0, 3), (9, 17), (24, 25), (33, 46)):
+        L[a:b] -= 20.0
+        for t in range(a, b):
+            L[t, rng.choice(200, 3, replace=False)] = -1.0
+    r = check(wf, oracle_mod, g, graph, L, (11.0, 3000, 6.0))
+    assert r.needed["frame_tokens"] > 2048
+
+
+def test_ties(wf, oracle_mod):
+    """Costs on a grid of 1/16: many equal costs, among them at the limit."""
+    g = graph_of(20_000, 60_000, 50, 0.2, 4, 2)
+    g["weight"] = synth._quantize(g["weight"])
+    graph = wf.Graph(g, 50)
+    check(wf, oracle_mod, g, graph, synth._quantize(flat(12, 50, 6)), (10.0, 1500, 5.0))
+
+
+def test_wide_start(wf, oracle_mod):
+    """Frame 0 itself outgrows the LDS table: the start state's epsilon arcs
+    reach more states than it has bucket entries."""
+    S, fan = 6000, 2500
+    src = np.concatenate([np.zeros(fan, np.int64), np.arange(1, S), np.arange(1, fan + 1)])
+    dst = np.concatenate([np.arange(1, fan + 1), np.roll(np.arange(1, S), 7), np.arange(1, fan + 1) + fan])
+    il = np.concatenate([np.zeros(fan, np.int64), 1 + np.arange(1, S) % 20, np.zeros(fan, np.int64)])
+    o = np.argsort(src, kind="stable")
+    row = np.zeros(S + 1, np.int64)
+    np.cumsum(np.bincount(src, minlength=S), out=row[1:])
+    w = np.random.default_rng(8).exponential(0.5, src.size).astype(np.float32)
+    g = synth._pack(dict(row_ptr=row, dst=dst[o], ilabel=il[o], olabel=dst[o] % 9, weight=w), S)
+    graph = wf.Graph(g, 20)
+    for mode in ("workgroup", "workgroup_levels"):
+        check(wf, oracle_mod, g, graph, flat(6, 20, 9), (30.0, 0, 8.0), mode)
+
+
+@pytest.mark.parametrize("B", [3, 9, 40])
+def test_batch(wf, oracle_mod, noisy, B):
+    """Lanes share the helpers of their XCD; some lanes have no large frame."""
+    import torch
+    g, graph = noisy
+    args = (11.0, 2500, 6.0)
+    Ls = [flat(4 + b % 7, 200, 20 + b) for b in range(B)]
+    for b in range(0, B, 4):
+        Ls[b] -= 10.0
+        Ls[b][:, b % 200] = 0.0
+    print(f"\n[gpu case] large frames, batch of {B}", flush=True)
+    rs = wf.decode_batch(graph, [torch.from_numpy(x).to(graph.device) for x in Ls], *args, mode="workgroup")
+    for x, r in zip(Ls, rs):
+        assert_same(r, oracle_mod.decode(g, x, *args))
+
+
+def test_stream(wf, oracle_mod, noisy):
+    """Chunks that end inside runs of large frames."""
+    import torch
+    g, graph = noisy
+    L, args = flat(17, 200, 11), (12.0, 3000, 6.0)
+    x = torch.from_numpy(L).to(graph.device)
+    print("\n[gpu case] large frames, streamed", flush=True)
+    s = wf.Stream(graph, 1, 32, *args, mode="workgroup", debug=True)
+    for a, b in ((0, 1), (1, 4), (4, 4), (4, 12), (12, 17)):
+        s.push([x[a:b]])
+    assert_same(s.end()[0], oracle_mod.decode(g, L, *args, debug=True), debug=True)
+
+
+def test_capacities(wf, oracle_mod, noisy):
+    """Per-frame capacities that a large frame outgrows are reported, and the
+    retry decodes."""
+    import torch
+    g, graph = noisy
+    L, args = flat(8, 200, 12), (12.0, 3000, 6.0)
+    x = torch.from_numpy(L).to(graph.device)
+    o = oracle_mod.decode(g, L, *args)
+    for caps in (wf.wd_caps(2500, 0, 0, 0, 0, 0), wf.wd_caps(0, 3000, 0, 0, 0, 0), wf.wd_caps(0, 0, 4000, 0, 0, 0)):
+        print("\n[gpu case] large frames, small capacities", flush=True)
+        with pytest.raises(wf.WdError) as e:
+            wf.decode_batch(graph, [x], *args, caps=caps, max_retries=0, mode="workgroup")
+        assert e.value.status == wf.WD_ECAPACITY
+        assert_same(wf.decode(graph, x, *args, caps=caps, mode="workgroup"), o)
