@@ -456,7 +456,8 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
     launch_lattice(run->g->dg, R.desc, B, lp, s);
     launch_grid_nodes(R.desc, R.grid, B, s);
   } else {
-    launch_links(run->g->dg, R.desc, B, s);
+    launch_sweep(run->g->dg, R.desc, B, run->prm, s);
+    launch_links(run->g->dg, R.desc, B, run->prm, s);
     launch_lattice(run->g->dg, R.desc, B, run->prm, s);
   }
   if (run->ev[2]) (void)hipEventRecord(run->ev[2], s);
@@ -730,7 +731,8 @@ extern "C" wd_status wd_decode_noalloc(const wd_graph* g, const float* loglikes,
   const Params prm{p->beam, p->max_active, p->lattice_beam, p->flags};
   launch_check_loglikes(R.desc, 1, g->P, R.bad, s);
   launch_forward(g->dg, R.desc, 1, prm, R.bad, s);
-  launch_links(g->dg, R.desc, 1, s);
+  launch_sweep(g->dg, R.desc, 1, prm, s);
+  launch_links(g->dg, R.desc, 1, prm, s);
   launch_lattice(g->dg, R.desc, 1, prm, s);
   LaneInfo I;
   if ((st = hip_check(hipGetLastError(), "launch")) ||

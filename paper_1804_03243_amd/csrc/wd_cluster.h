@@ -16,7 +16,7 @@
 // Nothing waits for a workgroup that may not be running: helpers register for
 // a run of frames while the leader holds the registration open for a few
 // microseconds, and the barriers count the registered ones only.  A helper
-// that is idle for kIdleTicks leaves, so the CUs of utterances that never have
+// that is idle for kIdleTicks (and a quarter of the time it has worked) leaves, so the CUs of utterances that never have
 // a large frame are free for other work soon after the launch.
 //
 // Per frame t, with the tokens of frame t - 1 as bits of a state bitmap (and
@@ -35,6 +35,8 @@
 // minima, the same cutoffs.
 #pragma once
 
+#include <stddef.h>
+
 #include "wd_block.h"
 
 namespace wd {
@@ -43,9 +45,9 @@ constexpr uint32_t kXcds = 8;              // consecutive workgroups go to the X
 constexpr uint32_t kClMax = 32;            // workgroups of a cluster (an XCD has 32 CUs)
 constexpr uint32_t kCoarse = 2048;         // state ranges counted for the shares of phase A
 constexpr uint32_t kClDigits = 3;          // radix digits of a 32-bit key (11, 11, 10)
-constexpr uint32_t kClosed = 0x80000000u;  // registration closed
 constexpr uint64_t kIdleTicks = 30000;     // 300 µs of the 100 MHz clock
-constexpr uint64_t kJoinTicks = 400;       // registration stays open this long at most (4 µs)
+constexpr uint64_t kJoinTicks = 400;       // a run waits for its helpers this long at most (4 µs)
+constexpr uint32_t kRegroupFrames = 4;     // frames after which a run takes in late helpers
 constexpr uint64_t kSpinTicks = 200000000; // a wait this long (2 s) is an error, not a hang
 // back to the LDS path once a frame is this small
 constexpr uint32_t kSmallTokens = 512;
@@ -59,11 +61,11 @@ struct alignas(128) ClusterCtl {
   uint32_t quit;    // the leader is done
   uint32_t bad;     // a wait ran into its limit
   uint32_t pad0[28];
-  uint32_t alive;   // helpers polling
-  uint32_t pad1[31];
-  uint32_t reg;     // run << 8 | helpers registered for it | kClosed
-  uint32_t pad2[31];
-  uint32_t nmem;    // run << 8 | workgroups of the run
+  uint32_t tickets; // helpers that have come up
+  uint32_t alive;   // of them, not gone
+  uint32_t pad1[30];
+  uint32_t join[kClMax];    // per helper: the run it waits to be taken into
+  unsigned long long members;  // run << 32 | mask of the helpers in it
   uint32_t t;       // the run's first frame
   uint32_t n_prev;  // tokens of the frame before it
   uint32_t node_base;  // nodes before that frame's successor (low, high)
@@ -71,16 +73,19 @@ struct alignas(128) ClusterCtl {
   uint32_t clear;   // the slot arrays have to be emptied first
   uint32_t hist_ok;
   uint32_t bar0;    // barrier arrivals before the run
-  uint32_t pad3[24];
+  uint32_t pad3;
+  unsigned long long links;  // raw lattice links of the run's frames
+  uint32_t pad4[20];
   uint32_t bar;     // barrier arrivals
-  uint32_t pad4[31];
+  uint32_t pad5[31];
   struct alignas(128) Frame {
     uint32_t best;       // smallest emitting candidate key, inverted (so that 0 is "none")
     uint32_t n_touched;
     uint32_t n_bk;       // bucketed by the expansion
     uint32_t n_bx;       // reached by epsilon paths (bucketed by level without a path table)
     uint32_t n_surv;
-    uint32_t pad0[3];
+    uint32_t regroup;    // helpers wait for the next run: the leader ends this one
+    uint32_t pad0[2];
     unsigned long long work;  // emitting arcs
     unsigned long long eps;   // epsilon arcs of the closure
     uint32_t pad1[20];
@@ -96,19 +101,29 @@ struct ClusterState {
   uint32_t ovf;
   uint32_t n_prev, W;  // tokens of the last frame done, their emitting arcs
   uint32_t hist_ok;
+  uint32_t again;      // the next frame is to be run as a large one, too
   uint64_t node_base;  // nodes before frame t
-  uint64_t arcs, eps, tokens, max_tokens, need_frame, need_arcs;  // of the run's frames
+  uint64_t arcs, eps, links, tokens, max_tokens, need_frame, need_arcs;  // of the run's frames
 };
+
+// The pruning sweep's cluster has a header of its own behind the block (of a
+// ClusterCtl only the part before `f`), so that it finds it clean.
+constexpr size_t kCtlHead = offsetof(ClusterCtl, f);
+constexpr size_t kCtlBytes = sizeof(ClusterCtl) + kCtlHead;
 
 // LDS of a workgroup while it runs large frames (laid over the LDS path's
 // token table and frontier).
 constexpr uint32_t kClTile = 1024;   // tokens or bucket entries per tile
 constexpr uint32_t kClRounds = 4;    // rounds of one touch per thread before the stage is flushed
+constexpr uint32_t kHeld = 3;        // touched states a thread keeps in registers over a frame's last steps
+constexpr uint32_t kSumList = 4096;  // bitmap words listed at once (in the stage)
 constexpr uint32_t kClBk = 2048;     // states with epsilon arcs staged
+constexpr uint32_t kClCand = 12288;  // candidate cost keys a workgroup keeps for the link count
 struct ClusterShared {
   BlockScratch bs;
-  uint32_t pre[kClTile], beg[kClTile], key[kClTile];
-  uint32_t st_n, st_nb, st_at, st_bat;
+  uint32_t pre[kClTile], beg[kClTile], key[kClTile], xbeg[kClTile], deg[kClTile];
+  uint32_t cand[kClCand];
+  uint32_t st_n, st_nb, st_at, st_bat, n_cand;
   uint32_t st[kClRounds * kThreads];
   uint4 bk[kClBk];
   uint32_t hist[kHistBins];
@@ -117,6 +132,7 @@ struct ClusterShared {
   uint32_t go;
   ClusterState out;
 };
+static_assert(kSumList <= kClRounds * (uint32_t)kThreads, "listed bitmap words in the stage");
 static_assert(kClTile == (uint32_t)kThreads, "one token or entry of a tile per thread");
 
 // ------------------------------------------------------------ shared memory
@@ -235,9 +251,14 @@ __device__ __forceinline__ unsigned long long cl_min64(WD_GLOBAL unsigned long l
   return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A kept token of state s: its bit, and its range's count.
-__device__ __forceinline__ void cl_mark(Ctl* C, const LaneDesc& L, int t, uint32_t wsh, uint32_t s) {
+// A kept token of state s: its bit (with `sum`: and the bit of its bitmap word
+// in the summary, kept in surv_state, which large frames do not need), and its
+// range's count.
+__device__ __forceinline__ void cl_mark(Ctl* C, const LaneDesc& L, bool sum, int t, uint32_t wsh, uint32_t s) {
   (void)__hip_atomic_fetch_or(&L.bitmap[s >> 5], 1u << (s & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (sum)
+    (void)__hip_atomic_fetch_or(&L.surv_state[s >> 10], 1u << ((s >> 5) & 31u), __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
   cl_add<uint32_t>(&C->coarse[t & 1][s >> (5u + wsh)], 1u);
 }
 
@@ -292,6 +313,9 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
   const uint32_t nw = (g.S + 31u) >> 5;
   uint32_t wsh = 0;  // bitmap words per counted range, as a shift
   while ((nw >> wsh) >= kCoarse) ++wsh;
+  // a summary bit per bitmap word, where there is room for it and a counted
+  // range is whole summary words (so that no two workgroups share one)
+  const bool sum = wsh >= 5u && (uint64_t)L.frame_cap * 32u >= nw;
   // ------------------------------------------------ a clean control block
   if (cl_load(&C->clear)) {
     const uint64_t n = (uint64_t)g.S, lo = n * w / N, hi = n * (w + 1) / N;
@@ -300,6 +324,8 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       L.slot2[i] = kEmpty;
     }
     for (uint32_t i = w * kThreads + tid; i < nw; i += N * kThreads) L.bitmap[i] = 0;
+    if (sum)
+      for (uint32_t i = w * kThreads + tid; i < (nw + 31u) >> 5; i += N * kThreads) L.surv_state[i] = 0;
   }
   for (uint32_t i = w * kThreads + tid; i < kCoarse; i += N * kThreads) {
     C->coarse[0][i] = 0;
@@ -313,10 +339,14 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
     S.st_nb = 0;
     S.out = ClusterState{};
   }
+  if (w == 0 && tid == 0) cl_store<unsigned long long>(&C->links, 0ull);
   cl_barrier(C, N, gen);
 
+  uint64_t my_links = 0;  // raw lattice links found by this thread
   bool stored = true;  // the frontier of frame t - 1 is in the workspace, with degree prefix sums
   bool small = false;  // frame t - 1 touched few states
+  bool regroup = false;  // the run ends so that more helpers can join the next
+  uint32_t frames = 0;
   uint32_t best_key = 0, kcutb = 0, cut_key = 0;  // of frame t - 1 (from the second frame on)
   int status = 0;
   uint32_t ovf = 0;
@@ -334,8 +364,8 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       n0 = (uint32_t)((uint64_t)n_all * w / N);
       n1 = (uint32_t)((uint64_t)n_all * (w + 1) / N);
     } else {
-      // equal shares of the kept tokens, cut at the counted ranges: range q
-      // belongs to the workgroup that its first token's share falls to
+      // equal shares of the kept tokens, cut at the counted ranges: from the
+      // first range that starts at or after the share's first token on
       const WD_GLOBAL uint32_t* co = C->coarse[(t - 1) & 1];
       const uint32_t c0 = cl_load(&co[2 * tid]), c1 = cl_load(&co[2 * tid + 1]);
       const uint32_t ex = block_excl_scan(c0 + c1, S.bs, par, &n_all);
@@ -346,17 +376,16 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
         S.base = n_all;
       }
       __syncthreads();
-      auto owner = [&](uint32_t q) -> int {
-        const uint64_t o = n_all ? (uint64_t)S.hist[q] * N / n_all : 0;
-        return (int)(o < N ? o : N - 1u);
-      };
+      const uint32_t a = (uint32_t)((uint64_t)n_all * w / N), b = (uint32_t)((uint64_t)n_all * (w + 1) / N);
       for (uint32_t q = 2 * tid; q < 2 * tid + 2; ++q) {
-        const int o = owner(q), b = q ? owner(q - 1) : -1;
-        if (b < (int)w && o >= (int)w) {
+        const uint32_t p = S.hist[q];
+        const bool first = q == 0;
+        const uint32_t before = first ? 0u : S.hist[q - 1];
+        if (p >= a && (first || before < a)) {
           S.lo = q;
-          S.base = S.hist[q];
+          S.base = p;
         }
-        if (b <= (int)w && o > (int)w) S.hi = q;
+        if (w + 1 < N && p >= b && (first || before < b)) S.hi = q;
       }
       __syncthreads();
       const uint32_t lo = S.lo, hi = S.hi;
@@ -367,25 +396,59 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       // the states, in order
       const uint32_t w0 = lo << wsh, w1 = (uint64_t)(hi << wsh) < nw ? hi << wsh : nw;
       n1 = n0;
-      for (uint32_t b = w0; b < w1; b += 4 * kThreads) {
-        uint32_t word[4], c = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-          const uint32_t i = b + 4 * tid + k;
-          word[k] = i < w1 ? cl_load(&L.bitmap[i]) : 0u;
-          c += (uint32_t)__popc(word[k]);
+      // the bits of word v (number i of the bitmap) from position p on
+      auto spread = [&](uint32_t i, uint32_t v, uint32_t p) {
+        if (v) L.bitmap[i] = 0;
+        while (v) {
+          const uint32_t bit = (uint32_t)__ffs(v) - 1u;
+          v &= v - 1u;
+          L.f_state[p++] = (i << 5) | bit;
         }
-        uint32_t tot;
-        uint32_t p = n1 + block_excl_scan(c, S.bs, par, &tot);
-        n1 += tot;
+      };
+      if (sum) {
+        // the summary names the words that are not empty: they are listed in
+        // LDS, then one word per thread (625 KB of bitmap at 5M states took 11
+        // of a frame's 59 µs with 8 workgroups)
+        for (uint32_t b = w0 >> 5; b < (w1 + 31u) >> 5; b += kThreads) {
+          const uint32_t i = b + tid;
+          const uint32_t v = i < (w1 + 31u) >> 5 ? cl_load(&L.surv_state[i]) : 0u;
+          if (v) L.surv_state[i] = 0;
+          uint32_t words;
+          const uint32_t p0 = block_excl_scan((uint32_t)__popc(v), S.bs, par, &words);
+          for (uint32_t c0 = 0; c0 < words; c0 += kSumList) {
+            uint32_t p = p0 - c0;  // (mod 2^32: below or beyond this part of the list)
+            for (uint32_t m = v; m; m &= m - 1u, ++p)
+              if (p < kSumList) S.st[p] = (i << 5) | ((uint32_t)__ffs(m) - 1u);
+            __syncthreads();
+            const uint32_t n = words - c0 < kSumList ? words - c0 : kSumList;
+            for (uint32_t c = 0; c < n; c += kThreads) {
+              const bool on = c + tid < n;
+              const uint32_t q = on ? S.st[c + tid] : 0u;
+              const uint32_t word = on ? cl_load(&L.bitmap[q]) : 0u;
+              uint32_t tot;
+              const uint32_t at = n1 + block_excl_scan((uint32_t)__popc(word), S.bs, par, &tot);
+              n1 += tot;
+              spread(q, word, at);
+            }
+            __syncthreads();
+          }
+        }
+      } else {
+        for (uint32_t b = w0; b < w1; b += 4 * kThreads) {
+          uint32_t word[4], c = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-          uint32_t v = word[k];
-          if (v) L.bitmap[b + 4 * tid + k] = 0;
-          while (v) {
-            const uint32_t bit = (uint32_t)__ffs(v) - 1u;
-            v &= v - 1u;
-            L.f_state[p++] = ((b + 4 * tid + k) << 5) | bit;
+          for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t i = b + 4 * tid + k;
+            word[k] = i < w1 ? cl_load(&L.bitmap[i]) : 0u;
+            c += (uint32_t)__popc(word[k]);
+          }
+          uint32_t tot;
+          uint32_t p = n1 + block_excl_scan(c, S.bs, par, &tot);
+          n1 += tot;
+#pragma unroll
+          for (uint32_t k = 0; k < 4; ++k) {
+            spread(b + 4 * tid + k, word[k], p);
+            p += (uint32_t)__popc(word[k]);
           }
         }
       }
@@ -401,17 +464,19 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
         L.best[t - 1] = key_cost(best_key);
         L.cutb[t - 1] = key_cost(kcutb);
         L.cut[t - 1] = key_cost(cut_key);
+        L.xmask[t - 1] = 1;  // (the frame's raw links are counted here)
         S.out.tokens += n_all;
         if (n_all > S.out.max_tokens) S.out.max_tokens = n_all;
         if (L.prof) L.prof[(size_t)(t - 1) * kProfSlots + kProfStamps] = (uint64_t)n_all << 8;
       }
       for (int k = 6; k < kProfStamps; ++k) stamp(t - 1, k);
-      done = t > T || (small && n_all <= kSmallTokens);
+      done = t > T || regroup || (small && n_all <= kSmallTokens);
     }
     if (!done) stamp(t, 0);
     const float* row = (const float*)L.ll + (size_t)(t > 0 ? t - 1 : 0) * g.P;
     uint32_t my_best = 0xffffffffu;
-    uint64_t my_work = 0;
+    if (tid == 0) S.n_cand = 0;
+    __syncthreads();
     if (t == 0 && w == 0) {  // the start token
       if (tid == 0) {
         const uint32_t s0 = g.start, cls = g.sclass[s0];
@@ -429,7 +494,7 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
     }
     for (uint32_t tb = n0; tb < n1; tb += kClTile) {
       const uint32_t m = n1 - tb < kClTile ? n1 - tb : kClTile;
-      uint32_t deg = 0, beg = 0, key = 0;
+      uint32_t deg = 0, beg = 0, key = 0, xdeg = 0, xbeg = 0;
       if (tid < m) {
         const uint32_t p = tb + tid;
         if (stored) {
@@ -439,12 +504,13 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
         } else {
           const uint32_t s = cl_load(&L.f_state[p]);
           const unsigned long long v = cl_load(&prev[s]);
-          const uint4 o0 = g.off[s];
-          const uint32_t e1 = g.off[s + 1].x;
+          const uint4 o0 = g.off[s], o1 = g.off[s + 1];
           prev[s] = kEmpty;
           key = (uint32_t)(v >> 32);
           beg = o0.x;
-          deg = e1 - o0.x;
+          deg = done ? 0u : o1.x - o0.x;
+          xbeg = o0.y;
+          xdeg = o1.y - o0.y;
           L.f_key[p] = key;
           if (hist_ok) {
             L.n_state[nb + p] = s;
@@ -453,56 +519,91 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
           }
         }
       }
-      if (done) continue;
+      // items: each token's emitting arcs, then its epsilon arcs (frame t - 1's
+      // epsilon links, which are only counted)
       uint32_t tot;
-      S.pre[tid] = block_excl_scan(deg, S.bs, par, &tot);
+      S.pre[tid] = block_excl_scan(deg + xdeg, S.bs, par, &tot);
       S.beg[tid] = beg;
       S.key[tid] = key;
+      S.deg[tid] = deg;
+      S.xbeg[tid] = xbeg;
       __syncthreads();
-      my_work += tot;
+      // two items per thread at a time, each step's loads together
+      constexpr uint32_t kU = 2;
       uint32_t round = 0;
-      for (uint32_t b = 0; b < tot; b += kThreads) {
-        const uint32_t it = b + tid;
-        bool first = false;
-        uint4 r = make_uint4(0, 0, 0, 0), o0 = r, o1 = r;
-        bool eps = false;
-        if (it < tot) {
-          const uint32_t j = cl_find(S.pre, m, it);
-          r = g.earc[S.beg[j] + (it - S.pre[j])];
-          const float ac = -row[(r.z & 0xffffffu) - 1u];
-          eps = (r.z >> 24) != kNoEps;
-          if (eps && paths) {
-            o0 = g.off[r.x];
-            o1 = g.off[r.x + 1];
-          }
-          float x = key_cost(S.key[j]) + ac;
-          x = canon(x + __uint_as_float(r.y));
-          const uint32_t xk = cost_key(x);
-          if (xk < kInfKey) {
-            my_best = xk < my_best ? xk : my_best;
-            first = cl_min64(&cur[r.x], pack_tok(xk, r.w)) == kEmpty;
+      for (uint32_t b = 0; b < tot; b += kU * kThreads) {
+        uint32_t j[kU];
+        bool emit[kU], eps[kU], first[kU];
+        uint4 r[kU];
+        uint2 ox[kU], op[kU];  // a destination's epsilon degree's ends, its paths
+#pragma unroll
+        for (uint32_t u = 0; u < kU; ++u) {
+          const uint32_t it = b + u * kThreads + tid;
+          emit[u] = false;
+          j[u] = 0;
+          r[u] = make_uint4(0, kNoArc, 0, 0);
+          if (it < tot) {
+            j[u] = cl_find(S.pre, m, it);
+            const uint32_t i = it - S.pre[j[u]], de = S.deg[j[u]];
+            emit[u] = i < de;
+            r[u] = emit[u] ? g.earc[S.beg[j[u]] + i] : g.xarc[S.xbeg[j[u]] + (i - de)];
           }
         }
-        const uint32_t p = wave_append(first, &S.st_n);
-        if (first) S.st[p] = r.x;
-        const uint32_t q = wave_append(first && eps, &S.st_nb);
-        if (first && eps) {
-          const uint4 e = paths ? make_uint4(r.x, o0.z, o1.z, o1.y - o0.y) : make_uint4(r.x, 0, 0, r.z >> 24);
-          if (q < kClBk) S.bk[q] = e;
-          else if (paths) cl_bucket_path(F, L, e);
-          else cl_bucket_level(F, L, e.x, e.w);
+        float ac[kU];
+#pragma unroll
+        for (uint32_t u = 0; u < kU; ++u) {
+          eps[u] = emit[u] && (r[u].z >> 24) != kNoEps;
+          ac[u] = emit[u] ? -row[(r[u].z & 0xffffffu) - 1u] : 0.0f;
+          ox[u] = op[u] = make_uint2(0, 0);
+          if (eps[u] && paths) {
+            const uint4 o0 = g.off[r[u].x], o1 = g.off[r[u].x + 1];
+            ox[u] = make_uint2(o0.y, o1.y);
+            op[u] = make_uint2(o0.z, o1.z);
+          }
         }
-        if (++round % kClRounds == 0) cl_flush(S, F, L, paths);
+#pragma unroll
+        for (uint32_t u = 0; u < kU; ++u) {
+          const uint32_t at = wave_append(emit[u], &S.n_cand);
+          first[u] = false;
+          const float c = key_cost(S.key[j[u]]);
+          if (emit[u]) {
+            const float x = canon((c + ac[u]) + __uint_as_float(r[u].y));
+            const uint32_t xk = cost_key(x);
+            if (at < kClCand) S.cand[at] = xk;
+            if (xk < kInfKey) {
+              my_best = xk < my_best ? xk : my_best;
+              first[u] = cl_min64(&cur[r[u].x], pack_tok(xk, r[u].w)) == kEmpty;
+            }
+          } else if (b + u * kThreads + tid < tot) {
+            const uint32_t xk = cost_key(canon(c + __uint_as_float(r[u].y)));
+            my_links += xk <= cut_key && xk < kInfKey ? 1u : 0u;
+          }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kU; ++u) {
+          const uint32_t p = wave_append(first[u], &S.st_n);
+          if (first[u]) S.st[p] = r[u].x;
+          const uint32_t q = wave_append(first[u] && eps[u], &S.st_nb);
+          if (first[u] && eps[u]) {
+            const uint4 e = paths ? make_uint4(r[u].x, op[u].x, op[u].y, ox[u].y - ox[u].x)
+                                  : make_uint4(r[u].x, 0, 0, r[u].z >> 24);
+            if (q < kClBk) S.bk[q] = e;
+            else if (paths) cl_bucket_path(F, L, e);
+            else cl_bucket_level(F, L, e.x, e.w);
+          }
+        }
+        if (++round % (kClRounds / kU) == 0) cl_flush(S, F, L, paths);
       }
       cl_flush(S, F, L, paths);
     }
     if (!stored) nb += n_all;
     if (done) break;
+    const uint32_t my_work = S.n_cand;  // this workgroup's emitting arcs
     my_best = (uint32_t)block_min64(my_best, S.bs, par);
     if (tid == 0) {
       if (my_best != 0xffffffffu)
         (void)__hip_atomic_fetch_max(&F->best, ~my_best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (my_work) cl_add<unsigned long long>(&F->work, my_work);
+      if (my_work) cl_add<unsigned long long>(&F->work, (unsigned long long)my_work);
     }
     stored = false;
     cl_barrier(C, N, gen);
@@ -514,7 +615,7 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
     const uint64_t work = cl_load(&F->work);
     if (w == 0 && tid == 0) {
       if (work > S.out.need_arcs) S.out.need_arcs = work;
-      if (L.prof) L.prof[(size_t)t * kProfSlots + kProfStamps + 1] = work;
+      if (L.prof) L.prof[(size_t)t * kProfSlots + kProfStamps + 1] = work | ((uint64_t)N << 32);
     }
     if (work > L.cand_cap) {
       status = 4;  // WD_ECAPACITY
@@ -649,6 +750,11 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       }
     }
     // (the slots are emptied only after every workgroup has counted)
+    // the next frame's log-likelihood row on its way to the L2 (no value has
+    // this payload)
+    if (t < T)
+      for (uint32_t k = (w * kThreads + tid) * 32u; k < g.P; k += N * kThreads * 32u)
+        my_links += __float_as_uint(L.ll[(size_t)t * g.P + k]) == 0x7fc00001u;
     const bool may_bind = prm.max_active > 0 && nt > (uint32_t)prm.max_active;
     const uint32_t span = kcutb - best_key;
     const uint32_t nbits = span ? 32u - (uint32_t)__clz(span) : 0u;
@@ -657,25 +763,43 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
     uint32_t my_ns = 0;  // survivors of this workgroup's share, in its part of the survivor arrays
     if (tid == 0) S.base = 0;
     __syncthreads();
-    for (uint32_t b = i0; b < i1; b += kThreads) {
+    // (the first kHeld states of each thread stay in registers until the
+    // frame's end)
+    uint32_t hs[kHeld], hk[kHeld];
+#pragma unroll
+    for (uint32_t u = 0; u < kHeld; ++u) {
+      const uint32_t i = i0 + u * kThreads + tid;
+      hs[u] = i < i1 ? cl_load(&L.touched[i]) : 0u;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kHeld; ++u) {
+      const uint32_t i = i0 + u * kThreads + tid;
+      hk[u] = i < i1 ? (uint32_t)(cl_load(&cur[hs[u]]) >> 32) : 0u;
+    }
+    uint32_t turn = 0;
+    for (uint32_t b = i0; b < i1; b += kThreads, ++turn) {
       const uint32_t i = b + tid;
-      uint32_t s = 0;
-      unsigned long long v = kEmpty;
-      if (i < i1) {
+      uint32_t s = 0, key = 0xffffffffu;
+      if (turn < kHeld) {
+#pragma unroll
+        for (uint32_t u = 0; u < kHeld; ++u)
+          if (turn == u) {
+            s = hs[u];
+            key = hk[u];
+          }
+      } else if (i < i1) {
         s = cl_load(&L.touched[i]);
-        v = cl_load(&cur[s]);
+        key = (uint32_t)(cl_load(&cur[s]) >> 32);
       }
-      const uint32_t key = (uint32_t)(v >> 32);
       const bool keep = i < i1 && key <= kcutb;
       if (may_bind) {
         if (keep) (void)atomicAdd(&S.hist[(key - best_key) >> shift], 1u);
         const uint32_t p = wave_append(keep, &S.base);
         if (keep) {
-          L.surv_state[i0 + p] = s;
-          L.surv_pack[i0 + p] = v;
+          L.surv_pack[i0 + p] = key;
         }
       } else if (keep) {
-        cl_mark(C, L, t, wsh, s);
+        cl_mark(C, L, sum, t, wsh, s);
       }
     }
     __syncthreads();
@@ -686,8 +810,15 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       if (tid == 0 && my_ns) cl_add<uint32_t>(&F->n_surv, my_ns);
       cl_merge_hist(S, C->hist[0]);
     }
+    // (late helpers: a launch's workgroups come up over tens of microseconds)
+    if (w == 0 && tid == 0 && N < kClMax) {
+      const uint32_t here = cl_load(&C->alive) + 1u;
+      if (here > N && frames >= kRegroupFrames) cl_store(&F->regroup, 1u);
+    }
     cl_barrier(C, N, gen);
     stamp(t, 3);
+    regroup = cl_load(&F->regroup) != 0;
+    ++frames;
     if (w == 0 && tid == 0) S.out.eps += cl_load(&F->eps);
     cut_key = kcutb;
     // ---------------------------------------- D, E: max-active, kept tokens
@@ -704,7 +835,7 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
           const uint32_t nsh = shift > 11u ? shift - 11u : 0u;
           bits = shift - nsh;
           for (uint32_t i = tid; i < my_ns; i += kThreads) {
-            const uint32_t k = (uint32_t)(cl_load(&L.surv_pack[i0 + i]) >> 32) - best_key;
+            const uint32_t k = (uint32_t)cl_load(&L.surv_pack[i0 + i]) - best_key;
             if ((k >> shift) == prefix) (void)atomicAdd(&S.hist[(k >> nsh) & ((1u << bits) - 1u)], 1u);
           }
           shift = nsh;
@@ -716,12 +847,46 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
       }
       stamp(t, 4);
     }
+    // the frame's emitting links: candidates within the cutoff
+    if (my_work <= kClCand) {
+      for (uint32_t i = tid; i < my_work; i += kThreads) my_links += S.cand[i] <= cut_key && S.cand[i] < kInfKey;
+    } else {
+      // more than LDS holds: formed again from the tokens
+      for (uint32_t tb = n0; tb < n1; tb += kClTile) {
+        const uint32_t m = n1 - tb < kClTile ? n1 - tb : kClTile;
+        uint32_t deg = 0;
+        if (tid < m) {
+          const uint32_t p = tb + tid;
+          const uint32_t s = cl_load(&L.f_state[p]), a0 = g.off[s].x;
+          deg = g.off[s + 1].x - a0;
+          S.beg[tid] = a0;
+          S.key[tid] = cl_load(&L.f_key[p]);
+        }
+        uint32_t tot;
+        S.pre[tid] = block_excl_scan(deg, S.bs, par, &tot);
+        __syncthreads();
+        for (uint32_t it = tid; it < tot; it += kThreads) {
+          const uint32_t j = cl_find(S.pre, m, it);
+          const uint4 r = g.earc[S.beg[j] + (it - S.pre[j])];
+          float x = key_cost(S.key[j]) + -row[(r.z & 0xffffffu) - 1u];
+          x = canon(x + __uint_as_float(r.y));
+          const uint32_t xk = cost_key(x);
+          my_links += xk <= cut_key && xk < kInfKey;
+        }
+        __syncthreads();
+      }
+    }
     // emptied slots: states touched but not kept
-    for (uint32_t i = i0 + tid; i < i1; i += kThreads) {
-      const uint32_t s = cl_load(&L.touched[i]);
-      const uint32_t key = (uint32_t)(cl_load(&cur[s]) >> 32);
+    auto finish = [&](uint32_t s, uint32_t key) {
       if (key > cut_key) cur[s] = kEmpty;
-      else if (may_bind) cl_mark(C, L, t, wsh, s);
+      else if (may_bind) cl_mark(C, L, sum, t, wsh, s);
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < kHeld; ++u)
+      if (i0 + u * kThreads + tid < i1) finish(hs[u], hk[u]);
+    for (uint32_t i = i0 + kHeld * kThreads + tid; i < i1; i += kThreads) {
+      const uint32_t s = cl_load(&L.touched[i]);
+      finish(s, (uint32_t)(cl_load(&cur[s]) >> 32));
     }
     if (may_bind) {
       cl_barrier(C, N, gen);
@@ -735,6 +900,8 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
 
   // ------------------------------------------------------- end of the run
   // (uniform over the cluster: every exit above follows from shared values)
+  my_links = block_sum64(my_links, S.bs, par);
+  if (tid == 0 && my_links) cl_add<unsigned long long>(&C->links, my_links);
   if (status == 0) cl_barrier(C, N, gen);
   if (w != 0) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -767,98 +934,107 @@ __device__ __forceinline__ void cl_run(const DevGraph& g, const LaneDesc& L, con
     S.out.W = W;
     S.out.hist_ok = hist_ok ? 1u : 0u;
     S.out.node_base = nb;
+    S.out.links = cl_load(&C->links);
+    S.out.again = regroup && !(small && n_all <= kSmallTokens) ? 1u : 0u;
   }
   __syncthreads();
 }
 
 // ------------------------------------------------------------ runs, helpers
 
+// The lane of a helper workgroup (blockIdx.x >= B): helpers go to the XCDs in
+// turn, as the leaders do, so it is one whose leader is expected on this
+// workgroup's XCD; false: there is none.
+__device__ __forceinline__ bool helper_lane(uint32_t B, uint32_t* lane) {
+  const uint32_t x = blockIdx.x % kXcds, nl = B > x ? (B - x + kXcds - 1) / kXcds : 0u;
+  if (nl == 0) return false;
+  *lane = x + kXcds * (((blockIdx.x - B) / kXcds) % nl);
+  return true;
+}
+
 // The leader opens run number `run` at frame t with whatever helpers answer;
-// returns the number of workgroups.  Whole workgroup; the frontier of frame
-// t - 1 is in the workspace.
-__device__ __forceinline__ uint32_t cl_open(Ctl* C, ClusterShared& S, int t, uint32_t n_prev, uint64_t node_base,
+// returns the number of workgroups.  Whole workgroup (`go`: a word of its
+// LDS); the frontier of frame t - 1 is in the workspace.
+__device__ __forceinline__ uint32_t cl_open(Ctl* C, uint32_t& go, int t, uint32_t n_prev, uint64_t node_base,
                                             bool hist_ok, bool clear, uint32_t run) {
   cl_drain();
   __syncthreads();
-  if (threadIdx.x == 0) {
-    cl_store(&C->t, (uint32_t)t);
-    cl_store(&C->n_prev, n_prev);
-    cl_store(&C->node_base, (uint32_t)node_base);
-    cl_store(&C->node_base_hi, (uint32_t)(node_base >> 32));
-    cl_store(&C->hist_ok, hist_ok ? 1u : 0u);
-    cl_store(&C->clear, clear ? 1u : 0u);
-    cl_store(&C->bar0, cl_load(&C->bar));
-    (void)__hip_atomic_exchange(&C->reg, run << 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    cl_drain();
-    cl_store(&C->cmd, run);
-    const uint64_t t0 = wall_clock64();
-    while ((cl_load(&C->reg) & 0xffu) < cl_load(&C->alive) && wall_clock64() - t0 < kJoinTicks) {
+  if (threadIdx.x < 64u) {
+    if (threadIdx.x == 0) {
+      cl_store(&C->t, (uint32_t)t);
+      cl_store(&C->n_prev, n_prev);
+      cl_store(&C->node_base, (uint32_t)node_base);
+      cl_store(&C->node_base_hi, (uint32_t)(node_base >> 32));
+      cl_store(&C->hist_ok, hist_ok ? 1u : 0u);
+      cl_store(&C->clear, clear ? 1u : 0u);
+      cl_store(&C->bar0, cl_load(&C->bar));
+      cl_drain();
+      cl_store(&C->cmd, run);
     }
-    const uint32_t n = __hip_atomic_fetch_or(&C->reg, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffu;
-    cl_store(&C->nmem, (run << 8) | (n + 1u));
-    S.go = n + 1u;
+    // the helpers that have answered when the wait ends are in the run
+    const uint64_t t0 = wall_clock64();
+    uint64_t mask;
+    do {
+      mask = __ballot(threadIdx.x < kClMax && cl_load(&C->join[threadIdx.x % kClMax]) == run);
+    } while ((uint32_t)__popcll(mask) < cl_load(&C->alive) && wall_clock64() - t0 < kJoinTicks);
+    if (threadIdx.x == 0) {
+      cl_store<unsigned long long>(&C->members, ((unsigned long long)run << 32) | mask);
+      go = (uint32_t)__popcll(mask) + 1u;
+    }
   }
   __syncthreads();
-  const uint32_t N = S.go;
+  const uint32_t N = go;
   __syncthreads();
   return N;
 }
 
-// A helper waits for the leader's next run: its place and the number of
+// A helper (its number in id, kClMax before it has one) waits for the leader's
+// next run: its place and the number of
 // workgroups as place << 8 | number, or 0 when it leaves (the leader is done,
-// is on another XCD, has enough helpers, or has had no run for kIdleTicks since
-// `idle`).  Whole workgroup.
-__device__ __forceinline__ uint32_t cl_wait(Ctl* C, ClusterShared& S, uint32_t& seen, bool& here) {
+// is on another XCD, has enough helpers, or opens no run for idle_ticks).
+// Whole workgroup.
+__device__ __forceinline__ uint32_t cl_wait(Ctl* C, uint32_t& go_lds, uint32_t& seen, uint32_t& id,
+                                            uint64_t idle_ticks) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint64_t idle = wall_clock64();
     uint32_t go = 0;
     while (true) {
-      if (cl_load(&C->quit) || wall_clock64() - idle > kIdleTicks) break;
-      if (!here) {
+      if (cl_load(&C->quit) || wall_clock64() - idle > idle_ticks) break;
+      if (id == kClMax) {
         const uint32_t x = cl_load(&C->xcc);
         if (x == 0) {
           __builtin_amdgcn_s_sleep(16);
           continue;
         }
         if (x - 1u != cl_xcc()) break;
-        here = true;
-        if (cl_add<uint32_t>(&C->alive, 1u) >= kClMax - 1u) break;
+        const uint32_t ticket = cl_add<uint32_t>(&C->tickets, 1u);
+        if (ticket >= kClMax - 1u) break;
+        id = ticket;
+        cl_add<uint32_t>(&C->alive, 1u);
       }
       const uint32_t run = cl_load(&C->cmd);
       if (run == seen) {
-        __builtin_amdgcn_s_sleep(16);
+        __builtin_amdgcn_s_sleep(8);
         continue;
       }
+      // answer, and see whether the leader took it in
       seen = run;
-      // register, unless the run has been closed (or is over) meanwhile
-      uint32_t r = cl_load(&C->reg);
-      bool in = false;
-      while (r >> 8 == run) {
-        uint32_t want = r;
-        if (__hip_atomic_compare_exchange_strong(&C->reg, &want, r + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT)) {
-          in = true;
-          break;
-        }
-        r = want;
-      }
-      if (!in) continue;
+      cl_store(&C->join[id], run);
       const uint64_t t0 = wall_clock64();
-      uint32_t nm = cl_load(&C->nmem);
-      while (nm >> 8 != run && wall_clock64() - t0 < kSpinTicks) nm = cl_load(&C->nmem);
-      if (nm >> 8 != run) {
-        cl_store(&C->bad, 1u);
-        break;
-      }
-      go = (((r & 0xffu) + 1u) << 8) | (nm & 0xffu);
+      unsigned long long m = cl_load(&C->members);
+      while ((uint32_t)(m >> 32) != run && cl_load(&C->cmd) == run && wall_clock64() - t0 < kSpinTicks)
+        m = cl_load(&C->members);
+      if ((uint32_t)(m >> 32) != run || !((m >> id) & 1u)) continue;
+      const uint32_t mask = (uint32_t)m;
+      go = (((uint32_t)__popc(mask & ((1u << id) - 1u)) + 1u) << 8) | ((uint32_t)__popc(mask) + 1u);
       break;
     }
-    if (go == 0 && here) (void)cl_add<uint32_t>(&C->alive, ~0u);
-    S.go = go;
+    if (go == 0 && id < kClMax) (void)cl_add<uint32_t>(&C->alive, ~0u);
+    go_lds = go;
   }
   __syncthreads();
-  const uint32_t go = S.go;
+  const uint32_t go = go_lds;
   __syncthreads();
   return go;
 }

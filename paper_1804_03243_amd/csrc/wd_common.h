@@ -103,6 +103,10 @@ struct DevGraph {
   //   ptail[p * pstride + i] = weight of arc i < k - 1 (pstride = longest path - 1)
   const uint4* phead;
   const float* ptail;
+  // In-arcs (for the pruning sweep): those of state s are [roff[s], roff[s+1]),
+  // each {source state, weight bits, ilabel (0: epsilon), arc id}
+  const uint32_t* roff;
+  const uint4* rarc;
   uint64_t npaths;
   uint32_t pstride;
   uint32_t S;

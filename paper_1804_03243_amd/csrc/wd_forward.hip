@@ -39,7 +39,7 @@ static_assert(kBkCap == (uint32_t)kThreads, "one bucket entry per thread in the 
 struct FwdShared {
   BlockScratch bs;
   // utterance counters, kept by thread 0 (in LDS to spare registers)
-  unsigned long long c_arcs, c_tokens, c_max_tokens, c_need_frame, c_need_arcs;
+  unsigned long long c_arcs, c_links, c_tokens, c_max_tokens, c_need_frame, c_need_arcs;
   uint32_t n_surv;     // survivors of the beam cutoff
   uint32_t sel_b;
   uint32_t sel_before;
@@ -168,7 +168,7 @@ __device__ __forceinline__ void h_clear(FwdShared& sh, uint32_t used) {
       }
     }
   }
-  for (uint32_t i = threadIdx.x; i <= (uint32_t)kMaxLevels; i += kThreads) sh.nbl[i] = 0;
+  for (uint32_t i = opaque(threadIdx.x); i <= (uint32_t)kMaxLevels; i += kThreads) sh.nbl[i] = 0;
   if (threadIdx.x == 0) {
     sh.hcount = 0;
     sh.spill = 0;
@@ -254,13 +254,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   const uint32_t tid = threadIdx.x;
   const bool lead = blockIdx.x < B;
   uint32_t lane_no = blockIdx.x;
-  if (!lead) {
-    // helpers go to XCDs in turn, as the leaders do: a lane whose leader is
-    // expected on this workgroup's XCD
-    const uint32_t x = blockIdx.x % kXcds, nl = B > x ? (B - x + kXcds - 1) / kXcds : 0u;
-    if (nl == 0) return;
-    lane_no = x + kXcds * (((blockIdx.x - B) / kXcds) % nl);
-  }
+  if (!lead && !helper_lane(B, &lane_no)) return;
   const LaneDesc& L = lanes[lane_no];
   Ctl* const C = (Ctl*)L.ctl;
   ClusterShared& cs = *reinterpret_cast<ClusterShared*>(sh.hist);
@@ -300,9 +294,12 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   uint64_t my_eps = 0;
   bool clean = false;     // the slot arrays and the bitmap are empty (large frames)
   uint32_t runs = 0;      // runs of large frames opened (leader), seen (helper)
-  bool here = false;      // helper: counted among the lane's helpers
+  uint32_t id = kClMax;   // helper: its number among the lane's helpers
+  bool again = false;     // the next frame is a large one (its run was only interrupted)
+  uint64_t busy = 0;      // helper: time spent in runs
   if (tid == 0) {
     sh.c_arcs = 0;
+    sh.c_links = 0;
     sh.c_tokens = 0;
     sh.c_max_tokens = 0;
     sh.c_need_frame = 1;
@@ -349,6 +346,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     my_eps = tid == 0 ? I.eps_arcs : 0;
     if (tid == 0) {
       sh.c_arcs = I.arcs_expanded - I.eps_arcs;
+      sh.c_links = I.links;
       sh.c_tokens = I.tokens;
       sh.c_max_tokens = I.max_tokens;
       sh.c_need_frame = I.need_frame_tokens;
@@ -382,7 +380,8 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
         }
         const Front fp = front_at(front_lds, sh, L);  // frontier of frame t-1
         const float* row = L.ll + (size_t)(t > 0 ? t - 1 : 0) * P;
-        if (W > kLdsWork) {
+        if (W > kLdsWork || again) {
+          again = false;
           large = true;
           break;
         }
@@ -514,7 +513,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
               if (tid < 64u) {
                 const uint32_t inc = wave_incl_scan(d), ex = inc - d;
                 const uint32_t all = lane63(inc);
-                sh.xp[tid] = ex;
+                sh.xp[opaque(tid)] = ex;
                 if (all <= kOwnCap)
                   for (uint32_t k = 0; k < d; ++k) own[ex + k] = (uint16_t)tid;
                 if (tid == 63u) sh.lvl_tot = all;
@@ -525,7 +524,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
               tot = sh.lvl_tot;
             } else {
               const uint32_t ex = block_excl_scan(d, sh.bs, par, &tot);
-              sh.xp[tid] = ex;
+              sh.xp[opaque(tid)] = ex;
               if (tot <= kOwnCap)
                 for (uint32_t k = 0; k < d; ++k) own[ex + k] = (uint16_t)tid;
               __syncthreads();
@@ -615,7 +614,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
               const uint32_t all = lane63(inc);
               if (all > 64u) break;  // (nothing of this level done yet)
               eps_frame += d;
-              sh.xp[tid] = ex;
+              sh.xp[opaque(tid)] = ex;
               for (uint32_t k = 0; k < d; ++k) own[ex + k] = (uint16_t)tid;
               __builtin_amdgcn_wave_barrier();
               if (tid < all) relax_eps(own[tid], tid);
@@ -648,7 +647,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
               if (tid < 64u) {
                 const uint32_t inc = wave_incl_scan(d), ex = inc - d;
                 const uint32_t all = lane63(inc);
-                sh.xp[tid] = ex;
+                sh.xp[opaque(tid)] = ex;
                 if (all <= kOwnCap)
                   for (uint32_t k = 0; k < d; ++k) own[ex + k] = (uint16_t)tid;
                 if (tid == 63u) sh.lvl_tot = all;
@@ -657,7 +656,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
               tot = sh.lvl_tot;
             } else {
               const uint32_t ex = block_excl_scan(d, sh.bs, par, &tot);
-              sh.xp[tid] = ex;
+              sh.xp[opaque(tid)] = ex;
               if (tot <= kOwnCap)
                 for (uint32_t k = 0; k < d; ++k) own[ex + k] = (uint16_t)tid;
               __syncthreads();
@@ -775,10 +774,11 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
             static_assert(kDirectRank <= kFrontCap, "a directly ranked frontier is in LDS");
             deg_ready = true;
             if (cut_key != kcutb) {
-              if (tid < m) {
+              const uint32_t i = opaque(tid);
+              if (i < m) {
                 uint32_t s = kNoKey;
-                if ((uint32_t)(sh.rs_pack[tid] >> 32) <= cut_key) s = sh.rs_state[tid];
-                sh.srt[tid] = s;
+                if ((uint32_t)(sh.rs_pack[i] >> 32) <= cut_key) s = sh.rs_state[i];
+                sh.srt[i] = s;
               }
               __syncthreads();
             }
@@ -928,6 +928,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
           L.best[t] = best;
           L.cutb[t] = cutb;
           L.cut[t] = key_cost(cut_key);
+          L.xmask[t] = 0;  // (its links are not counted yet)
         }
         if (tid == kBook) {
           sh.c_tokens += n_keep;
@@ -942,8 +943,8 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
           if (tid >= 768u) {
             const uint32_t k = (opaque(tid) - 768u) * 32u;
             if (k < P) warm = L.ll[(size_t)t * P + k];
-          } else if (fl && tid >= 512u && tid - 512u < W_next) {
-            const uint32_t w = tid - 512u, p = search_le(fs.edeg, n_keep, w);
+          } else if (fl && tid >= 512u && opaque(tid) - 512u < W_next) {
+            const uint32_t w = opaque(tid) - 512u, p = search_le(fs.edeg, n_keep, w);
             warm = __uint_as_float(g.earc[fs.ebeg[p] + (w - fs.edeg[p])].y);
           }
         }
@@ -975,14 +976,16 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
       if (!large) break;
       if (front_lds) front_out();
       w = 0;
-      N = cl_open(C, cs, t, n_prev, node_base, hist_ok, !clean, ++runs);
+      N = cl_open(C, cs.go, t, n_prev, node_base, hist_ok, !clean, ++runs);
     } else {
-      const uint32_t go = cl_wait(C, cs, runs, here);
+      const uint32_t go = cl_wait(C, cs.go, runs, id, kIdleTicks + busy / 4);
       if (go == 0) return;
       w = go >> 8;
       N = go & 0xffu;
     }
+    const uint64_t t0 = wall_clock64();
     cl_run(g, L, prm, cs, C, w, N, paths);
+    busy += wall_clock64() - t0;
     if (!lead) continue;
     // the run's outcome; the LDS tables start afresh
     const ClusterState& o = cs.out;
@@ -993,12 +996,14 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     W = __builtin_amdgcn_readfirstlane(o.W);
     hist_ok = __builtin_amdgcn_readfirstlane(o.hist_ok) != 0;
     node_base = uniform64(o.node_base);
+    again = __builtin_amdgcn_readfirstlane(o.again) != 0;
     front_lds = false;
     front_own = false;
     clean = true;
     if (tid == 0) {
       my_eps += o.eps;
       sh.c_arcs += o.arcs;
+      sh.c_links += o.links;
       sh.c_tokens += o.tokens;
       if (o.max_tokens > sh.c_max_tokens) sh.c_max_tokens = o.max_tokens;
       if (o.need_frame > sh.c_need_frame) sh.c_need_frame = o.need_frame;
@@ -1025,7 +1030,9 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     info->eps_arcs = eps;
     info->tokens = sh.c_tokens;
     info->max_tokens = sh.c_max_tokens;
-    // (links, need_links: set by the link kernels after the forward pass)
+    // (the large frames' raw links; the link kernels count the other frames'
+    // after the forward pass, or all of them)
+    info->links = sh.c_links;
     info->need_frame_tokens = sh.c_need_frame;
     info->need_frame_arcs = sh.c_need_arcs;
     info->last_tokens = n_prev;
@@ -1047,22 +1054,25 @@ __global__ void __launch_bounds__(kThreads) k_forward_phases(DevGraph g, const L
   forward_body<true>(sh, g, lanes, prm, bad, B);
 }
 
-// A batch that leaves CUs idle brings helpers for large frames: one workgroup
-// per CU in all (they leave within 300 µs when no frame needs them).
-void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm,
-                    const uint32_t* bad, hipStream_t s) {
+int cluster_grid(int B) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     cus = 0;
-  const int grid = B < cus ? cus : B;
+  return B < cus ? cus : B;
+}
+
+// A batch that leaves CUs idle brings helpers for large frames: one workgroup
+// per CU in all (they leave within 300 µs when no frame needs them).
+void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm,
+                    const uint32_t* bad, hipStream_t s) {
+  const int grid = cluster_grid(B);
   if (prm.flags & WD_FLAG_PHASES)
     hipLaunchKernelGGL(k_forward_phases, dim3(grid), dim3(kThreads), 0, s, g, lanes, prm, bad, (uint32_t)B);
   else
     hipLaunchKernelGGL(k_forward, dim3(grid), dim3(kThreads), 0, s, g, lanes, prm, bad, (uint32_t)B);
 }
 
-size_t cluster_ctl_bytes() { return sizeof(ClusterCtl); }
-size_t cluster_ctl_clear_bytes() { return offsetof(ClusterCtl, f); }
+size_t cluster_ctl_bytes() { return kCtlBytes; }
 
 }  // namespace wd

@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "wd_block.h"
 #include "wd_host.h"
 
 namespace wd {
@@ -34,7 +35,7 @@ struct Prepared {
 };
 
 struct Layout {
-  uint64_t off, earc, xarc, xnext, sclass, final_w, ilabel, olabel, weight, level_base, phead, ptail, total;
+  uint64_t off, earc, xarc, xnext, sclass, final_w, ilabel, olabel, weight, level_base, phead, ptail, roff, rarc, total;
 };
 
 Layout layout(int64_t S, int64_t A, uint64_t Ae, uint64_t Ax, uint32_t nlevels, bool finals, uint64_t npaths,
@@ -58,6 +59,8 @@ Layout layout(int64_t S, int64_t A, uint64_t Ae, uint64_t Ax, uint32_t nlevels, 
   l.level_base = take(sizeof(uint32_t) * (uint64_t)(nlevels + 1));
   l.phead = npaths ? take(sizeof(uint4) * 2 * npaths) : 0;
   l.ptail = npaths && pstride ? take(sizeof(float) * npaths * pstride) : 0;
+  l.roff = take(sizeof(uint32_t) * (uint64_t)(S + 1));
+  l.rarc = take(sizeof(uint4) * (uint64_t)(A ? A : 1));
   l.total = p;
   return l;
 }
@@ -247,6 +250,60 @@ wd_status prepare(const wd_graph_desc* d, Prepared& p, uint64_t* Ae_out, uint64_
   return WD_OK;
 }
 
+// The in-arcs of every state, from the uploaded out-arcs: in-degrees, their
+// prefix sums, then each arc into its destination's range (in no particular
+// order: the pruning sweep takes minima over them).  roff[s + 1] is state s's
+// degree, then its start, and after the last step its end.
+__global__ void k_rev_zero(uint32_t* roff, uint64_t n) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    roff[i] = 0;
+}
+
+__global__ void k_rev_count(const uint4* __restrict__ arc, uint64_t n, uint32_t* roff) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    atomicAdd(&roff[arc[i].x + 1], 1u);
+}
+
+// One workgroup: exclusive prefix sums of roff[1..S] in place.
+__global__ void __launch_bounds__(kThreads) k_rev_scan(uint32_t* roff, uint32_t S) {
+  __shared__ BlockScratch bs;
+  constexpr uint32_t kPer = 16;
+  uint32_t par = 0, run = 0;
+  for (uint64_t b = 0; b < S; b += kPer * kThreads) {
+    const uint64_t i0 = b + (uint64_t)threadIdx.x * kPer;
+    uint32_t v[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      v[k] = i0 + k < S ? roff[1 + i0 + k] : 0u;
+      sum += v[k];
+    }
+    uint32_t tot;
+    uint32_t ex = run + block_excl_scan(sum, bs, par, &tot);
+    run += tot;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      if (i0 + k < S) roff[1 + i0 + k] = ex;
+      ex += v[k];
+    }
+  }
+}
+
+// A thread per state: its emitting, then its epsilon arcs.
+__global__ void k_rev_fill(const uint4* __restrict__ off, const uint4* __restrict__ earc,
+                           const uint4* __restrict__ xarc, uint32_t S, uint32_t* roff, uint4* __restrict__ rarc) {
+  for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x) {
+    const uint4 o0 = off[s], o1 = off[s + 1];
+    for (uint32_t a = o0.x; a < o1.x; ++a) {
+      const uint4 r = earc[a];
+      rarc[atomicAdd(&roff[r.x + 1], 1u)] = make_uint4(s, r.y, r.z & 0xffffffu, r.w);
+    }
+    for (uint32_t a = o0.y; a < o1.y; ++a) {
+      const uint4 r = xarc[a];
+      rarc[atomicAdd(&roff[r.x + 1], 1u)] = make_uint4(s, r.y, 0u, r.w);
+    }
+  }
+}
+
 }  // namespace
 
 }  // namespace wd
@@ -297,6 +354,18 @@ extern "C" wd_status wd_graph_load(const wd_graph_desc* d, void* dev_buf, size_t
       (npaths && (st = put(l.phead, p.phead.data(), sizeof(uint4) * 2 * npaths))) ||
       (npaths && p.pstride && (st = put(l.ptail, p.ptail.data(), sizeof(float) * npaths * p.pstride))))
     return st;
+  {
+    const uint4* off = (const uint4*)(base + l.off);
+    const uint4 *ea = (const uint4*)(base + l.earc), *xa = (const uint4*)(base + l.xarc);
+    uint32_t* roff = (uint32_t*)(base + l.roff);
+    hipLaunchKernelGGL(k_rev_zero, dim3(1024), dim3(256), 0, s, roff, (uint64_t)S + 1);
+    if (Ae) hipLaunchKernelGGL(k_rev_count, dim3(2048), dim3(256), 0, s, ea, Ae, roff);
+    if (Ax) hipLaunchKernelGGL(k_rev_count, dim3(2048), dim3(256), 0, s, xa, Ax, roff);
+    hipLaunchKernelGGL(k_rev_scan, dim3(1), dim3(kThreads), 0, s, roff, (uint32_t)S);
+    hipLaunchKernelGGL(k_rev_fill, dim3(2048), dim3(256), 0, s, off, ea, xa, (uint32_t)S, roff,
+                       (uint4*)(base + l.rarc));
+    if ((st = hip_check(hipGetLastError(), "in-arcs"))) return st;
+  }
   if ((st = hip_check(hipStreamSynchronize(s), "graph upload sync"))) return st;
   wd_graph* g = new wd_graph();
   g->S = (int32_t)S;
@@ -320,6 +389,8 @@ extern "C" wd_status wd_graph_load(const wd_graph_desc* d, void* dev_buf, size_t
   dg.level_base = (const uint32_t*)(base + l.level_base);
   dg.phead = npaths ? (const uint4*)(base + l.phead) : nullptr;
   dg.ptail = npaths && p.pstride ? (const float*)(base + l.ptail) : nullptr;
+  dg.roff = (const uint32_t*)(base + l.roff);
+  dg.rarc = (const uint4*)(base + l.rarc);
   dg.npaths = npaths;
   dg.pstride = p.pstride;
   dg.S = (uint32_t)S;

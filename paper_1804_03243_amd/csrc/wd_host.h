@@ -28,12 +28,15 @@ void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Param
                     const uint32_t* bad, hipStream_t s);
 // Lattice links of one-workgroup decodes, from the node store, after the
 // forward pass (all frames at once); before launch_lattice.
-void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, hipStream_t s);
+void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s);
+// Backward pruning sweep over the live nodes only, for the utterances that
+// sparse_lane chooses; before launch_links, which then forms their kept links.
+void launch_sweep(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s);
 void launch_lattice(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s);
-// One-workgroup mode: the control block of an utterance's workgroup cluster,
-// of which the first part is zero when a launch of the forward pass starts.
+// The control block of an utterance's workgroup cluster.
 size_t cluster_ctl_bytes();
-size_t cluster_ctl_clear_bytes();
+// Workgroups of a launch of B leaders that brings helpers: one per CU in all.
+int cluster_grid(int B);
 size_t grid_lane_bytes();
 // Raw window slots of the link store with incremental pruning.
 uint32_t grid_window_slots();

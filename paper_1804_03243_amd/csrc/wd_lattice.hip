@@ -9,7 +9,7 @@
 // 1-best path is traced back during the same sweep.  Then fp64 forward-backward
 // posteriors over the kept links (Sec. 4.1 uses lattice posteriors) and the
 // final merge of the kept links (Sec. 3.5) in (t, arc id) order.
-#include "wd_block.h"
+#include "wd_sparse.h"
 
 namespace wd {
 
@@ -1207,7 +1207,9 @@ __global__ void __launch_bounds__(kLT) k_lattice(DevGraph g, const LaneDesc* __r
 
   // ------------------------------------------------ backward extra-cost sweep
   lstamp(1);
-  if (!swept && !sweep_staged(L, g, sh, tid, par, final_used, best_total)) sweep_block(L, g, sh, tid, final_used, best_total);
+  // (a sparse utterance's links are its kept ones, with their extra costs)
+  const bool sparse = sparse_lane(L, prm.flags);
+  if (!swept && !sparse && !sweep_staged(L, g, sh, tid, par, final_used, best_total)) sweep_block(L, g, sh, tid, final_used, best_total);
   __syncthreads();
   lstamp(2);
 

@@ -17,12 +17,15 @@
 // store's capacity), then the links, each frame by one workgroup.
 #include "wd_block.h"
 #include "wd_host.h"
+#include "wd_sparse.h"
 
 namespace wd {
 
 constexpr int kLT = 256;              // threads per workgroup
 constexpr int kLWv = kLT / 64;        // wavefronts
 constexpr uint32_t kLinkBlocks = 256;  // workgroups per utterance (frames in turn)
+constexpr uint32_t kSpBWin = 2048;     // sparse utterances: states of one frame held in LDS
+constexpr uint32_t kSpTile = 2048;     // nodes whose live ones are listed together
 
 struct LinkShared {
   BlockScratch bs;
@@ -131,6 +134,125 @@ __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& 
   return n;
 }
 
+// ------------------------------------------------- sparse utterances' links
+
+struct SpLinkShared {
+  BlockScratch bs;
+  uint32_t win[kSpBWin];
+  uint32_t list[kSpTile];  // live nodes of a tile, as offsets from its first node
+  uint32_t pre[kLT], beg[kLT], node[kLT];
+  float cost[kLT];
+  uint32_t cls[kLT];
+};
+
+// The kept emitting links into frame t out of frame t - 1's live nodes (kEps
+// false), or the kept epsilon links of frame t: counted, or written from link
+// `at` on, in the order of their sources' states and arcs.
+template <bool kEps, bool kWrite>
+__device__ __forceinline__ uint32_t sp_run(const DevGraph& g, const LaneDesc& L, SpLinkShared& sh, uint32_t& par, int t,
+                                           const SpFrame& df, uint32_t lb_key, uint64_t at, uint32_t* xmask) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t p0 = L.node_off[kEps ? t : t - 1], p1 = L.node_off[kEps ? t + 1 : t];
+  const float* row = (const float*)L.ll + (size_t)(t > 0 ? t - 1 : 0) * g.P;
+  const uint32_t cut = cost_key(L.cut[t]);
+  uint32_t n = 0;
+  for (uint64_t q0 = p0 & ~31ull; q0 < p1; q0 += kSpTile) {
+    // live nodes among [q0, q0 + kSpTile): 128 bitmap words
+    uint32_t word = 0;
+    if (tid < kSpTile / 32u && q0 + 32u * tid < p1) {
+      const uint64_t b = q0 + 32u * tid;
+      word = L.used[b >> 5];
+      if (b < p0) word &= ~0u << (p0 - b);
+      if (p1 - b < 32u) word &= (1u << (p1 - b)) - 1u;
+    }
+    uint32_t live;
+    uint32_t pos = block_excl_scan<kLWv>((uint32_t)__popc(word), sh.bs, par, &live);
+    while (word) {
+      const uint32_t b = (uint32_t)__ffs(word) - 1u;
+      word &= word - 1u;
+      sh.list[pos++] = 32u * tid + b;
+    }
+    __syncthreads();
+    for (uint32_t l0 = 0; l0 < live; l0 += kLT) {
+      const uint32_t m = live - l0 < (uint32_t)kLT ? live - l0 : (uint32_t)kLT;
+      uint32_t deg = 0, a0 = 0, c = 0, node = 0;
+      float cost = 0.0f;
+      if (tid < m) {
+        node = (uint32_t)(q0 + sh.list[l0 + tid]);
+        const uint32_t s = L.n_state[node];
+        cost = key_cost((uint32_t)(L.n_pack[node] >> 32));
+        const uint4 o0 = g.off[s], o1 = g.off[s + 1];
+        a0 = kEps ? o0.y : o0.x;
+        deg = kEps ? o1.y - o0.y : o1.x - o0.x;
+        if (kEps) {
+          c = g.sclass[s];
+          if (!kWrite) {  // (every live node of frame t once: its forward-backward sums start at 0)
+            L.alpha[node] = 0.0;
+            L.beta[node] = 0.0;
+          }
+        }
+      }
+      uint32_t tot;
+      sh.pre[tid] = block_excl_scan<kLWv>(deg, sh.bs, par, &tot);
+      sh.beg[tid] = a0;
+      sh.cost[tid] = cost;
+      sh.node[tid] = node;
+      sh.cls[tid] = c;
+      __syncthreads();
+      for (uint32_t w0 = 0; w0 < tot; w0 += kLT) {
+        const uint32_t it = w0 + tid;
+        bool in = false;
+        uint32_t j = 0, xb = 0, dn = ~0u, le = kInfKey;
+        uint4 r = make_uint4(0, 0, 0, 0);
+        if (it < tot) {
+          j = search_le(sh.pre, m, it);
+          const uint32_t a = sh.beg[j] + (it - sh.pre[j]);
+          r = kEps ? g.xarc[a] : g.earc[a];
+          dn = sp_lookup<kSpBWin>(L, df, sh.win, r.x);
+          if (dn != ~0u) {
+            const float exd = key_cost(L.extra_key[dn]);
+            const float cd = key_cost((uint32_t)(L.n_pack[dn] >> 32));
+            float x = sh.cost[j];
+            if (!kEps) x = x + -row[(r.z & 0xffffffu) - 1u];
+            x = canon(x + __uint_as_float(r.y));
+            xb = __float_as_uint(x);
+            const uint32_t xk = cost_key(x);
+            le = cost_key(exd + (x - cd));
+            in = xk <= cut && xk < kInfKey && le <= lb_key && le < kInfKey;
+          }
+        }
+        uint32_t nsub;
+        const uint32_t p = n + block_excl_scan<kLWv>(in ? 1u : 0u, sh.bs, par, &nsub);
+        n += nsub;
+        if (!kWrite || !in) continue;
+        L.links[at + p] = make_uint4(r.w, sh.node[j], dn, xb);
+        L.le_key[at + p] = le;
+        if (kEps) {
+          const uint32_t cl = sh.cls[j];
+          L.link_lvl[at + p] = (uint8_t)cl;
+          *xmask |= 1u << (cl < 31u ? cl : 31u);
+        }
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+  }
+  return n;
+}
+
+__device__ __forceinline__ SpFrame sp_dest(const LaneDesc& L, SpLinkShared& sh, int t) {
+  const SpFrame f = sp_frame(L, t, kSpBWin);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < f.m; i += kLT) sh.win[i] = L.n_state[f.n0 + ((uint64_t)i << f.k)];
+  __syncthreads();
+  return f;
+}
+
+union LinkLds {
+  LinkShared dense;
+  SpLinkShared sparse;
+};
+
 // A decode whose forward pass stopped, or whose node store overflowed, gets
 // no links (its status already says so).
 __device__ __forceinline__ bool links_wanted(const LaneDesc& L) {
@@ -139,11 +261,35 @@ __device__ __forceinline__ bool links_wanted(const LaneDesc& L) {
 
 // Per frame: emitting links into link_xoff[t], epsilon links into link_end[t]
 // (counts; the offset kernel turns them into offsets).
-__global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc* __restrict__ lanes) {
-  __shared__ LinkShared sh;
+__global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc* __restrict__ lanes, Params prm) {
+  __shared__ LinkLds lds;
+  LinkShared& sh = lds.dense;
   const LaneDesc& L = lanes[blockIdx.y];
   if (!links_wanted(L)) return;
   uint32_t par = 0;
+  if (sparse_lane(L, prm.flags)) {
+    const uint32_t lb_key = cost_key(prm.lattice_beam);
+    for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
+      uint64_t raw = 0;
+      if (!(prm.flags & kFlagSwept) && L.xmask[t] == 0) {
+        // a frame whose raw links the forward pass has not counted
+        const uint32_t cut = cost_key(L.cut[t]);
+        if (t > 0) raw = link_run<false, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr);
+        raw += link_run<true, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr);
+        __syncthreads();
+      }
+      const SpFrame f = sp_dest(L, lds.sparse, t);
+      const uint32_t ne = t > 0 ? sp_run<false, false>(g, L, lds.sparse, par, t, f, lb_key, 0, nullptr) : 0u;
+      const uint32_t nx = sp_run<true, false>(g, L, lds.sparse, par, t, f, lb_key, 0, nullptr);
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        L.link_xoff[t] = ne;
+        L.link_end[t] = nx;
+        if (raw) atomicAdd((unsigned long long*)&L.info->links, (unsigned long long)raw);
+      }
+    }
+    return;
+  }
   for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
     const uint32_t cut = cost_key(L.cut[t]);
     const uint32_t ne = t > 0 ? link_run<false, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr) : 0u;
@@ -162,7 +308,7 @@ __global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc*
 
 // Per utterance: the frames' link offsets from their counts, the store's
 // capacity check and the link totals.
-__global__ void __launch_bounds__(kLT) k_links_offsets(const LaneDesc* __restrict__ lanes) {
+__global__ void __launch_bounds__(kLT) k_links_offsets(const LaneDesc* __restrict__ lanes, Params prm) {
   __shared__ BlockScratch bs;
   const LaneDesc& L = lanes[blockIdx.x];
   if (!links_wanted(L)) return;
@@ -185,7 +331,8 @@ __global__ void __launch_bounds__(kLT) k_links_offsets(const LaneDesc* __restric
   if (threadIdx.x == 0) {
     L.link_off[T1] = total;
     LaneInfo* I = L.info;
-    I->links = total;
+    // (a sparse utterance's raw links have been counted; it stores its kept ones)
+    if (!sparse_lane(L, prm.flags)) I->links = total;
     I->need_links = total;
     if (total > L.link_cap) {
       I->overflow |= kOvfLinks;
@@ -195,11 +342,24 @@ __global__ void __launch_bounds__(kLT) k_links_offsets(const LaneDesc* __restric
 }
 
 // Per frame: the links, at the frame's offsets; the frame's epsilon levels.
-__global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc* __restrict__ lanes) {
-  __shared__ LinkShared sh;
+__global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc* __restrict__ lanes, Params prm) {
+  __shared__ LinkLds lds;
+  LinkShared& sh = lds.dense;
   const LaneDesc& L = lanes[blockIdx.y];
   if (!links_wanted(L)) return;
   uint32_t par = 0, bad = 0;
+  if (sparse_lane(L, prm.flags)) {
+    const uint32_t lb_key = cost_key(prm.lattice_beam);
+    for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
+      const SpFrame f = sp_dest(L, lds.sparse, t);
+      uint32_t xmask = 0;
+      if (t > 0) (void)sp_run<false, true>(g, L, lds.sparse, par, t, f, lb_key, L.link_off[t], &xmask);
+      (void)sp_run<true, true>(g, L, lds.sparse, par, t, f, lb_key, L.link_xoff[t], &xmask);
+      const uint32_t all = block_or<kLWv>(xmask, lds.sparse.bs, par);
+      if (threadIdx.x == 0) L.xmask[t] = all;
+    }
+    return;
+  }
   for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
     const uint32_t cut = cost_key(L.cut[t]);
     uint32_t xmask = 0;
@@ -211,10 +371,10 @@ __global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc*
   if (bad) L.info->status = kStatusInternal;
 }
 
-void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_links_count, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes);
-  hipLaunchKernelGGL(k_links_offsets, dim3(B), dim3(kLT), 0, s, lanes);
-  hipLaunchKernelGGL(k_links_write, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes);
+void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s) {
+  hipLaunchKernelGGL(k_links_count, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes, prm);
+  hipLaunchKernelGGL(k_links_offsets, dim3(B), dim3(kLT), 0, s, lanes, prm);
+  hipLaunchKernelGGL(k_links_write, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes, prm);
 }
 
 }  // namespace wd

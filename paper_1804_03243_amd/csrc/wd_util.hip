@@ -1,5 +1,6 @@
 // Small per-decode kernels around the decoder: input checks, fills, the lane
 // frame ranges of a stream, and the packing of results for the host.
+#include "wd_cluster.h"
 #include "wd_host.h"
 
 namespace wd {
@@ -75,29 +76,34 @@ struct FrameSet {
   int32_t b0, n, open;
 };
 
-__device__ __forceinline__ void clear_cluster(const LaneDesc& L, uint32_t n) {
+// The headers of a cluster's control block, clean for a launch of the forward
+// pass and of the pruning sweep.
+__device__ __forceinline__ void clear_cluster(const LaneDesc& L) {
   WD_GLOBAL uint32_t* w = (WD_GLOBAL uint32_t*)L.ctl;
   if (!w) return;
-  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) w[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kCtlHead / 4u; i += blockDim.x) {
+    w[i] = 0;
+    w[sizeof(ClusterCtl) / 4u + i] = 0;
+  }
 }
 
 // A workgroup per utterance.
-__global__ void k_set_frames(LaneDesc* lanes, FrameSet f, uint32_t ctl_words) {
+__global__ void k_set_frames(LaneDesc* lanes, FrameSet f) {
   LaneDesc& L = lanes[f.b0 + (int)blockIdx.x];
   if (threadIdx.x == 0) {
     L.T = f.T[blockIdx.x];
     L.t0 = f.t0[blockIdx.x];
     L.open = f.open;
   }
-  clear_cluster(L, ctl_words);
+  clear_cluster(L);
 }
 
-__global__ void k_clear_clusters(const LaneDesc* __restrict__ lanes, uint32_t ctl_words) {
-  clear_cluster(lanes[blockIdx.x], ctl_words);
+__global__ void k_clear_clusters(const LaneDesc* __restrict__ lanes) {
+  clear_cluster(lanes[blockIdx.x]);
 }
 
 void launch_clear_clusters(const LaneDesc* lanes, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_clusters, dim3(B), dim3(128), 0, s, lanes, (uint32_t)(cluster_ctl_clear_bytes() / 4));
+  hipLaunchKernelGGL(k_clear_clusters, dim3(B), dim3(128), 0, s, lanes);
 }
 
 void launch_set_frames(LaneDesc* lanes, int B, const int32_t* T, const int32_t* t0, int32_t open, hipStream_t s) {
@@ -110,7 +116,7 @@ void launch_set_frames(LaneDesc* lanes, int B, const int32_t* T, const int32_t* 
       f.T[i] = T[b0 + i];
       f.t0[i] = t0[b0 + i];
     }
-    hipLaunchKernelGGL(k_set_frames, dim3(f.n), dim3(128), 0, s, lanes, f, (uint32_t)(cluster_ctl_clear_bytes() / 4));
+    hipLaunchKernelGGL(k_set_frames, dim3(f.n), dim3(128), 0, s, lanes, f);
   }
 }
 

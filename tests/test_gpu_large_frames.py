@@ -34,11 +34,14 @@ def noisy(wf):
     return g, wf.Graph(g, 200)
 
 
-def check(wf, oracle_mod, g, graph, L, args, mode="workgroup", debug=True):
+def check(wf, oracle_mod, g, graph, L, args, mode="workgroup"):
     import torch
     print(f"\n[gpu case] large frames S={g['num_states']} T={L.shape[0]} args={args} mode={mode}", flush=True)
-    r = wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, debug=debug, mode=mode)
-    assert_same(r, oracle_mod.decode(g, L, *args, debug=debug), debug=debug)
+    x, o = torch.from_numpy(L).to(graph.device), oracle_mod.decode(g, L, *args, debug=True)
+    # (without the debug outputs the lattice is pruned from the node store)
+    assert_same(wf.decode(graph, x, *args, mode=mode), o)
+    r = wf.decode(graph, x, *args, debug=True, mode=mode)
+    assert_same(r, o, debug=True)
     return r
 
 
@@ -65,6 +68,24 @@ def test_in_and_out(wf, oracle_mod, noisy):
             L[t, rng.choice(200, 3, replace=False)] = -1.0
     r = check(wf, oracle_mod, g, graph, L, (11.0, 3000, 6.0))
     assert r.needed["frame_tokens"] > 2048
+
+
+@pytest.mark.parametrize("lb", [0.0, 0.5, 30.0, float("inf")])
+def test_lattice_beam(wf, oracle_mod, noisy, lb):
+    """From the best path alone to every link: one live node a frame, and all
+    of them."""
+    g, graph = noisy
+    check(wf, oracle_mod, g, graph, flat(9, 200, 13), (11.0, 2500, lb))
+
+
+def test_finals(wf, oracle_mod):
+    """Final weights: some states final; then none of the last tokens' states."""
+    g = graph_of(30_000, 80_000, 100, 0.2, 4, 3)
+    rng = np.random.default_rng(14)
+    for share in (0.3, 0.0):
+        fw = np.where(rng.random(30_000) < share, rng.exponential(1.0, 30_000), np.inf).astype(np.float32)
+        h = dict(g, final_weight=fw)
+        check(wf, oracle_mod, h, wf.Graph(h, 100), flat(7, 100, 15), (13.0, 0, 7.0))
 
 
 def test_ties(wf, oracle_mod):
