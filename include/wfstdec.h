@@ -7,7 +7,7 @@
  * Decoder with Exact Lattice Generation", Interspeech 2018 -- token passing
  * and atomic recombination (Sec. 3.2, Alg. 1), load-balanced arc expansion
  * (Sec. 3.3, Alg. 2), lattice-arc recording (Sec. 3.4), lattice pruning and
- * final merge (Sec. 3.5, also incrementally on a second stream, Sec. 3.1),
+ * final merge (Sec. 3.5),
  * lattice posteriors (Sec. 4.1), the compact exact lattice (Sec. 3.4, on the
  * host), streaming decodes (the integration with acoustic inference the
  * paper leaves to future work, Sec. 5).
@@ -18,9 +18,7 @@
  *  - "device" pointers are HIP device memory owned by the caller (e.g. torch
  *    tensors).  The library borrows them for the duration of the call (a
  *    stream: until wd_stream_end / wd_stream_free returns) and never
- *    allocates device memory itself; its only device resources are one
- *    pruning stream per device (created on first use, kept for the process)
- *    and a few events per chip-wide decode.
+ *    allocates device memory itself.
  *  - Work is enqueued on the caller's stream; wd_decode / wd_decode_batch
  *    return after the results have been copied to host memory.
  *  - Results are deterministic: identical inputs give identical outputs,
@@ -96,20 +94,14 @@ typedef struct {
  * arcs of one token) instead of the static prefix-sum work space.  The
  * result is identical; the flag exists for the A/B comparison. */
 #define WD_FLAG_DYNAMIC_LB 16u
-/* Chip-wide mode prunes the lattice conservatively while decoding, on a
- * second stream of the library's own (Fig. 1 of the paper prunes on a second
- * stream as decoding goes): frames are recorded in windows of 32 into two raw
- * window slots taken in turn; 8 frames after a window's last frame, its links
- * (and those of the 8 frames after it) are swept with the lowest possible
- * extra cost (0) on the 8th frame's tokens, and the window's links that cannot
- * be kept by the final pruning are dropped while the rest are appended to the
- * compacted region of the link store.  Decoding goes on meanwhile and only
- * waits for a window's pruning before it reuses that window's slot.  The link
- * store then holds the compacted region (capacity `links`) plus the two slots
- * (`window_links` each) instead of every raw link.  The result is identical.
- * This flag turns it off (A/B).  Never done with WD_FLAG_DEBUG, which returns
- * the raw lattice.  Decodes on one device share the library's pruning stream
- * and are ordered on it by events. */
+/* Large frames (every frame in chip-wide mode; utterances of many tokens per
+ * frame in one-workgroup mode) prune the lattice without storing the raw one:
+ * a link's extra cost is at least its destination's, so the backward sweep
+ * walks the in-arcs of the nodes within the lattice beam only, and just the
+ * kept links are formed (raw links are counted).  The link store then holds
+ * the kept links (capacity `links`).  This flag forms, stores and sweeps every
+ * raw link instead (A/B; the result is identical), as WD_FLAG_DEBUG does, which
+ * returns them. */
 #define WD_FLAG_NO_INCREMENTAL_PRUNE 32u
 /* Step profile of the one-workgroup forward pass (a measurement aid, off in
  * timed runs; WD_EINVAL in chip-wide mode): a separately compiled copy of the
@@ -150,11 +142,10 @@ typedef struct {
   int64_t frame_tokens;   /* tokens touched in one frame (<= S) */
   int64_t frame_arcs;     /* emitting arcs expanded in one frame */
   int64_t nodes;          /* surviving tokens summed over all frames (< 2^32) */
-  int64_t links;          /* lattice links recorded before pruning (the link store; with
-                             chip-wide incremental pruning its compacted region) */
+  int64_t links;          /* lattice links stored (every raw link, or with large frames the
+                             kept ones: see WD_FLAG_NO_INCREMENTAL_PRUNE) */
   int64_t kept_links;     /* lattice links returned (after pruning; raw links with WD_FLAG_DEBUG) */
-  int64_t window_links;   /* chip-wide incremental pruning: raw links of one 32-frame window
-                             (`links` is then the compacted region); unused otherwise */
+  int64_t window_links;   /* unused (0) */
 } wd_caps;
 
 /* One lattice link of the pruned lattice, i.e. one token-passing operation

@@ -32,7 +32,7 @@ wd_status hip_check(hipError_t e, const char* what) {
 namespace {
 
 struct Caps {
-  uint64_t frame, arcs, nodes, links, kept, raw, words, win;
+  uint64_t frame, arcs, nodes, links, kept, raw, words;
   uint64_t prof;  // step-profile words per utterance (WD_FLAG_PHASES)
   bool chip;      // chip-wide mode
 };
@@ -44,7 +44,8 @@ bool chip_wide_mode(const wd_params* p) {
          (!(p->flags & WD_FLAG_ONE_WORKGROUP) && (p->max_active == 0 || p->max_active >= WD_CHIP_WIDE_MAX_ACTIVE));
 }
 
-bool incremental_prune(const wd_params* p) {
+// Chip-wide decodes prune the lattice from the node store (kFlagSparse).
+bool sparse_chip(const wd_params* p) {
   return chip_wide_mode(p) && !(p->flags & (WD_FLAG_DEBUG | WD_FLAG_NO_INCREMENTAL_PRUNE));
 }
 
@@ -64,9 +65,6 @@ Caps resolve_caps(const wd_graph* g, int32_t max_T, const wd_params* p, const wd
   r.links = (c && c->links > 0) ? (uint64_t)c->links : 4 * r.nodes;
   r.kept = (c && c->kept_links > 0) ? (uint64_t)c->kept_links : std::min<uint64_t>(r.links, 1u << 20);
   r.raw = (p->flags & WD_FLAG_DEBUG) ? r.links : 0;
-  r.win = 0;
-  if (incremental_prune(p))
-    r.win = (c && c->window_links > 0) ? (uint64_t)c->window_links : std::max<uint64_t>(r.links / 4, 1);
   r.words = T1 * (g->nlevels + 1) + 1;
   r.chip = chip_wide_mode(p);
   // (one row per frame, then one for the lattice pass)
@@ -84,7 +82,8 @@ struct Regions {
   unsigned long long* slot;
   uint32_t* bitmap;
   uint32_t* used;
-  void* grid;    // chip-wide: GridLanes; one-workgroup: the clusters' control blocks
+  void* grid;    // chip-wide: GridLanes
+  void* ctl;     // the clusters' control blocks
   uint64_t grid_bytes;
   uint64_t bitmap_words, used_words;
   uint64_t total;
@@ -107,6 +106,7 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   // (one size, so that a workspace does not depend on the mode)
   R.grid_bytes = align_up(std::max(grid_lane_bytes(), cluster_ctl_bytes()), 256);
   R.grid = take(R.grid_bytes);
+  R.ctl = c.chip ? take(align_up(cluster_ctl_bytes(), 256)) : R.grid;  // (one workgroup: nothing else there)
   R.bitmap_words = (S + 31) / 32;
   R.used_words = (c.nodes + 31) / 32 + 1;
   char* slot = take(8 * S);
@@ -131,7 +131,7 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   char* n_state = take(4 * c.nodes);
   char* n_pack = take(8 * c.nodes);
   char* n_pred = take(4 * c.nodes);
-  const uint64_t nlink = c.links + grid_window_slots() * c.win;  // compacted region + raw window slots
+  const uint64_t nlink = c.links;
   char* links = take(16 * nlink);
   char* link_lvl = take(nlink);
   char* node_off = take(8 * T2);
@@ -167,14 +167,13 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
       L.cand_cap = c.arcs;
       L.node_cap = c.nodes;
       L.link_cap = c.links;
-      L.win_cap = c.win;
       L.kept_cap = c.kept;
       L.raw_cap = c.raw;
       L.word_cap = c.words;
       L.slot = (decltype(L.slot))at(slot, 8 * S);
       L.idx = c.chip ? (decltype(L.idx))at(idx, 4 * S) : nullptr;
       L.slot2 = c.chip ? nullptr : (decltype(L.slot2))at(slot2, 8 * S);
-      L.ctl = c.chip ? nullptr : (decltype(L.ctl))at((char*)R.grid, R.grid_bytes);
+      L.ctl = (decltype(L.ctl))at((char*)R.ctl, c.chip ? align_up(cluster_ctl_bytes(), 256) : R.grid_bytes);
       L.bitmap = (decltype(L.bitmap))at(bitmap, 4 * R.bitmap_words);
       L.bucket = c.chip ? (decltype(L.bucket))at(bucket, 4 * S) : nullptr;
       L.touched = (decltype(L.touched))at(touched, 4 * c.frame);
@@ -270,7 +269,7 @@ extern "C" wd_status wd_workspace_bytes(const wd_graph* g, int32_t lanes, int32_
     caps_out->nodes = (int64_t)c.nodes;
     caps_out->links = (int64_t)c.links;
     caps_out->kept_links = (int64_t)c.kept;
-    caps_out->window_links = (int64_t)c.win;
+    caps_out->window_links = 0;
   }
   return WD_OK;
 }
@@ -290,11 +289,9 @@ struct wd_stream {
   std::vector<int32_t> next;  // first frame not yet decoded
   hipStream_t s = nullptr;
   bool chip = false, open = false;
-  GridRun gr;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
 
   ~wd_stream() {
-    grid_release(&gr);
     for (auto& e : ev)
       if (e) (void)hipEventDestroy(e);
   }
@@ -348,7 +345,10 @@ static wd_status run_setup(wd_stream* run, const wd_graph* g, int32_t B, const f
       if ((st = hip_check(hipEventCreate(&e), "event"))) return st;
   if (run->ev[0]) (void)hipEventRecord(run->ev[0], s);
   run->chip = chip_wide_mode(p);
-  if (run->chip) return grid_begin(&run->gr, R.desc, R.grid, B, incremental_prune(p), R.bad, s);
+  if (run->chip) {
+    if (sparse_chip(p)) run->prm.flags |= kFlagSparse;
+    grid_begin(R.desc, R.grid, B, R.bad, s);
+  }
   return WD_OK;
 }
 
@@ -366,7 +366,7 @@ static wd_status run_frames(wd_stream* run, bool update) {
       lo = std::min(lo, run->next[b]);
       hi = std::max(hi, run->T[b]);
     }
-    st = grid_frames(&run->gr, run->g->dg, R.desc, R.grid, B, run->prm, R.bad, lo, hi, s);
+    grid_frames(run->g->dg, R.desc, R.grid, B, run->prm, R.bad, lo, hi, s);
   } else {
     launch_forward(run->g->dg, R.desc, B, run->prm, R.bad, s);
   }
@@ -447,12 +447,12 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
   const int B = run->B;
   const wd_params* p = &run->p;
   wd_status st;
-  if (run->chip && (st = grid_end(&run->gr, R.desc, R.grid, B, s))) return st;
+  if (run->chip) grid_end(R.desc, R.grid, B, s);
   if (run->ev[1]) (void)hipEventRecord(run->ev[1], s);
   if (run->chip) {
-    launch_grid_sweep(run->g->dg, R.desc, R.grid, B, run->max_T, p->lattice_beam, s);
     Params lp = run->prm;
     lp.flags |= kFlagSwept;
+    launch_grid_sweep(run->g->dg, R.desc, R.grid, B, run->max_T, lp, s);
     launch_lattice(run->g->dg, R.desc, B, lp, s);
     launch_grid_nodes(R.desc, R.grid, B, s);
   } else {

@@ -158,6 +158,9 @@ enum : uint32_t { kOvfFrame = 1, kOvfArcs = 2, kOvfNodes = 4, kOvfLinks = 8, kOv
 // Params::flags bit set by the host for the lattice kernel when the pruning
 // sweep already ran as chip-wide kernels.
 constexpr uint32_t kFlagSwept = 1u << 30;
+// Params::flags bit set by the host for chip-wide decodes whose lattice is
+// pruned from the node store: the forward pass only counts the raw links.
+constexpr uint32_t kFlagSparse = 1u << 29;
 // LaneInfo::status value for an internal consistency failure caught by a
 // kernel's own bounds checks (reported as WD_EDEVICE).
 constexpr int32_t kStatusInternal = 5;
@@ -204,7 +207,6 @@ struct LaneDesc {
   int32_t open;                // streaming: more frames may follow
   int32_t pad0;
   uint64_t frame_cap, cand_cap, node_cap, link_cap, kept_cap, word_cap;
-  uint64_t win_cap;            // incremental pruning: links of one raw window slot (0: off)
   // per-frame scratch
   WD_GLOBAL unsigned long long* slot;    // [S] packed (cost key, arc id); kEmpty between frames
   // one-workgroup mode: the slots of odd frames (large frames only; both slot
@@ -233,8 +235,6 @@ struct LaneDesc {
   WD_GLOBAL uint32_t* n_state;           // [node_cap]
   WD_GLOBAL unsigned long long* n_pack;  // [node_cap] (cost key, predecessor arc)
   WD_GLOBAL uint32_t* n_pred;            // [node_cap] predecessor node
-  // link store [link_cap + 3*win_cap]: with incremental pruning, the compacted
-  // region [0, link_cap) then three raw window slots of win_cap links each
   WD_GLOBAL uint4* links;                // {arc, src node, dst node, x bits}
   WD_GLOBAL uint8_t* link_lvl;           // epsilon level of the source (epsilon links)
   WD_GLOBAL uint64_t* node_off;          // [T+2]
@@ -247,7 +247,7 @@ struct LaneDesc {
   WD_GLOBAL float* cut;                  // [T+1]
   // lattice pass
   WD_GLOBAL uint32_t* extra_key;         // [node_cap]
-  WD_GLOBAL uint32_t* le_key;            // [link_cap + 3*win_cap]
+  WD_GLOBAL uint32_t* le_key;            // [link_cap]
   WD_GLOBAL double* alpha;               // [node_cap] forward sums Sa (linear domain)
   WD_GLOBAL double* beta;                // [node_cap] backward sums Sb (linear domain)
   WD_GLOBAL uint32_t* used;              // [ceil(node_cap/32)+1] lattice-node bitmap

@@ -14,8 +14,6 @@
 // identical.  The backward pruning sweep of Sec. 3.5 has a chip-wide form too.
 // Every kernel reads the frame's sizes from device memory, so the host never
 // waits between frames; an utterance whose status is set skips the rest.
-#include <mutex>
-
 #include "wd_block.h"
 #include "wd_host.h"
 #include "../../include/wfstdec.h"
@@ -26,28 +24,6 @@ constexpr int kGT = 256;          // threads per workgroup
 constexpr int kGW = kGT / 64;     // wavefronts per workgroup
 constexpr uint32_t kGB = 1024;    // workgroups per utterance
 constexpr uint32_t kSeg = 4096;   // frontier prefix sums a workgroup keeps in LDS
-
-// Incremental pruning runs in windows of this many frames, recorded in
-// kSlots raw slots in turn; its sweep kernels use a quarter of the
-// workgroups, leaving room for the decoding kernels.
-constexpr int kPruneEvery = 32;
-// A window is pruned kLookahead frames after its last frame (the sweep runs
-// back from there), in one of kSlots raw slots.
-constexpr int kLookahead = 8;
-constexpr uint32_t kSlots = kLookahead < kPruneEvery ? 2u : 3u;
-constexpr uint32_t kPB = kGB / 4;
-
-// Incremental pruning state of one utterance, written only by the kernels on
-// the pruning stream and, once the host has made the decoding stream wait for
-// them, by the last window's gather.
-struct PruneLane {
-  uint64_t kend;      // links in the compacted region (still counted after an overflow)
-  uint32_t go;        // the current window is pruned
-  uint32_t ovf;       // the compacted region overflowed
-  uint32_t next;      // first frame not yet pruned
-  uint32_t pad0;
-  unsigned long long part[kGB + 1];  // kept links per workgroup, then their prefix
-};
 
 // Per-utterance state carried from kernel to kernel.
 struct GridLane {
@@ -67,13 +43,12 @@ struct GridLane {
   uint32_t sel_active, sel_rank, sel_prefix, sel_less, sel_bits;
   uint32_t xmask;
   uint32_t final_used, best_total_key;
+  unsigned long long eps_frame;  // the frame's epsilon arcs | links counted by the closure << 32
   unsigned long long best_total;  // (final cost key, node offset) of the best end token
   uint64_t node_base, node_base_prev, link_base;
   uint64_t arcs, eps_arcs, tokens, max_tokens, need_frame, need_arcs;
   uint64_t raw_total;              // links ever recorded
-  uint64_t slot_lo, slot_hi;       // where links go: the whole store, or the window's slot
-  uint64_t need_win;               // largest occupancy of the store (or of a slot)
-  PruneLane pr;
+  uint64_t need_links;             // link store used
   uint32_t nb[kMaxLevels + 1];
   uint32_t hist[kHistBins];
   // per-workgroup partial sums, then their exclusive prefix (+ total at kGB):
@@ -238,17 +213,12 @@ __global__ void __launch_bounds__(kGT) k_g_scan(const LaneDesc* __restrict__ lan
 // ---------------------------------------------------------------- forward pass
 
 __global__ void k_g_init(const LaneDesc* __restrict__ lanes, GridLane* gl, const uint32_t* __restrict__ bad) {
-  const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
   uint32_t* w = reinterpret_cast<uint32_t*>(&G);
   for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(GridLane) / 4); i += blockDim.x) w[i] = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     G.hist_ok = 1;
-    // with incremental pruning, frames 0..31 go to the first window slot
-    G.slot_lo = L.win_cap ? L.link_cap : 0;
-    G.slot_hi = L.win_cap ? L.link_cap + L.win_cap : L.link_cap;
-    G.link_base = G.slot_lo;
     if (bad[blockIdx.y]) {
       G.status = 1;  // WD_EINVAL
       G.stop = 1;
@@ -406,6 +376,7 @@ __global__ void __launch_bounds__(kGT) k_g_expand(DevGraph g, const LaneDesc* __
   if (!expand_begin(g, L, G, prm, t, s, &ub)) return;
   const uint32_t W = G.W, n_prev = G.n_prev;
   const uint64_t nbp = G.node_base_prev;
+  const bool sparse = (prm.flags & kFlagSparse) != 0;
   const float* row = L.ll + (size_t)(t - 1) * g.P;
   uint64_t blo, bhi;
   chunk(W, blockIdx.x, &blo, &bhi);
@@ -430,7 +401,8 @@ __global__ void __launch_bounds__(kGT) k_g_expand(DevGraph g, const LaneDesc* __
           my_best = xk < my_best ? xk : my_best;
           if (old == kEmpty) stage_touch(ts, G, L, g, r.x, r.z >> 24);
         }
-        L.cand[w] = make_uint4(r.w, (uint32_t)(nbp + i), r.x, __float_as_uint(x));
+        if (sparse) ((WD_GLOBAL uint32_t*)L.cand)[w] = xk;  // (the link count's input)
+        else L.cand[w] = make_uint4(r.w, (uint32_t)(nbp + i), r.x, __float_as_uint(x));
       }
       stage_flush(ts, G, L, g);
     }
@@ -462,6 +434,7 @@ __global__ void __launch_bounds__(kGT) k_g_expand_dyn(DevGraph g, const LaneDesc
   if (!expand_begin(g, L, G, prm, t, s, &ub)) return;
   const uint32_t n_prev = G.n_prev;
   const uint64_t nbp = G.node_base_prev;
+  const bool sparse = (prm.flags & kFlagSparse) != 0;
   const float* row = L.ll + (size_t)(t - 1) * g.P;
   stage_reset(ts, g.nlevels);
   __syncthreads();
@@ -488,7 +461,8 @@ __global__ void __launch_bounds__(kGT) k_g_expand_dyn(DevGraph g, const LaneDesc
           my_best = xk < my_best ? xk : my_best;
           if (old == kEmpty) stage_touch(ts, G, L, g, r.x, r.z >> 24);
         }
-        L.cand[w0 + j] = make_uint4(r.w, (uint32_t)(nbp + i), r.x, __float_as_uint(x));
+        if (sparse) ((WD_GLOBAL uint32_t*)L.cand)[w0 + j] = xk;
+        else L.cand[w0 + j] = make_uint4(r.w, (uint32_t)(nbp + i), r.x, __float_as_uint(x));
       }
     }
   }
@@ -514,7 +488,7 @@ __global__ void __launch_bounds__(kGT) k_g_level(DevGraph g, const LaneDesc* __r
   __shared__ GScratch s;
   __shared__ TouchStage ts;
   __shared__ uint32_t t_beg[kGT], t_ex[kGT], t_key[kGT];
-  __shared__ uint32_t t_tot;
+  __shared__ uint32_t t_tot, n_link;
   const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
   if (G.stop) return;
@@ -528,6 +502,10 @@ __global__ void __launch_bounds__(kGT) k_g_level(DevGraph g, const LaneDesc* __r
   const uint32_t kcutb = cost_key(key_cost(G.best_key) + prm.beam);
   const uint32_t* bk = L.bucket + g.level_base[lvl];
   stage_reset(ts, g.nlevels);
+  if (threadIdx.x == 0) n_link = 0;
+  // (without max-active the beam cutoff is the frame's cutoff, and a token is
+  // final when its level is relaxed: every arc within it is a lattice link)
+  uint32_t links = 0;
   unsigned long long eps = 0;
   for (uint32_t base = blockIdx.x * tile; base < n; base += kGB * tile) {
     const uint32_t i = base + threadIdx.x;
@@ -574,12 +552,17 @@ __global__ void __launch_bounds__(kGT) k_g_level(DevGraph g, const LaneDesc* __r
       const uint4 r = g.xarc[t_beg[j] + (w - t_ex[j])];
       const uint32_t xk = cost_key(canon(key_cost(t_key[j]) + __uint_as_float(r.y)));
       if (xk > kcutb || xk >= kInfKey) continue;
+      ++links;
       const unsigned long long old = atomicMin(&L.slot[r.x], pack_tok(xk, r.w));
       if (old == kEmpty) stage_touch(ts, G, L, g, r.x, r.z);
     }
     stage_flush(ts, G, L, g);
   }
-  if (threadIdx.x == 0 && eps) atomicAdd((unsigned long long*)&G.eps_arcs, eps);
+  // one add for both counts (and one per wavefront in LDS)
+  const uint32_t wl = wave_incl_scan(links);
+  if (lane_id() == 63u && wl) (void)atomicAdd(&n_link, wl);
+  __syncthreads();
+  if (threadIdx.x == 0 && eps) atomicAdd(&G.eps_frame, eps | ((unsigned long long)n_link << 32));
 }
 
 // A frame without max-active whose touched states are more than one in 32 of
@@ -793,7 +776,7 @@ __global__ void __launch_bounds__(kGT) k_g_mark(const LaneDesc* __restrict__ lan
 
 // Kept states per workgroup chunk of the bitmap; node capacity check.
 __global__ void __launch_bounds__(kGT) k_g_bits(DevGraph g, const LaneDesc* __restrict__ lanes, GridLane* gl,
-                                                Params prm) {
+                                                Params prm, int t) {
   __shared__ GScratch s;
   const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
@@ -841,6 +824,18 @@ __global__ void __launch_bounds__(kGT) k_g_bits(DevGraph g, const LaneDesc* __re
   }
   c = gsum64(c, s);
   if (threadIdx.x == 0) G.part[0][blockIdx.x] = c;
+  if ((prm.flags & kFlagSparse) && prm.max_active == 0) {
+    // the frame's emitting links: candidates within the cutoff (with
+    // max-active the link count kernel does this)
+    uint64_t wlo, whi;
+    chunk(t > 0 ? G.W : 0u, blockIdx.x, &wlo, &whi);
+    const WD_GLOBAL uint32_t* cand = (const WD_GLOBAL uint32_t*)L.cand;
+    const uint32_t cut = G.kcutb;
+    unsigned long long n = 0;
+    for (uint64_t i = wlo + threadIdx.x; i < whi; i += kGT) n += cand[i] <= cut && cand[i] < kInfKey;
+    n = gsum64(n, s);
+    if (threadIdx.x == 0) G.part[2][blockIdx.x] = n;
+  }
 }
 
 // The frontier in state order: node store, frontier arrays, idx[state] = node
@@ -879,6 +874,7 @@ __global__ void __launch_bounds__(kGT) k_g_compact(DevGraph g, const LaneDesc* _
   }
   const uint32_t best = G.best_key;
   const bool in_slot = prm.max_active == 0;  // the kept tokens are still in their slots
+  const bool links = !(prm.flags & kFlagSparse), eps = links || prm.max_active > 0;
   unsigned long long deg = 0;
   constexpr uint32_t per = kCW / kGT;
   for (uint64_t r0 = blo; r0 < bhi; r0 += kCW) {
@@ -917,21 +913,24 @@ __global__ void __launch_bounds__(kGT) k_g_compact(DevGraph g, const LaneDesc* _
       if (store) {
         L.n_state[node] = st;
         L.n_pack[node] = v;
-        L.n_pred[node] = kNoArc;
+        if (links) L.n_pred[node] = kNoArc;
       }
-      L.idx[st] = (uint32_t)node;
-      L.f_state[p] = st;
       L.f_key[p] = (uint32_t)(v >> 32);
-      L.f_arc[p] = (uint32_t)v;
+      if (links) {  // (read by the link kernels only)
+        L.idx[st] = (uint32_t)node;
+        L.f_arc[p] = (uint32_t)v;
+        L.f_cls[p] = g.sclass[st];
+      }
       if ((uint32_t)(v >> 32) == best) atomicMin(&G.best_pos, (uint32_t)p);
-      // the token's arc ranges, its degrees for now (the degree kernel turns
-      // them into prefix sums) and its epsilon level
+      // the token's arc ranges and its degrees for now (the degree kernel
+      // turns them into prefix sums)
       const uint4 o0 = g.off[st], o1 = g.off[st + 1];
       L.f_ebeg[p] = o0.x;
-      L.f_xbeg[p] = o0.y;
       L.f_edeg[p] = o1.x - o0.x;
-      L.f_xdeg[p] = o1.y - o0.y;
-      L.f_cls[p] = g.sclass[st];
+      if (eps) {
+        L.f_xbeg[p] = o0.y;
+        L.f_xdeg[p] = o1.y - o0.y;
+      }
       deg += ((unsigned long long)(o1.y - o0.y) << 32) | (o1.x - o0.x);
     }
     pos0 += tot;
@@ -943,8 +942,7 @@ __global__ void __launch_bounds__(kGT) k_g_compact(DevGraph g, const LaneDesc* _
 
 // Degree prefix sums of the frontier: each workgroup rescans the degrees of
 // the frontier range it compacted.
-__global__ void __launch_bounds__(kGT) k_g_degrees(DevGraph g, const LaneDesc* __restrict__ lanes,
-                                                   GridLane* gl) {
+__global__ void __launch_bounds__(kGT) k_g_degrees(const LaneDesc* __restrict__ lanes, GridLane* gl, Params prm) {
   __shared__ GScratch s;
   const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
@@ -956,14 +954,16 @@ __global__ void __launch_bounds__(kGT) k_g_degrees(DevGraph g, const LaneDesc* _
   const uint32_t n = (uint32_t)n_all;
   uint64_t lo, hi;
   sub_chunk(blo, bhi, &lo, &hi);
+  // (the epsilon degrees are read by the link kernels only)
+  const bool eps = !(prm.flags & kFlagSparse) || prm.max_active > 0;
   unsigned long long c = 0;
-  for (uint64_t p = lo; p < hi; ++p) c += ((unsigned long long)L.f_xdeg[p] << 32) | L.f_edeg[p];
+  for (uint64_t p = lo; p < hi; ++p) c += ((unsigned long long)(eps ? L.f_xdeg[p] : 0u) << 32) | L.f_edeg[p];
   unsigned long long tot;
   unsigned long long q = d_before + gexcl64(c, s, &tot);
   for (uint64_t p = lo; p < hi; ++p) {
-    const unsigned long long d = ((unsigned long long)L.f_xdeg[p] << 32) | L.f_edeg[p];
+    const unsigned long long d = ((unsigned long long)(eps ? L.f_xdeg[p] : 0u) << 32) | L.f_edeg[p];
     L.f_edeg[p] = (uint32_t)q;
-    L.f_xdeg[p] = (uint32_t)(q >> 32);
+    if (eps) L.f_xdeg[p] = (uint32_t)(q >> 32);
     q += d;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -985,7 +985,11 @@ struct LinkItem {
 };
 
 __device__ __forceinline__ bool link_item(const DevGraph& g, const LaneDesc& L, uint32_t W, uint32_t cut,
-                                          uint32_t it, const Seg& sg, const uint32_t* seg, LinkItem* o) {
+                                          uint32_t it, const Seg& sg, const uint32_t* seg, bool sparse, LinkItem* o) {
+  if (it < W && sparse) {
+    const uint32_t xk = ((const WD_GLOBAL uint32_t*)L.cand)[it];
+    return xk <= cut && xk < kInfKey;
+  }
   if (it < W) {
     const uint4 c = L.cand[it];
     const uint32_t xk = cost_key(__uint_as_float(c.w));
@@ -997,7 +1001,7 @@ __device__ __forceinline__ bool link_item(const DevGraph& g, const LaneDesc& L, 
   const uint4 r = g.xarc[L.f_xbeg[p] + (e - L.f_xdeg[p])];
   const float x = canon(key_cost(L.f_key[p]) + __uint_as_float(r.y));
   const uint32_t xk = cost_key(x);
-  *o = LinkItem{r.w, p, r.x, __float_as_uint(x), L.f_cls[p]};  // src: frontier position
+  *o = LinkItem{r.w, p, r.x, __float_as_uint(x), sparse ? 0u : L.f_cls[p]};  // src: frontier position
   return xk <= cut && xk < kInfKey;
 }
 
@@ -1010,7 +1014,7 @@ __device__ __forceinline__ Seg link_seg(const LaneDesc& L, uint32_t W, uint32_t 
 }
 
 __global__ void __launch_bounds__(kGT) k_g_link_count(DevGraph g, const LaneDesc* __restrict__ lanes,
-                                                      GridLane* gl, int t) {
+                                                      GridLane* gl, Params prm, int t) {
   __shared__ GScratch s;
   __shared__ uint32_t seg[kSeg];
   __shared__ uint32_t rng[2];
@@ -1025,7 +1029,7 @@ __global__ void __launch_bounds__(kGT) k_g_link_count(DevGraph g, const LaneDesc
     const Seg sg = link_seg(L, W, n, blo, bhi, seg, rng);
     for (uint64_t it = blo + threadIdx.x; it < bhi; it += kGT) {
       LinkItem o;
-      if (link_item(g, L, W, cut, (uint32_t)it, sg, seg, &o)) c += it < W ? 1ull : (1ull << 32);
+      if (link_item(g, L, W, cut, (uint32_t)it, sg, seg, (prm.flags & kFlagSparse) != 0, &o)) c += it < W ? 1ull : (1ull << 32);
     }
   }
   c = gsum64(c, s);
@@ -1056,7 +1060,7 @@ __global__ void __launch_bounds__(kGT) k_g_link_write(DevGraph g, const LaneDesc
   part_prefix(G.part[2], blockIdx.x, s, &run, &all);
   const uint64_t nE = (uint32_t)all;
   const uint64_t lb = G.link_base, nb = G.node_base;
-  if (!G.hist_ok || lb + nE + (all >> 32) > G.slot_hi) return;
+  if (!G.hist_ok || lb + nE + (all >> 32) > L.link_cap) return;
   uint64_t blo, bhi;
   chunk((uint64_t)W + G.W_eps, blockIdx.x, &blo, &bhi);
   if (blo >= bhi) return;
@@ -1070,7 +1074,7 @@ __global__ void __launch_bounds__(kGT) k_g_link_write(DevGraph g, const LaneDesc
 #pragma unroll
     for (uint32_t k = 0; k < kLinkBatch; ++k) {
       const uint64_t it = base + k * kGT + threadIdx.x;
-      on[k] = it < bhi && link_item(g, L, W, cut, (uint32_t)it, sg, seg, &o[k]);
+      on[k] = it < bhi && link_item(g, L, W, cut, (uint32_t)it, sg, seg, false, &o[k]);
       be[k] = __ballot(on[k] && it < W);
       bx[k] = __ballot(on[k] && it >= W);
       if (lane_id() == 0) {
@@ -1137,7 +1141,7 @@ __global__ void __launch_bounds__(kGT) k_g_link_write(DevGraph g, const LaneDesc
 }
 
 // End of frame t: per-frame records, counters, and the state of frame t+1.
-__global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lanes, GridLane* gl, int t) {
+__global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lanes, GridLane* gl, Params prm, int t) {
   __shared__ GScratch s;
   const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
@@ -1153,38 +1157,40 @@ __global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lane
     return;
   }
   const uint32_t n = G.n_keep;
-  const uint64_t nE = (uint32_t)all, nX = all >> 32;
-  const uint64_t end = G.link_base + nE + nX;
-  G.raw_total += nE + nX;
-  if (end - G.slot_lo > G.need_win) G.need_win = end - G.slot_lo;
-  if (G.hist_ok && end > G.slot_hi) {
-    G.hist_ok = 0;
-    G.ovf |= kOvfLinks;
-  }
   L.node_off[t] = G.node_base;
   L.node_off[t + 1] = G.node_base + n;
-  L.link_off[t] = G.link_base;
-  L.link_xoff[t] = G.link_base + nE;
-  L.link_end[t] = end;
-  L.link_off[t + 1] = end;
-  L.xmask[t] = G.xmask;
+  const uint64_t nE = (uint32_t)all;
+  if (prm.flags & kFlagSparse) {
+    // (counted only; the kept links are formed after the forward pass)
+    G.raw_total += nE + (prm.max_active > 0 ? all >> 32 : G.eps_frame >> 32);
+  } else {
+    const uint64_t end = G.link_base + nE + (all >> 32);
+    G.raw_total += end - G.link_base;
+    G.need_links = end;
+    if (G.hist_ok && end > L.link_cap) {
+      G.hist_ok = 0;
+      G.ovf |= kOvfLinks;
+    }
+    L.link_off[t] = G.link_base;
+    L.link_xoff[t] = G.link_base + nE;
+    L.link_end[t] = end;
+    L.link_off[t + 1] = end;
+    L.xmask[t] = G.xmask;
+    G.link_base = end;
+  }
   L.best[t] = key_cost(G.best_key);
   L.cutb[t] = key_cost(G.kcutb);
   L.cut[t] = key_cost(G.cut_key);
   G.tokens += n;
   G.max_tokens = n > G.max_tokens ? n : G.max_tokens;
-  G.link_base = end;
-  if (L.win_cap && (t + 1) % kPruneEvery == 0) {  // next window: the next slot
-    G.slot_lo = L.link_cap + (((uint32_t)(t + 1) / kPruneEvery) % kSlots) * L.win_cap;
-    G.slot_hi = G.slot_lo + L.win_cap;
-    G.link_base = G.slot_lo;
-  }
   G.node_base_prev = G.node_base;
   G.node_base += n;
   G.n_prev = n;
   G.W = G.W_next;
   G.n_touched = 0;
   G.n_surv = 0;
+  G.eps_arcs += (uint32_t)G.eps_frame;
+  G.eps_frame = 0;
   G.xmask = 0;
   G.best_key = 0xffffffffu;  // the next frame's expansion takes the minimum
   G.disp = 0;
@@ -1199,18 +1205,19 @@ __global__ void k_g_finish(const LaneDesc* __restrict__ lanes, GridLane* gl) {
   if (threadIdx.x != 0 || G.status == 1) return;
   LaneInfo* info = L.info;
   int32_t status = G.status;
-  const uint32_t ovf = G.ovf | (G.pr.ovf ? (uint32_t)kOvfLinks : 0u);
+  const uint32_t ovf = G.ovf;
   if (status == 0 && (ovf & (kOvfNodes | kOvfLinks))) status = 4;
   info->status = status;
   info->frames_done = (int32_t)G.frames;
   info->overflow = ovf;
-  info->arcs_expanded = G.arcs + G.eps_arcs;
-  info->eps_arcs = G.eps_arcs;
+  const uint64_t eps = G.eps_arcs + (uint32_t)G.eps_frame;  // (with those of a frame that stopped)
+  info->arcs_expanded = G.arcs + eps;
+  info->eps_arcs = eps;
   info->tokens = G.tokens;
   info->max_tokens = G.max_tokens;
   info->links = G.raw_total;
-  info->need_links = L.win_cap ? G.pr.kend : G.need_win;
-  info->need_window = L.win_cap ? G.need_win : 0;
+  info->need_links = G.need_links;  // (sparse: set by the link kernels)
+  info->need_window = 0;
   info->need_frame_tokens = G.need_frame;
   info->need_frame_arcs = G.need_arcs;
 }
@@ -1290,12 +1297,11 @@ __global__ void __launch_bounds__(kGT) k_gs_init(DevGraph g, const LaneDesc* __r
 // Relaxes links into their source's extra cost: the emitting links that
 // leave frame t (emit != 0), or frame t's epsilon links whose source is on
 // level `lvl`.  extra(link) = extra(dst) + (x - cost(dst)).
-// `prune`: the conservative sweep of incremental pruning, while decoding.
 __global__ void __launch_bounds__(kGT) k_gs_relax(const LaneDesc* __restrict__ lanes, const GridLane* gl,
-                                                  int t, int emit, int lvl, int prune) {
+                                                  int t, int emit, int lvl) {
   const LaneDesc& L = lanes[blockIdx.y];
   const GridLane& G = gl[blockIdx.y];
-  if (prune ? !G.pr.go : (L.info->status != 0 || t > L.T || G.best_total_key >= kInfKey)) return;
+  if (L.info->status != 0 || t > L.T || G.best_total_key >= kInfKey) return;
   uint64_t k0, k1;
   if (emit) {
     if (t == L.T) return;
@@ -1381,11 +1387,12 @@ __global__ void __launch_bounds__(kGT) k_gk_write(DevGraph g, const LaneDesc* __
 
 // The linear-domain forward and backward sums of every node start at 0 (the
 // lattice kernel then only adds into the nodes that kept links reach).
-__global__ void __launch_bounds__(kGT) k_gs_fill_ab(const LaneDesc* __restrict__ lanes) {
+__global__ void __launch_bounds__(kGT) k_gs_fill_ab(const LaneDesc* __restrict__ lanes, bool fill) {
   const LaneDesc& L = lanes[blockIdx.y];
   if (L.info->status != 0) return;
   const uint64_t n = L.node_off[L.T + 1];
-  for (uint64_t i = (uint64_t)blockIdx.x * kGT + threadIdx.x; i < n; i += (uint64_t)kGB * kGT) {
+  // (`fill` false: the link kernels have done it for the nodes that count)
+  for (uint64_t i = (uint64_t)blockIdx.x * kGT + threadIdx.x; fill && i < n; i += (uint64_t)kGB * kGT) {
     L.alpha[i] = 0.0;
     L.beta[i] = 0.0;
   }
@@ -1470,192 +1477,9 @@ __global__ void __launch_bounds__(kGT) k_gn_write(const LaneDesc* __restrict__ l
   }
 }
 
-// ------------------------------------------------------ incremental pruning
-//
-// Frames are recorded in windows of kPruneEvery frames, window j in raw slot
-// j mod kSlots of the link store.  Window j = [t0, t1] is pruned once frame
-// tb = t1 + kLookahead is done too, by the pruning stream while decoding goes
-// on: the nodes of frame tb get extra cost 0, the lowest an extra cost can
-// be, and the sweep of Sec. 3.5 back from tb over window j then gives every
-// node and link of window j a lower bound of its final extra cost (the
-// recursion is monotone in the frame-tb values), one that already knows which
-// paths die or fall behind within the kLookahead frames after the window.  A
-// link of window j whose bound is above the lattice beam (or +inf: it leads
-// nowhere) cannot be kept by the final pruning, and nothing it could decide
-// survives either: a node's final extra cost is the minimum over its
-// out-links, reached by a link within the beam whenever it matters.  Window
-// j's other links are appended, in order, to the compacted region
-// [0, link_cap), and its frame offsets move with them.  Decoding waits for
-// window j's pruning only before window j + kSlots reuses its slot.  At the
-// end, the frames after the last pruned window (at most two windows, the last
-// of them partial) are gathered behind the compacted region, which then holds
-// every frame in order, as the link store does without incremental pruning.
-//
-// Decoding and pruning touch disjoint data while they overlap: the window's
-// links, link offsets, extra costs and le_key belong to the pruning stream;
-// node offsets and costs of the window are final and only read.  The gate
-// `go` is taken once per window from the decoding state: the window's frames
-// are decoded (frames only grows), and status and hist_ok still say OK (they
-// only ever change to a failure, whose result is not returned).
-
-__global__ void k_gp_go(GridLane* gl, int t) {
-  GridLane& G = gl[blockIdx.y];
-  if (threadIdx.x != 0) return;
-  const int32_t status = __hip_atomic_load(&G.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const uint32_t ok = __hip_atomic_load(&G.hist_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const uint32_t done = __hip_atomic_load(&G.frames, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  G.pr.go = ((uint32_t)t < done && status == 0 && ok) ? 1u : 0u;
-}
-
-__global__ void __launch_bounds__(kGT) k_gp_init(const LaneDesc* __restrict__ lanes, const GridLane* gl,
-                                                 int t0, int t) {
-  const LaneDesc& L = lanes[blockIdx.y];
-  const GridLane& G = gl[blockIdx.y];
-  if (!G.pr.go) return;
-  const uint64_t n0 = L.node_off[t0], nt = L.node_off[t], n1 = L.node_off[t + 1];
-  for (uint64_t n = n0 + (uint64_t)blockIdx.x * kGT + threadIdx.x; n < n1; n += (uint64_t)gridDim.x * kGT)
-    L.extra_key[n] = n >= nt ? cost_key(0.0f) : kInfKey;
-}
-
-__device__ __forceinline__ bool gp_kept(const LaneDesc& L, uint64_t k, uint32_t lb_key) {
-  const uint32_t le = L.le_key[k];
-  return le <= lb_key && le < kInfKey;
-}
-
-__global__ void __launch_bounds__(kGT) k_gp_count(const LaneDesc* __restrict__ lanes, GridLane* gl, int t0,
-                                                  int t, uint32_t lb_key) {
-  __shared__ GScratch s;
-  const LaneDesc& L = lanes[blockIdx.y];
-  GridLane& G = gl[blockIdx.y];
-  if (!G.pr.go) return;
-  const uint64_t base = L.link_off[t0], end = L.link_end[t];
-  uint64_t blo, bhi;
-  chunk(end - base, blockIdx.x, &blo, &bhi);
-  unsigned long long c = 0;
-  for (uint64_t k = base + blo + threadIdx.x; k < base + bhi; k += kGT) c += gp_kept(L, k, lb_key);
-  c = gsum64(c, s);
-  if (threadIdx.x == 0) G.pr.part[blockIdx.x] = c;
-}
-
-__global__ void __launch_bounds__(kGT) k_gp_scan(GridLane* gl) {
-  __shared__ GScratch s;
-  GridLane& G = gl[blockIdx.y];
-  if (!G.pr.go) return;
-  scan_parts(G.pr.part, s);
-}
-
-// Kept links to the compacted region in order (when they fit); le_key[k] :=
-// kept links of the window before k, for the offsets.
-__global__ void __launch_bounds__(kGT) k_gp_write(const LaneDesc* __restrict__ lanes, GridLane* gl, int t0,
-                                                  int t, uint32_t lb_key) {
-  __shared__ GScratch s;
-  const LaneDesc& L = lanes[blockIdx.y];
-  GridLane& G = gl[blockIdx.y];
-  if (!G.pr.go) return;
-  const uint64_t base = L.link_off[t0], end = L.link_end[t];
-  const uint64_t k0 = G.pr.kend, nk = G.pr.part[kGB];
-  const bool fits = !G.pr.ovf && k0 + nk <= L.link_cap;
-  uint64_t blo, bhi;
-  chunk(end - base, blockIdx.x, &blo, &bhi);
-  unsigned long long run = G.pr.part[blockIdx.x];
-  for (uint64_t b0 = base + blo; b0 < base + bhi; b0 += kGT) {
-    const uint64_t k = b0 + threadIdx.x;
-    const bool on = k < base + bhi && gp_kept(L, k, lb_key);
-    unsigned long long tile;
-    const unsigned long long ex = run + gexcl64(on ? 1ull : 0ull, s, &tile);
-    run += tile;
-    if (k >= base + bhi) continue;
-    L.le_key[k] = (uint32_t)ex;
-    if (on && fits) {
-      L.links[k0 + ex] = L.links[k];
-      L.link_lvl[k0 + ex] = L.link_lvl[k];
-    }
-  }
-}
-
-// The window's frame offsets in the compacted region, and its new end.
-__global__ void __launch_bounds__(kGT) k_gp_fix(const LaneDesc* __restrict__ lanes, GridLane* gl, int t0, int t) {
-  const LaneDesc& L = lanes[blockIdx.y];
-  GridLane& G = gl[blockIdx.y];
-  if (!G.pr.go) return;
-  const uint64_t end = L.link_end[t], k0 = G.pr.kend, nk = G.pr.part[kGB];
-  __syncthreads();  // every thread has read link_end[t] before it moves
-  auto moved = [&](uint64_t o) -> uint64_t { return k0 + (o < end ? (uint64_t)L.le_key[o] : nk); };
-  for (int f = t0 + (int)threadIdx.x; f <= t; f += kGT) {
-    L.link_off[f] = moved(L.link_off[f]);
-    L.link_xoff[f] = moved(L.link_xoff[f]);
-    L.link_end[f] = moved(L.link_end[f]);
-  }
-  if (threadIdx.x == 0) {
-    if (k0 + nk > L.link_cap) G.pr.ovf = 1;
-    G.pr.kend = k0 + nk;
-    G.pr.next = (uint32_t)t + 1u;
-  }
-}
-
-// The frames after the last pruned window (t0 .. T; none when it ended at
-// T), behind the compacted region: frames t0 .. a1 of t0's window, then
-// a1 + 1 .. T of the next one (empty when T ends t0's window), each
-// contiguous in its slot.  On the decoding stream, after it has waited for
-// the pruning stream.
-struct Gather {
-  int t0, a1;
-  uint64_t srcA, nA, srcB, nB;
-};
-
-__device__ __forceinline__ bool gather_range(const LaneDesc& L, const GridLane& G, Gather* r) {
-  if (!L.win_cap || G.status != 0 || !G.hist_ok) return false;
-  const int t0 = (int)G.pr.next, T = L.T;
-  r->t0 = t0;
-  r->a1 = t0 + kPruneEvery - 1 < T ? t0 + kPruneEvery - 1 : T;
-  r->srcA = t0 <= T ? L.link_off[t0] : 0;
-  r->nA = t0 <= T ? L.link_end[r->a1] - r->srcA : 0;
-  r->srcB = r->a1 < T ? L.link_off[r->a1 + 1] : 0;
-  r->nB = r->a1 < T ? L.link_end[T] - r->srcB : 0;
-  return true;
-}
-
-__global__ void __launch_bounds__(kGT) k_gp_gather(const LaneDesc* __restrict__ lanes, const GridLane* gl) {
-  const LaneDesc& L = lanes[blockIdx.y];
-  const GridLane& G = gl[blockIdx.y];
-  Gather r;
-  if (!gather_range(L, G, &r)) return;
-  const uint64_t k0 = G.pr.kend, n = r.nA + r.nB;
-  if (G.pr.ovf || k0 + n > L.link_cap) return;
-  for (uint64_t i = (uint64_t)blockIdx.x * kGT + threadIdx.x; i < n; i += (uint64_t)kGB * kGT) {
-    const uint64_t src = i < r.nA ? r.srcA + i : r.srcB + (i - r.nA);
-    L.links[k0 + i] = L.links[src];
-    L.link_lvl[k0 + i] = L.link_lvl[src];
-  }
-}
-
-__global__ void __launch_bounds__(kGT) k_gp_gather_fix(const LaneDesc* __restrict__ lanes, GridLane* gl) {
-  const LaneDesc& L = lanes[blockIdx.y];
-  GridLane& G = gl[blockIdx.y];
-  Gather r;
-  if (!gather_range(L, G, &r)) return;
-  const uint64_t k0 = G.pr.kend, n = r.nA + r.nB;
-  const bool fits = !G.pr.ovf && k0 + n <= L.link_cap;
-  __syncthreads();  // every thread has read the offsets before they move
-  if (fits)
-    for (int f = r.t0 + (int)threadIdx.x; f <= L.T; f += kGT) {
-      const uint64_t dst = f <= r.a1 ? k0 - r.srcA : k0 + r.nA - r.srcB;  // (mod 2^64)
-      L.link_off[f] = L.link_off[f] + dst;
-      L.link_xoff[f] = L.link_xoff[f] + dst;
-      L.link_end[f] = L.link_end[f] + dst;
-    }
-  if (threadIdx.x == 0) {
-    if (fits) L.link_off[L.T + 1] = k0 + n;
-    else G.pr.ovf = 1;
-    G.pr.kend = k0 + n;
-  }
-}
-
 // -------------------------------------------------------------------- launches
 
 size_t grid_lane_bytes() { return sizeof(GridLane); }
-
-uint32_t grid_window_slots() { return kSlots; }
 
 // Decoding-state update for a stream's utterances: a workgroup per lane.
 __global__ void k_g_bad(const LaneDesc* __restrict__ lanes, GridLane* gl, const uint32_t* __restrict__ bad) {
@@ -1666,74 +1490,18 @@ __global__ void k_g_bad(const LaneDesc* __restrict__ lanes, GridLane* gl, const 
   lanes[blockIdx.y].info->status = 1;
 }
 
-namespace {
-
-// The library's pruning stream of each device (default priority, never
-// blocking on the null stream).
-hipError_t prune_stream(hipStream_t* out) {
-  static std::mutex create;
-  static hipStream_t per_dev[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lk(create);
-  if (!per_dev[dev]) {
-    hipStream_t q = nullptr;
-    if ((e = hipStreamCreateWithFlags(&q, hipStreamNonBlocking)) != hipSuccess) return e;
-    per_dev[dev] = q;
-  }
-  *out = per_dev[dev];
-  return hipSuccess;
-}
-
-}  // namespace
-
-void grid_release(GridRun* run) {
-  // a run that did not reach grid_end may still have windows being pruned
-  if (run->q && !run->ended && run->nwin > 0) (void)hipStreamSynchronize(run->q);
-  for (int i = 0; i < 4; ++i) {
-    if (run->ready[i]) (void)hipEventDestroy(run->ready[i]);
-    if (run->done[i]) (void)hipEventDestroy(run->done[i]);
-    run->ready[i] = run->done[i] = nullptr;
-  }
-  run->q = nullptr;
-}
-
-wd_status grid_begin(GridRun* run, const LaneDesc* lanes, void* glv, int B, bool prune, const uint32_t* bad,
-                     hipStream_t st) {
-  *run = GridRun{};
-  if (prune) {
-    hipError_t e = prune_stream(&run->q);
-    for (int i = 0; i < 4 && e == hipSuccess; ++i) {
-      e = hipEventCreateWithFlags(&run->ready[i], hipEventDisableTiming);
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&run->done[i], hipEventDisableTiming);
-    }
-    if (e != hipSuccess) {
-      grid_release(run);
-      return hip_check(e, "pruning stream");
-    }
-  }
+void grid_begin(const LaneDesc* lanes, void* glv, int B, const uint32_t* bad, hipStream_t st) {
   hipLaunchKernelGGL(k_g_init, dim3(1, B), dim3(kGT), 0, st, lanes, (GridLane*)glv, bad);
-  return WD_OK;
 }
 
-// Frames t_from..t_to.  Window u's links go to slot u % kSlots: the first
-// frame of window u waits for the pruning of window u - kSlots; kLookahead
-// frames after the last frame of window j, an event hands window j to the
-// pruning stream (ready[j % 4] / done[j % 4]; every wait is enqueued before
-// its event is recorded again).
-wd_status grid_frames(GridRun* run, const DevGraph& g, const LaneDesc* lanes, void* glv, int B, const Params& prm,
-                      const uint32_t* bad, int t_from, int t_to, hipStream_t st) {
+// Frames t_from..t_to.
+void grid_frames(const DevGraph& g, const LaneDesc* lanes, void* glv, int B, const Params& prm, const uint32_t* bad,
+                 int t_from, int t_to, hipStream_t st) {
   GridLane* gl = (GridLane*)glv;
-  const dim3 one(1, B), all(kGB, B), part(kPB, B), blk(kGT);
-  const uint32_t lb_key = cost_key(prm.lattice_beam);
-  hipError_t e = hipSuccess;
+  const dim3 one(1, B), all(kGB, B), blk(kGT);
+  const bool sparse = (prm.flags & kFlagSparse) != 0;
   hipLaunchKernelGGL(k_g_bad, one, dim3(64), 0, st, lanes, gl, bad);
-  for (int t = t_from; t <= t_to && e == hipSuccess; ++t) {
-    const int reuse = t / kPruneEvery - (int)kSlots;
-    if (run->q && t % kPruneEvery == 0 && reuse >= 0 && reuse < run->nwin)
-      e = hipStreamWaitEvent(st, run->done[reuse % 4], 0);
+  for (int t = t_from; t <= t_to; ++t) {
     // per frame: expansion (with the frame's start), epsilon levels,
     // survivors (with the cutoff and capacity checks), [max-active select],
     // kept-state counts, compaction, degrees, link counts, links, end
@@ -1750,54 +1518,18 @@ wd_status grid_frames(GridRun* run, const DevGraph& g, const LaneDesc* lanes, vo
       }
       hipLaunchKernelGGL(k_g_mark, all, blk, 0, st, lanes, gl);
     }
-    hipLaunchKernelGGL(k_g_bits, all, blk, 0, st, g, lanes, gl, prm);
+    hipLaunchKernelGGL(k_g_bits, all, blk, 0, st, g, lanes, gl, prm, t);
     hipLaunchKernelGGL(k_g_compact, all, blk, 0, st, g, lanes, gl, prm);
-    hipLaunchKernelGGL(k_g_degrees, all, blk, 0, st, g, lanes, gl);
-    hipLaunchKernelGGL(k_g_link_count, all, blk, 0, st, g, lanes, gl, t);
-    hipLaunchKernelGGL(k_g_link_write, all, blk, 0, st, g, lanes, gl, t);
-    hipLaunchKernelGGL(k_g_end, one, blk, 0, st, lanes, gl, t);
-    if (run->q && (t + 1 - kLookahead) % kPruneEvery == 0 && t + 1 - kLookahead >= kPruneEvery) {
-      // window j = [t0, t1] against frame t, kLookahead frames after it
-      const int t1 = t - kLookahead, t0 = t1 + 1 - kPruneEvery, j = run->nwin++;
-      hipStream_t q = run->q;
-      e = hipEventRecord(run->ready[j % 4], st);
-      if (e == hipSuccess) e = hipStreamWaitEvent(q, run->ready[j % 4], 0);
-      if (e != hipSuccess) break;
-      hipLaunchKernelGGL(k_gp_go, one, dim3(64), 0, q, gl, t);
-      hipLaunchKernelGGL(k_gp_init, part, blk, 0, q, lanes, gl, t0, t);
-      // frame f: the emitting links leaving it, then its epsilon levels; down
-      // to f = t0 - 1 for the emitting links into t0 (the window's first run;
-      // the extra costs this leaves on frame t0 - 1 are never read)
-      for (int f = t; f >= t0 - 1 && f >= 0; --f) {
-        if (f < t) hipLaunchKernelGGL(k_gs_relax, part, blk, 0, q, lanes, gl, f, 1, 0, 1);
-        if (f >= t0)
-          for (int l = (int)g.nlevels - 1; l >= 0; --l)
-            hipLaunchKernelGGL(k_gs_relax, part, blk, 0, q, lanes, gl, f, 0, l, 1);
-      }
-      hipLaunchKernelGGL(k_gp_count, all, blk, 0, q, lanes, gl, t0, t1, lb_key);
-      hipLaunchKernelGGL(k_gp_scan, one, blk, 0, q, gl);
-      hipLaunchKernelGGL(k_gp_write, all, blk, 0, q, lanes, gl, t0, t1, lb_key);
-      hipLaunchKernelGGL(k_gp_fix, one, blk, 0, q, lanes, gl, t0, t1);
-      e = hipEventRecord(run->done[j % 4], q);
-    }
+    hipLaunchKernelGGL(k_g_degrees, all, blk, 0, st, lanes, gl, prm);
+    if (!sparse || prm.max_active > 0) hipLaunchKernelGGL(k_g_link_count, all, blk, 0, st, g, lanes, gl, prm, t);
+    if (!sparse) hipLaunchKernelGGL(k_g_link_write, all, blk, 0, st, g, lanes, gl, t);
+    hipLaunchKernelGGL(k_g_end, one, blk, 0, st, lanes, gl, prm, t);
   }
-  return hip_check(e, "pruning stream");
 }
 
-// After the last frame: wait for the pruning stream, gather the frames after
-// the last pruned window, final counters.
-wd_status grid_end(GridRun* run, const LaneDesc* lanes, void* glv, int B, hipStream_t st) {
-  GridLane* gl = (GridLane*)glv;
-  const dim3 one(1, B), all(kGB, B), blk(kGT);
-  hipError_t e = hipSuccess;
-  if (run->q) {
-    if (run->nwin > 0) e = hipStreamWaitEvent(st, run->done[(run->nwin - 1) % 4], 0);
-    hipLaunchKernelGGL(k_gp_gather, all, blk, 0, st, lanes, gl);
-    hipLaunchKernelGGL(k_gp_gather_fix, one, blk, 0, st, lanes, gl);
-  }
-  hipLaunchKernelGGL(k_g_finish, one, dim3(64), 0, st, lanes, gl);
-  run->ended = e == hipSuccess;
-  return hip_check(e, "pruning stream");
+// After the last frame: the final counters.
+void grid_end(const LaneDesc* lanes, void* glv, int B, hipStream_t st) {
+  hipLaunchKernelGGL(k_g_finish, dim3(1, B), dim3(64), 0, st, lanes, (GridLane*)glv);
 }
 
 void launch_grid_nodes(const LaneDesc* lanes, void* glv, int B, hipStream_t st) {
@@ -1808,24 +1540,29 @@ void launch_grid_nodes(const LaneDesc* lanes, void* glv, int B, hipStream_t st) 
   hipLaunchKernelGGL(k_gn_write, all, blk, 0, st, lanes, gl);
 }
 
-void launch_grid_sweep(const DevGraph& g, const LaneDesc* lanes, void* glv, int B, int maxT, float lattice_beam,
+void launch_grid_sweep(const DevGraph& g, const LaneDesc* lanes, void* glv, int B, int maxT, const Params& prm,
                        hipStream_t st) {
   GridLane* gl = (GridLane*)glv;
   const dim3 one(1, B), all(kGB, B), blk(kGT);
-  hipLaunchKernelGGL(k_gs_final_any, all, blk, 0, st, g, lanes, gl);
-  hipLaunchKernelGGL(k_gs_final_min, all, blk, 0, st, g, lanes, gl);
-  hipLaunchKernelGGL(k_gs_final, one, dim3(64), 0, st, lanes, gl);
-  hipLaunchKernelGGL(k_gs_init, all, blk, 0, st, g, lanes, gl);
-  for (int t = maxT; t >= 0; --t) {
-    hipLaunchKernelGGL(k_gs_relax, all, blk, 0, st, lanes, gl, t, 1, 0, 0);
-    for (int l = (int)g.nlevels - 1; l >= 0; --l)
-      hipLaunchKernelGGL(k_gs_relax, all, blk, 0, st, lanes, gl, t, 0, l, 0);
+  if (prm.flags & kFlagSparse) {
+    launch_sweep(g, lanes, B, prm, st);
+    launch_links(g, lanes, B, prm, st);
+  } else {
+    hipLaunchKernelGGL(k_gs_final_any, all, blk, 0, st, g, lanes, gl);
+    hipLaunchKernelGGL(k_gs_final_min, all, blk, 0, st, g, lanes, gl);
+    hipLaunchKernelGGL(k_gs_final, one, dim3(64), 0, st, lanes, gl);
+    hipLaunchKernelGGL(k_gs_init, all, blk, 0, st, g, lanes, gl);
+    for (int t = maxT; t >= 0; --t) {
+      hipLaunchKernelGGL(k_gs_relax, all, blk, 0, st, lanes, gl, t, 1, 0);
+      for (int l = (int)g.nlevels - 1; l >= 0; --l)
+        hipLaunchKernelGGL(k_gs_relax, all, blk, 0, st, lanes, gl, t, 0, l);
+    }
   }
-  const uint32_t lb_key = cost_key(lattice_beam);
+  const uint32_t lb_key = cost_key(prm.lattice_beam);
   hipLaunchKernelGGL(k_gk_count, all, blk, 0, st, lanes, gl, lb_key);
   hipLaunchKernelGGL(k_g_scan, one, blk, 0, st, lanes, gl, 3, 1);
   hipLaunchKernelGGL(k_gk_write, all, blk, 0, st, g, lanes, gl, lb_key);
-  hipLaunchKernelGGL(k_gs_fill_ab, all, blk, 0, st, lanes);
+  hipLaunchKernelGGL(k_gs_fill_ab, all, blk, 0, st, lanes, (prm.flags & kFlagSparse) == 0);
 }
 
 }  // namespace wd

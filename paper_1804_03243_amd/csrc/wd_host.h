@@ -38,28 +38,14 @@ size_t cluster_ctl_bytes();
 // Workgroups of a launch of B leaders that brings helpers: one per CU in all.
 int cluster_grid(int B);
 size_t grid_lane_bytes();
-// Raw window slots of the link store with incremental pruning.
-uint32_t grid_window_slots();
 // Chip-wide forward pass in three steps, so that a stream can decode frames as
-// they arrive: begin (per-utterance state; with `prune`, incremental lattice
-// pruning on the library's pruning stream of the current device, ordered
-// against `s` by the run's events), frames t_from..t_to (any number of calls,
-// in order), end.  Errors are HIP errors of the pruning stream or its events.
-// grid_release frees the events (after waiting for the pruning stream if the
-// run did not reach grid_end).
-struct GridRun {
-  hipStream_t q = nullptr;  // pruning stream, or nullptr
-  hipEvent_t ready[4] = {}, done[4] = {};
-  int nwin = 0;             // windows handed to the pruning stream
-  bool ended = false;       // grid_end made the decoding stream wait for them
-};
-wd_status grid_begin(GridRun* run, const LaneDesc* lanes, void* grid, int B, bool prune, const uint32_t* bad,
-                     hipStream_t s);
-wd_status grid_frames(GridRun* run, const DevGraph& g, const LaneDesc* lanes, void* grid, int B, const Params& prm,
-                      const uint32_t* bad, int t_from, int t_to, hipStream_t s);
-wd_status grid_end(GridRun* run, const LaneDesc* lanes, void* grid, int B, hipStream_t s);
-void grid_release(GridRun* run);
-void launch_grid_sweep(const DevGraph& g, const LaneDesc* lanes, void* grid, int B, int maxT, float lattice_beam,
+// they arrive: begin (per-utterance state), frames t_from..t_to (any number of
+// calls, in order), end.
+void grid_begin(const LaneDesc* lanes, void* grid, int B, const uint32_t* bad, hipStream_t s);
+void grid_frames(const DevGraph& g, const LaneDesc* lanes, void* grid, int B, const Params& prm, const uint32_t* bad,
+                 int t_from, int t_to, hipStream_t s);
+void grid_end(const LaneDesc* lanes, void* grid, int B, hipStream_t s);
+void launch_grid_sweep(const DevGraph& g, const LaneDesc* lanes, void* grid, int B, int maxT, const Params& prm,
                        hipStream_t s);
 void launch_grid_nodes(const LaneDesc* lanes, void* grid, int B, hipStream_t s);
 void launch_check_loglikes(const LaneDesc* lanes, int B, uint32_t P, uint32_t* bad, hipStream_t s);

@@ -1315,13 +1315,14 @@ __global__ void __launch_bounds__(kLT) k_lattice(DevGraph g, const LaneDesc* __r
     // (done in LDS)
   } else if (!wide) {
     __syncthreads();  // (a compact attempt that did not fit has used the LDS)
-    if (tid < 64) alpha_wave<64>(L, g, sh, tid, swept, start_node);
-    else if (tid < 128) beta_wave<64>(L, g, sh, tid - 64, swept, final_used, best_total);
+    // (a sparse utterance's link kernels have set its live nodes' sums to 0)
+    if (tid < 64) alpha_wave<64>(L, g, sh, tid, swept || sparse, start_node);
+    else if (tid < 128) beta_wave<64>(L, g, sh, tid - 64, swept || sparse, final_used, best_total);
   } else {
-    alpha_wave<kLT>(L, g, sh, tid, swept, start_node);
+    alpha_wave<kLT>(L, g, sh, tid, swept || sparse, start_node);
     if (!swept) {
       __syncthreads();
-      beta_wave<kLT>(L, g, sh, tid, swept, final_used, best_total);
+      beta_wave<kLT>(L, g, sh, tid, sparse, final_used, best_total);
     }
   }
   __syncthreads();

@@ -25,7 +25,7 @@ constexpr int kLT = 256;              // threads per workgroup
 constexpr int kLWv = kLT / 64;        // wavefronts
 constexpr uint32_t kLinkBlocks = 256;  // workgroups per utterance (frames in turn)
 constexpr uint32_t kSpBWin = 2048;     // sparse utterances: states of one frame held in LDS
-constexpr uint32_t kSpTile = 2048;     // nodes whose live ones are listed together
+constexpr uint32_t kSpList = 2048;     // live nodes listed together
 
 struct LinkShared {
   BlockScratch bs;
@@ -139,7 +139,7 @@ __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& 
 struct SpLinkShared {
   BlockScratch bs;
   uint32_t win[kSpBWin];
-  uint32_t list[kSpTile];  // live nodes of a tile, as offsets from its first node
+  uint32_t list[kSpList];  // live nodes of a tile, as offsets from its first node
   uint32_t pre[kLT], beg[kLT], node[kLT];
   float cost[kLT];
   uint32_t cls[kLT];
@@ -156,86 +156,87 @@ __device__ __forceinline__ uint32_t sp_run(const DevGraph& g, const LaneDesc& L,
   const float* row = (const float*)L.ll + (size_t)(t > 0 ? t - 1 : 0) * g.P;
   const uint32_t cut = cost_key(L.cut[t]);
   uint32_t n = 0;
-  for (uint64_t q0 = p0 & ~31ull; q0 < p1; q0 += kSpTile) {
-    // live nodes among [q0, q0 + kSpTile): 128 bitmap words
+  for (uint64_t q0 = p0 & ~31ull; q0 < p1; q0 += 32u * kLT) {
+    // live nodes of a tile, a bitmap word per thread, listed kSpList at a time
     uint32_t word = 0;
-    if (tid < kSpTile / 32u && q0 + 32u * tid < p1) {
-      const uint64_t b = q0 + 32u * tid;
-      word = L.used[b >> 5];
-      if (b < p0) word &= ~0u << (p0 - b);
-      if (p1 - b < 32u) word &= (1u << (p1 - b)) - 1u;
+    const uint64_t wb = q0 + 32u * tid;
+    if (wb < p1) {
+      word = L.used[wb >> 5];
+      if (wb < p0) word &= ~0u << (p0 - wb);
+      if (p1 - wb < 32u) word &= (1u << (p1 - wb)) - 1u;
     }
-    uint32_t live;
-    uint32_t pos = block_excl_scan<kLWv>((uint32_t)__popc(word), sh.bs, par, &live);
-    while (word) {
-      const uint32_t b = (uint32_t)__ffs(word) - 1u;
-      word &= word - 1u;
-      sh.list[pos++] = 32u * tid + b;
-    }
-    __syncthreads();
-    for (uint32_t l0 = 0; l0 < live; l0 += kLT) {
-      const uint32_t m = live - l0 < (uint32_t)kLT ? live - l0 : (uint32_t)kLT;
-      uint32_t deg = 0, a0 = 0, c = 0, node = 0;
-      float cost = 0.0f;
-      if (tid < m) {
-        node = (uint32_t)(q0 + sh.list[l0 + tid]);
-        const uint32_t s = L.n_state[node];
-        cost = key_cost((uint32_t)(L.n_pack[node] >> 32));
-        const uint4 o0 = g.off[s], o1 = g.off[s + 1];
-        a0 = kEps ? o0.y : o0.x;
-        deg = kEps ? o1.y - o0.y : o1.x - o0.x;
-        if (kEps) {
-          c = g.sclass[s];
-          if (!kWrite) {  // (every live node of frame t once: its forward-backward sums start at 0)
-            L.alpha[node] = 0.0;
-            L.beta[node] = 0.0;
+    uint32_t all;
+    const uint32_t pos0 = block_excl_scan<kLWv>((uint32_t)__popc(word), sh.bs, par, &all);
+    for (uint32_t c0 = 0; c0 < all; c0 += kSpList) {
+      const uint32_t live = all - c0 < kSpList ? all - c0 : kSpList;
+      uint32_t pos = pos0 - c0;  // (mod 2^32: below or beyond this part)
+      for (uint32_t m = word; m; m &= m - 1u, ++pos)
+        if (pos < kSpList) sh.list[pos] = 32u * tid + ((uint32_t)__ffs(m) - 1u);
+      __syncthreads();
+      for (uint32_t l0 = 0; l0 < live; l0 += kLT) {
+        const uint32_t m = live - l0 < (uint32_t)kLT ? live - l0 : (uint32_t)kLT;
+        uint32_t deg = 0, a0 = 0, c = 0, node = 0;
+        float cost = 0.0f;
+        if (tid < m) {
+          node = (uint32_t)(q0 + sh.list[l0 + tid]);
+          const uint32_t s = L.n_state[node];
+          cost = key_cost((uint32_t)(L.n_pack[node] >> 32));
+          const uint4 o0 = g.off[s], o1 = g.off[s + 1];
+          a0 = kEps ? o0.y : o0.x;
+          deg = kEps ? o1.y - o0.y : o1.x - o0.x;
+          if (kEps) {
+            c = g.sclass[s];
+            if (!kWrite) {  // (every live node of frame t once: its forward-backward sums start at 0)
+              L.alpha[node] = 0.0;
+              L.beta[node] = 0.0;
+            }
           }
         }
-      }
-      uint32_t tot;
-      sh.pre[tid] = block_excl_scan<kLWv>(deg, sh.bs, par, &tot);
-      sh.beg[tid] = a0;
-      sh.cost[tid] = cost;
-      sh.node[tid] = node;
-      sh.cls[tid] = c;
-      __syncthreads();
-      for (uint32_t w0 = 0; w0 < tot; w0 += kLT) {
-        const uint32_t it = w0 + tid;
-        bool in = false;
-        uint32_t j = 0, xb = 0, dn = ~0u, le = kInfKey;
-        uint4 r = make_uint4(0, 0, 0, 0);
-        if (it < tot) {
-          j = search_le(sh.pre, m, it);
-          const uint32_t a = sh.beg[j] + (it - sh.pre[j]);
-          r = kEps ? g.xarc[a] : g.earc[a];
-          dn = sp_lookup<kSpBWin>(L, df, sh.win, r.x);
-          if (dn != ~0u) {
-            const float exd = key_cost(L.extra_key[dn]);
-            const float cd = key_cost((uint32_t)(L.n_pack[dn] >> 32));
-            float x = sh.cost[j];
-            if (!kEps) x = x + -row[(r.z & 0xffffffu) - 1u];
-            x = canon(x + __uint_as_float(r.y));
-            xb = __float_as_uint(x);
-            const uint32_t xk = cost_key(x);
-            le = cost_key(exd + (x - cd));
-            in = xk <= cut && xk < kInfKey && le <= lb_key && le < kInfKey;
+        uint32_t tot;
+        sh.pre[tid] = block_excl_scan<kLWv>(deg, sh.bs, par, &tot);
+        sh.beg[tid] = a0;
+        sh.cost[tid] = cost;
+        sh.node[tid] = node;
+        sh.cls[tid] = c;
+        __syncthreads();
+        for (uint32_t w0 = 0; w0 < tot; w0 += kLT) {
+          const uint32_t it = w0 + tid;
+          bool in = false;
+          uint32_t j = 0, xb = 0, dn = ~0u, le = kInfKey;
+          uint4 r = make_uint4(0, 0, 0, 0);
+          if (it < tot) {
+            j = search_le(sh.pre, m, it);
+            const uint32_t a = sh.beg[j] + (it - sh.pre[j]);
+            r = kEps ? g.xarc[a] : g.earc[a];
+            dn = sp_lookup<kSpBWin>(L, df, sh.win, r.x);
+            if (dn != ~0u) {
+              const float exd = key_cost(L.extra_key[dn]);
+              const float cd = key_cost((uint32_t)(L.n_pack[dn] >> 32));
+              float x = sh.cost[j];
+              if (!kEps) x = x + -row[(r.z & 0xffffffu) - 1u];
+              x = canon(x + __uint_as_float(r.y));
+              xb = __float_as_uint(x);
+              const uint32_t xk = cost_key(x);
+              le = cost_key(exd + (x - cd));
+              in = xk <= cut && xk < kInfKey && le <= lb_key && le < kInfKey;
+            }
+          }
+          uint32_t nsub;
+          const uint32_t p = n + block_excl_scan<kLWv>(in ? 1u : 0u, sh.bs, par, &nsub);
+          n += nsub;
+          if (!kWrite || !in) continue;
+          L.links[at + p] = make_uint4(r.w, sh.node[j], dn, xb);
+          L.le_key[at + p] = le;
+          if (kEps) {
+            const uint32_t cl = sh.cls[j];
+            L.link_lvl[at + p] = (uint8_t)cl;
+            *xmask |= 1u << (cl < 31u ? cl : 31u);
           }
         }
-        uint32_t nsub;
-        const uint32_t p = n + block_excl_scan<kLWv>(in ? 1u : 0u, sh.bs, par, &nsub);
-        n += nsub;
-        if (!kWrite || !in) continue;
-        L.links[at + p] = make_uint4(r.w, sh.node[j], dn, xb);
-        L.le_key[at + p] = le;
-        if (kEps) {
-          const uint32_t cl = sh.cls[j];
-          L.link_lvl[at + p] = (uint8_t)cl;
-          *xmask |= 1u << (cl < 31u ? cl : 31u);
-        }
+        __syncthreads();
       }
       __syncthreads();
     }
-    __syncthreads();
   }
   return n;
 }

@@ -30,7 +30,10 @@ namespace wd {
 constexpr uint32_t kSpTok = kThreads;          // live nodes per tile
 constexpr uint32_t kSpWin = 8192;              // states of one frame held in LDS
 constexpr uint32_t kSpPer = kSpWin / kThreads;  // loaded per thread
-constexpr uint64_t kSpGather = 300;            // helpers have 3 µs to come up
+constexpr uint64_t kSpGather = 300;            // helpers have 3 µs to come up,
+constexpr uint64_t kSpGatherWide = 10000;      // 100 µs where frames average more than
+constexpr uint64_t kSpWide = 30000;            // this many tokens
+constexpr uint32_t kSpHelpers = 28;            // (an XCD's CUs, but for a few)
 
 struct SpShared {
   BlockScratch bs;
@@ -270,11 +273,14 @@ __global__ void __launch_bounds__(kThreads) k_sp_sweep(DevGraph g, const LaneDes
   uint32_t w = 0, N = 1;
   if (lead) {
     if (threadIdx.x == 0) cl_store(&C->xcc, cl_xcc() + 1u);
-    // (helpers of this launch come up within a few microseconds; those that
-    // have not arrived when the run opens stay out of it)
-    const uint64_t t0 = wall_clock64();
+    // Helpers of this launch come up over tens of microseconds; those that have
+    // not arrived when the run opens stay out of it.  Frames of a few live
+    // nodes gain little from them (and each adds to the barriers); wide ones,
+    // with thousands, are worth the wait.
+    const bool wide = L.info->tokens > kSpWide * ((uint64_t)L.T + 1);
+    const uint64_t t0 = wall_clock64(), limit = wide ? kSpGatherWide : kSpGather;
     if (gridDim.x > B && threadIdx.x == 0)
-      while (wall_clock64() - t0 < kSpGather) __builtin_amdgcn_s_sleep(2);
+      while (wall_clock64() - t0 < limit && cl_load(&C->alive) < kSpHelpers) __builtin_amdgcn_s_sleep(2);
     __syncthreads();
     N = cl_open(C, S.go, 0, 0, 0, false, false, 1u);
   } else {

@@ -511,8 +511,8 @@ def decode_batch(graph: Graph, loglikes: list, beam: float, max_active: int, lat
     """Decode utterances (device float32 tensors, T_i x P) concurrently.
     `mode`: "workgroup" (one workgroup per utterance), "chip" (chip-wide
     kernels per frame), "chip_dyn" (chip-wide with dynamic load balancing of
-    the emitting arcs), "chip_noprune" (chip-wide without incremental lattice
-    pruning), "workgroup_levels" (one workgroup, epsilon closure level by
+    the emitting arcs), "chip_noprune" (chip-wide with every raw lattice link
+    stored and swept), "workgroup_levels" (one workgroup, epsilon closure level by
     level instead of by the graph's epsilon paths) or "auto" (the library's
     choice).  `flags`: further WD_FLAG_*
     bits (e.g. WD_FLAG_PHASES).  Returns one result namespace per utterance."""
