@@ -7,6 +7,7 @@
 // the paper's sequence parallelism (Sec. 4.2) done in one process.
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -236,12 +237,52 @@ wd_status check_params(const wd_params* p) {
 
 }  // namespace wd
 
+namespace wd {
+
+// Pinned host memory that result downloads land in, a few blocks per device.
+// A decode leases a free block, the copy engine writes its packed results
+// there, and the results view them in place: the block goes back when the last
+// result of the call is freed.  (Copied into vectors, a batch's 25 MB of results
+// cost 6 ms of page faults and copies, a wide lattice's 70 MB 20 ms.)  At most
+// kPinnedBlocks blocks of at most kPinnedMax bytes; a call that finds none free
+// (in a program that keeps its results) downloads into ordinary memory.
+constexpr int kPinnedBlocks = 3;
+constexpr uint64_t kPinnedMax = 512ull << 20;
+
+struct PinnedBlock {
+  char* p = nullptr;
+  uint64_t cap = 0;
+  bool leased = false;
+};
+struct PinnedPool {
+  std::mutex mu;
+  PinnedBlock block[kPinnedBlocks];
+};
+
+// A leased block; gives it back when the last holder is gone.
+struct PinnedLease {
+  PinnedPool* pool;
+  PinnedBlock* block;
+  char* p;
+  ~PinnedLease() {
+    std::lock_guard<std::mutex> lk(pool->mu);
+    block->leased = false;
+  }
+};
+
+}  // namespace wd
+
 struct wd_result {
   wd_status status = WD_OK;
   float cost = 0.0f;
-  std::vector<int32_t> words;
-  std::vector<wd_lat_arc> links, raw;
-  std::vector<wd_lat_node> nodes;
+  // words, links and nodes: in the lease's block, or in own
+  const int32_t* words = nullptr;
+  const wd_lat_arc* links = nullptr;
+  const wd_lat_node* nodes = nullptr;
+  int64_t n_words = 0, n_links = 0, n_nodes = 0;
+  std::shared_ptr<wd::PinnedLease> lease;
+  std::vector<char> own;
+  std::vector<wd_lat_arc> raw;
   std::vector<wd_token> tokens;
   std::vector<float> best, cutb, cut;
   std::vector<uint64_t> prof;  // WD_FLAG_PHASES: (T+2) x WD_PHASE_SLOTS (the last row: the lattice pass)
@@ -405,42 +446,42 @@ static const char* status_message(wd_status st) {
                               : "decode failed";
 }
 
-// Lattice pass, then the results of every utterance (synchronises).
-// Pinned host memory for result downloads, one buffer per device, grown on
-// demand and kept until the process ends.  Its mutex is held from the copy
-// until the results are unpacked (decodes on one device take turns there).
-struct PinnedBuffer {
-  std::mutex mu;
-  char* p = nullptr;
-  uint64_t cap = 0;
-};
-
-// Locks the current device's buffer (holding at least `bytes`) and returns it
-// locked in *out.
-static wd_status pinned_of_current_device(uint64_t bytes, PinnedBuffer** out) {
-  static PinnedBuffer bufs[64];
+// A block of at least `bytes` of the current device's pool in *out, or null
+// when none is free (or the size is beyond the pool's).
+static wd_status lease_pinned(uint64_t bytes, std::shared_ptr<PinnedLease>* out) {
+  static PinnedPool* pools = new PinnedPool[64];  // (kept until the process ends: results may outlive statics)
+  out->reset();
   int dev = 0;
   wd_status st = hip_check(hipGetDevice(&dev), "device");
   if (st != WD_OK) return st;
-  if (dev < 0 || dev >= 64) return fail(WD_EINVAL, "pinned buffer: device index out of range");
-  PinnedBuffer& b = bufs[dev];
-  b.mu.lock();
-  if (b.cap < bytes) {
-    if (b.p) (void)hipHostFree(b.p);
-    b.p = nullptr;
-    b.cap = 0;
+  if (dev < 0 || dev >= 64) return fail(WD_EINVAL, "pinned memory: device index out of range");
+  if (bytes > kPinnedMax) return WD_OK;
+  PinnedPool& pool = pools[dev];
+  std::lock_guard<std::mutex> lk(pool.mu);
+  PinnedBlock* best = nullptr;  // a free block, preferably the smallest that holds the bytes
+  for (PinnedBlock& b : pool.block) {
+    if (b.leased) continue;
+    if (!best || (b.cap >= bytes ? best->cap < bytes || b.cap < best->cap : best->cap < bytes && b.cap > best->cap))
+      best = &b;
+  }
+  if (!best) return WD_OK;
+  if (best->cap < bytes) {
+    if (best->p) (void)hipHostFree(best->p);
+    best->p = nullptr;
+    best->cap = 0;
     const uint64_t want = std::max<uint64_t>(bytes + bytes / 4, 1ull << 20);
-    if ((st = hip_check(hipHostMalloc((void**)&b.p, want, hipHostMallocDefault), "pinned buffer"))) {
-      b.p = nullptr;
-      b.mu.unlock();
+    if ((st = hip_check(hipHostMalloc((void**)&best->p, want, hipHostMallocDefault), "pinned memory"))) {
+      best->p = nullptr;
       return st;
     }
-    b.cap = want;
+    best->cap = want;
   }
-  *out = &b;
+  best->leased = true;
+  out->reset(new PinnedLease{&pool, best, best->p});
   return WD_OK;
 }
 
+// Lattice pass, then the results of every utterance (synchronises).
 static wd_status run_finish(wd_stream* run, wd_result** out) {
   const Regions& R = run->R;
   hipStream_t s = run->s;
@@ -486,16 +527,19 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
     poff[b + 1] = poff[b] + n;
   }
   const bool packed = !debug && poff[B] > 0 && poff[B] <= (uint64_t)B * run->c.arcs * 16;
-  // the packed results land in the device's pinned download buffer (a DMA
-  // straight into it; pageable memory would be copied through staging)
-  PinnedBuffer* pin = nullptr;
-  std::unique_lock<std::mutex> pin_lock;
+  // they land in a leased block of pinned memory (a DMA straight into it)
+  // and stay there; with no block free, in ordinary memory of each result's own
+  std::shared_ptr<PinnedLease> lease;
+  std::vector<char> plain;
+  const char* host = nullptr;
   if (packed) {
-    if ((st = pinned_of_current_device(poff[B], &pin))) return st;
-    pin_lock = std::unique_lock<std::mutex>(pin->mu, std::adopt_lock);
+    if ((st = lease_pinned(poff[B], &lease))) return st;
+    if (!lease) plain.resize(poff[B]);
+    char* dst = lease ? lease->p : plain.data();
+    host = dst;
     launch_pack_results(R.desc, B, run->lanes[0].cand, s);
     if ((st = hip_check(hipGetLastError(), "launch")) ||
-        (st = hip_check(hipMemcpyAsync(pin->p, run->lanes[0].cand, poff[B], hipMemcpyDeviceToHost, s),
+        (st = hip_check(hipMemcpyAsync(dst, run->lanes[0].cand, poff[B], hipMemcpyDeviceToHost, s),
                         "result download")) ||
         (st = hip_check(hipStreamSynchronize(s), "result download")))
       return st;
@@ -513,9 +557,24 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
     r->stats = lane_stats(I, Tb, fwd_ms, lat_ms, debug);
     out[b] = r;
     if (ls != WD_OK) continue;
-    r->words.resize(I.nwords);
-    r->links.resize(I.kept);
-    r->nodes.resize(I.out_nodes);
+    r->n_words = (int64_t)I.nwords;
+    r->n_links = (int64_t)I.kept;
+    r->n_nodes = (int64_t)I.out_nodes;
+    // links, nodes, words, one after another: where the packed results are, or
+    // in memory of the result's own
+    const uint64_t lbytes = sizeof(OutLink) * I.kept, nbytes = sizeof(OutNode) * I.out_nodes;
+    const char* at = nullptr;
+    if (packed && lease) {
+      r->lease = lease;
+      at = host + poff[b];
+    } else {
+      r->own.resize(lbytes + nbytes + 4 * I.nwords);
+      if (packed) std::memcpy(r->own.data(), host + poff[b], r->own.size());
+      at = r->own.data();
+    }
+    r->links = (const wd_lat_arc*)at;
+    r->nodes = (const wd_lat_node*)(at + lbytes);
+    r->words = (const int32_t*)(at + lbytes + nbytes);
     auto d2h = [&](void* dst, const void* src, uint64_t bytes) -> wd_status {
       if (!bytes) return WD_OK;
       return hip_check(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s), "result download");
@@ -529,10 +588,9 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
         return st;
       r->tick_hz = 1e3 * khz;
     }
-    if (packed) continue;  // copied below, all lanes at once
-    if ((st = d2h(r->words.data(), L.out_words, 4 * I.nwords)) ||
-        (st = d2h(r->links.data(), L.out_links, sizeof(OutLink) * I.kept)) ||
-        (st = d2h(r->nodes.data(), L.out_nodes, sizeof(OutNode) * I.out_nodes)))
+    if (packed) continue;
+    if ((st = d2h(r->own.data(), L.out_links, lbytes)) || (st = d2h(r->own.data() + lbytes, L.out_nodes, nbytes)) ||
+        (st = d2h(r->own.data() + lbytes + nbytes, L.out_words, 4 * I.nwords)))
       return st;
     if (debug) {
       const uint64_t nn = I.tokens;
@@ -557,17 +615,6 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
           r->tokens[n] = wd_token{t, (int32_t)ns[n], key_cost((uint32_t)(np[n] >> 32)), (uint32_t)np[n]};
     }
   }
-  if (packed)
-    for (int b = 0; b < B; ++b) {
-      wd_result* r = out[b];
-      if (!r || r->status != WD_OK) continue;
-      const char* src = pin->p + poff[b];
-      std::memcpy(r->links.data(), src, sizeof(OutLink) * r->links.size());
-      src += sizeof(OutLink) * r->links.size();
-      std::memcpy(r->nodes.data(), src, sizeof(OutNode) * r->nodes.size());
-      src += sizeof(OutNode) * r->nodes.size();
-      std::memcpy(r->words.data(), src, 4 * r->words.size());
-    }
   if ((st = hip_check(hipStreamSynchronize(s), "result download"))) return st;
   if (first_bad != WD_OK) set_error(status_message(first_bad));
   return first_bad;
@@ -763,16 +810,16 @@ extern "C" wd_status wd_decode_noalloc(const wd_graph* g, const float* loglikes,
 extern "C" wd_status wd_result_status(const wd_result* r) { return r->status; }
 extern "C" float wd_result_cost(const wd_result* r) { return r->cost; }
 extern "C" int32_t wd_result_words(const wd_result* r, const int32_t** w) {
-  *w = r->words.data();
-  return (int32_t)r->words.size();
+  *w = r->words;
+  return (int32_t)r->n_words;
 }
 extern "C" int64_t wd_result_lattice(const wd_result* r, const wd_lat_arc** a) {
-  *a = r->links.data();
-  return (int64_t)r->links.size();
+  *a = r->links;
+  return r->n_links;
 }
 extern "C" int64_t wd_result_nodes(const wd_result* r, const wd_lat_node** n) {
-  *n = r->nodes.data();
-  return (int64_t)r->nodes.size();
+  *n = r->nodes;
+  return r->n_nodes;
 }
 extern "C" int64_t wd_result_tokens(const wd_result* r, const wd_token** t) {
   *t = r->tokens.data();
