@@ -43,16 +43,17 @@ struct GridLane {
   uint32_t sel_active, sel_rank, sel_prefix, sel_less, sel_bits;
   uint32_t xmask;
   uint32_t final_used, best_total_key;
-  unsigned long long eps_frame;  // the frame's epsilon arcs | links counted by the closure << 32
   unsigned long long best_total;  // (final cost key, node offset) of the best end token
   uint64_t node_base, node_base_prev, link_base;
   uint64_t arcs, eps_arcs, tokens, max_tokens, need_frame, need_arcs;
   uint64_t raw_total;              // links ever recorded
   uint64_t need_links;             // link store used
   uint32_t nb[kMaxLevels + 1];
+  uint32_t nbt[kMaxLevels + 1];  // states of a level bucketed by the path kernel, behind the others
   uint32_t hist[kHistBins];
   // per-workgroup partial sums, then their exclusive prefix (+ total at kGB):
-  // [0] frontier counts, [1] degree sums, [2] link counts, [3] kept links
+  // [0] frontier counts, [1] degree sums, [2] link counts, [3] kept links (in the
+  // forward pass: the frame's epsilon arcs | links counted by the closure << 32)
   unsigned long long part[4][kGB + 1];
 };
 
@@ -318,7 +319,9 @@ __device__ __forceinline__ void stage_reset(TouchStageT<CAP>& ts, uint32_t nleve
   }
 }
 
-template <uint32_t CAP>
+// (PATHS: the path kernel's touches, counted in nbt behind the nb entries, which
+// stay as they are while it runs.)
+template <bool PATHS = false, uint32_t CAP>
 __device__ __forceinline__ void stage_touch(TouchStageT<CAP>& ts, GridLane& G, const LaneDesc& L, const DevGraph& g,
                                             uint32_t dst, uint32_t cls) {
   const uint32_t p = atomicAdd(&ts.nt, 1u);
@@ -334,19 +337,21 @@ __device__ __forceinline__ void stage_touch(TouchStageT<CAP>& ts, GridLane& G, c
       ts.bk_state[q] = dst;
       ts.bk_tag[q] = (cls << 16) | atomicAdd(&ts.lcnt[cls], 1u);
     } else {
-      L.bucket[g.level_base[cls] + atomicAdd(&G.nb[cls], 1u)] = dst;
+      const uint32_t b = PATHS ? G.nb[cls] + atomicAdd(&G.nbt[cls], 1u) : atomicAdd(&G.nb[cls], 1u);
+      L.bucket[g.level_base[cls] + b] = dst;
     }
   }
 }
 
 // Publishes the staged entries and empties the stage.  Whole workgroup.
-template <uint32_t CAP>
+template <bool PATHS = false, uint32_t CAP>
 __device__ __forceinline__ void stage_flush(TouchStageT<CAP>& ts, GridLane& G, const LaneDesc& L, const DevGraph& g) {
   __syncthreads();
   const uint32_t nt = ts.nt < CAP ? ts.nt : CAP, nbk = ts.nbk < CAP ? ts.nbk : CAP;
   if (threadIdx.x == 0 && nt) ts.gt = atomicAdd(&G.n_touched, nt);
   for (uint32_t l = threadIdx.x; l < g.nlevels; l += kGT)
-    if (ts.lcnt[l]) ts.lbase[l] = atomicAdd(&G.nb[l], ts.lcnt[l]);
+    if (ts.lcnt[l])
+      ts.lbase[l] = PATHS ? G.nb[l] + atomicAdd(&G.nbt[l], ts.lcnt[l]) : atomicAdd(&G.nb[l], ts.lcnt[l]);
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < nt; i += kGT) {
     const uint32_t pos = ts.gt + i;
@@ -558,11 +563,99 @@ __global__ void __launch_bounds__(kGT) k_g_level(DevGraph g, const LaneDesc* __r
     }
     stage_flush(ts, G, L, g);
   }
-  // one add for both counts (and one per wavefront in LDS)
+  // (both counts of the workgroup in its own word, summed at the frame's end: a
+  // word that all share costs 11.5 ns for each of hundreds of workgroups)
   const uint32_t wl = wave_incl_scan(links);
   if (lane_id() == 63u && wl) (void)atomicAdd(&n_link, wl);
   __syncthreads();
-  if (threadIdx.x == 0 && eps) atomicAdd(&G.eps_frame, eps | ((unsigned long long)n_link << 32));
+  if (threadIdx.x == 0 && eps) G.part[3][blockIdx.x] += eps | ((unsigned long long)n_link << 32);
+}
+
+// The upper epsilon levels in one launch: the states bucketed on levels from
+// kPathLevel on relax every epsilon path out of them (the graph's path table),
+// as the one-workgroup closure does for all levels: a path's cost adds its
+// arcs' weights in path order, so the minimum over the paths into a state is
+// what one pass per level gives it, arc ids included.  A level holds half the
+// states of the one below and its launch costs 9-11 µs however few they are,
+// while the paths out of the upper levels are few (all paths are 3.2 times the
+// arcs on the wide-beam graph, and relaxing those of level 0 costs more than
+// its launch).  What the states' epsilon arcs add to the counts is taken from
+// their final costs by the survivor kernel.
+constexpr uint32_t kPathLevel = 2;
+
+__host__ __device__ inline uint32_t path_level(const DevGraph& g, const Params& prm) {
+  return g.npaths != 0 && g.nlevels > kPathLevel + 1u && !(prm.flags & WD_FLAG_EPS_LEVELS) ? kPathLevel : g.nlevels;
+}
+
+__global__ void __launch_bounds__(kGT) k_g_paths(DevGraph g, const LaneDesc* __restrict__ lanes, GridLane* gl,
+                                                 Params prm) {
+  __shared__ GScratch s;
+  __shared__ TouchStage ts;
+  __shared__ uint32_t t_beg[kGT], t_ex[kGT], t_key[kGT], base[kMaxLevels + 2];
+  const LaneDesc& L = lanes[blockIdx.y];
+  GridLane& G = gl[blockIdx.y];
+  if (G.stop || G.best_key >= kInfKey) return;
+  // the levels' entries as one list
+  const uint32_t l0 = kPathLevel;
+  if (threadIdx.x == 0) {
+    uint32_t n = 0;
+    for (uint32_t l = l0; l < g.nlevels; ++l) {
+      base[l] = n;
+      n += G.nb[l];
+    }
+    base[g.nlevels] = n;
+  }
+  __syncthreads();
+  const uint32_t n = base[g.nlevels];
+  uint32_t tile = kLvlMinTile;
+  while (tile < (uint32_t)kGT && (uint64_t)tile * kGB < n) tile <<= 1;
+  if (n == 0 || blockIdx.x * tile >= n) return;
+  const uint32_t kcutb = cost_key(key_cost(G.best_key) + prm.beam);
+  stage_reset(ts, g.nlevels);
+  for (uint32_t b = blockIdx.x * tile; b < n; b += kGB * tile) {
+    const uint32_t i = b + threadIdx.x;
+    uint32_t deg = 0, p0 = 0, k = 0;
+    if (threadIdx.x < tile && i < n) {
+      uint32_t l = l0;
+      while (base[l + 1] <= i) ++l;
+      const uint32_t st = L.bucket[g.level_base[l] + (i - base[l])];
+      const unsigned long long sv = L.slot[st];
+      const uint32_t z0 = g.off[st].z, z1 = g.off[st + 1].z;
+      k = (uint32_t)(sv >> 32);
+      const bool live = k <= kcutb;
+      p0 = z0;
+      deg = live ? z1 - z0 : 0u;
+    }
+    unsigned long long tt;
+    const uint32_t ex = (uint32_t)gexcl64(deg, s, &tt);
+    const uint32_t tot = (uint32_t)tt;
+    if (threadIdx.x < tile) {
+      t_beg[threadIdx.x] = p0;
+      t_ex[threadIdx.x] = ex;
+      t_key[threadIdx.x] = k;
+    }
+    __syncthreads();
+    for (uint32_t w = threadIdx.x; w < tot; w += kGT) {
+      const uint32_t j = search_le(t_ex, tile, w);
+      const size_t p = t_beg[j] + (w - t_ex[j]);
+      const uint4 h = g.phead[2 * p], hw = g.phead[2 * p + 1];
+      const uint32_t len = h.w & 0xffu;
+      float x = key_cost(t_key[j]);
+      if (len > 1u) {
+        x = canon(x + __uint_as_float(hw.x));
+        if (len > 2u) x = canon(x + __uint_as_float(hw.y));
+        if (len > 3u) x = canon(x + __uint_as_float(hw.z));
+        if (len > 4u) x = canon(x + __uint_as_float(hw.w));
+        const float* tw = g.ptail + p * g.pstride;
+        for (uint32_t q = 4; q + 1 < len; ++q) x = canon(x + tw[q]);
+      }
+      const uint32_t xk = cost_key(canon(x + __uint_as_float(h.z)));
+      if (xk > kcutb || xk >= kInfKey) continue;
+      const unsigned long long old = atomicMin(&L.slot[h.x], pack_tok(xk, h.y));
+      if (old == kEmpty) stage_touch<true>(ts, G, L, g, h.x, (h.w >> 8) ? (uint32_t)g.sclass[h.x] : kNoEps);
+    }
+    stage_flush<true>(ts, G, L, g);
+  }
 }
 
 // A frame without max-active whose touched states are more than one in 32 of
@@ -617,17 +710,90 @@ __global__ void __launch_bounds__(kGT) k_g_count(DevGraph g, const LaneDesc* __r
     }
   }
   if (nopath || over) return;
+  // The epsilon arcs (and, where the beam cutoff is the frame's, the lattice
+  // links) of the states the path kernel took, from a token's final cost: in a
+  // dense frame over their lists (nothing is emptied here), else as the loops
+  // below read each touched slot.
+  const uint32_t l0 = path_level(g, prm);
+  const bool count_links = (prm.flags & kFlagSparse) && prm.max_active == 0;
+  unsigned long long cnt_x = 0;
+  auto tally = [&](uint32_t st, uint32_t k) {
+    const uint32_t a0 = g.off[st].y, a1 = g.off[st + 1].y;
+    if (k > kcutb) return;
+    cnt_x += a1 - a0;
+    if (count_links)
+      for (uint32_t a = a0; a < a1; ++a) {
+        const uint32_t xk = cost_key(canon(key_cost(k) + __uint_as_float(g.xarc[a].y)));
+        if (xk <= kcutb && xk < kInfKey) cnt_x += 1ull << 32;
+      }
+  };
+  auto upper = [&](uint32_t st) -> bool {
+    const uint32_t c = l0 < g.nlevels ? (uint32_t)g.sclass[st] : kNoEps;
+    return c != kNoEps && c >= l0;
+  };
+  auto tallied = [&]() {
+    if (l0 >= g.nlevels) return;
+    cnt_x = gsum64(cnt_x, s);
+    if (threadIdx.x == 0 && cnt_x) G.part[3][blockIdx.x] += cnt_x;
+  };
+  if (dense_frame(prm, nt, g.S)) {
+    // (the state-bitmap kernel finds the survivors in the slot array itself;
+    // here a state per thread, then its arcs over the workgroup)
+    if (l0 >= g.nlevels) return;
+    uint32_t* const base = hist;                                    // [nlevels + 1]
+    uint32_t* const ex = hist + 256;                                // [kGT + 1]
+    uint32_t* const key = st_state;                                 // [kGT]
+    uint32_t* const beg = reinterpret_cast<uint32_t*>(st_pack);     // [kGT]
+    static_assert(256 + kGT < kHistBins && kMaxLevels + 2 <= 256, "the histogram's LDS");
+    if (threadIdx.x == 0) {
+      uint32_t n = 0;
+      for (uint32_t l = l0; l < g.nlevels; ++l) {
+        base[l] = n;
+        n += G.nb[l] + G.nbt[l];
+      }
+      base[g.nlevels] = n;
+    }
+    __syncthreads();
+    const uint32_t n = base[g.nlevels];
+    for (uint32_t b = blockIdx.x * kGT; b < n; b += kGB * kGT) {
+      const uint32_t i = b + threadIdx.x;
+      uint32_t k = 0xffffffffu, a0 = 0, deg = 0;
+      if (i < n) {
+        uint32_t l = l0;
+        while (base[l + 1] <= i) ++l;
+        const uint32_t st = L.bucket[g.level_base[l] + (i - base[l])];
+        k = (uint32_t)(L.slot[st] >> 32);
+        a0 = g.off[st].y;
+        const uint32_t a1 = g.off[st + 1].y;
+        deg = k <= kcutb ? a1 - a0 : 0u;
+      }
+      unsigned long long tot;
+      ex[threadIdx.x] = (uint32_t)gexcl64(deg, s, &tot);
+      key[threadIdx.x] = k;
+      beg[threadIdx.x] = a0;
+      cnt_x += deg;
+      __syncthreads();
+      if (count_links)
+        for (uint32_t w = threadIdx.x; w < (uint32_t)tot; w += kGT) {
+          const uint32_t j = search_le(ex, kGT, w);
+          const uint32_t xk = cost_key(canon(key_cost(key[j]) + __uint_as_float(g.xarc[beg[j] + (w - ex[j])].y)));
+          if (xk <= kcutb && xk < kInfKey) cnt_x += 1ull << 32;
+        }
+      __syncthreads();
+    }
+    if (blockIdx.x * kGT < n) tallied();
+    return;
+  }
   if (prm.max_active == 0) {
-    // dense frames: the state-bitmap kernel finds the survivors in the slot
-    // array itself
-    if (dense_frame(prm, nt, g.S)) return;
     // every survivor is kept: mark its state; its token stays in the slot,
     // where the compaction reads and resets it
     if (blockIdx.x * kGT >= nt) return;
     unsigned long long cnt = 0;
     for (uint32_t i = blockIdx.x * kGT + threadIdx.x; i < nt; i += kGB * kGT) {
       const uint32_t st = L.touched[i];
-      if ((uint32_t)(L.slot[st] >> 32) <= kcutb) {
+      const uint32_t k = (uint32_t)(L.slot[st] >> 32);
+      if (upper(st)) tally(st, k);
+      if (k <= kcutb) {
         atomicOr(&L.bitmap[st >> 5], 1u << (st & 31u));
         ++cnt;
       } else {
@@ -636,6 +802,7 @@ __global__ void __launch_bounds__(kGT) k_g_count(DevGraph g, const LaneDesc* __r
     }
     cnt = gsum64(cnt, s);
     if (threadIdx.x == 0 && cnt) atomicAdd(&G.n_surv, (uint32_t)cnt);
+    tallied();
     return;
   }
   if (blockIdx.x * kStage >= nt) return;
@@ -650,6 +817,7 @@ __global__ void __launch_bounds__(kGT) k_g_count(DevGraph g, const LaneDesc* __r
       const uint32_t st = L.touched[i];
       const unsigned long long v = L.slot[st];
       L.slot[st] = kEmpty;
+      if (upper(st)) tally(st, (uint32_t)(v >> 32));
       if ((uint32_t)(v >> 32) <= kcutb) {
         const uint32_t p = atomicAdd(&n_st, 1u);
         st_state[p] = st;
@@ -672,6 +840,7 @@ __global__ void __launch_bounds__(kGT) k_g_count(DevGraph g, const LaneDesc* __r
   if (use_hist)
     for (uint32_t i = threadIdx.x; i < (uint32_t)kHistBins; i += kGT)
       if (hist[i]) atomicAdd(&G.hist[i], hist[i]);
+  tallied();
 }
 
 // Max-active by radix select: step 0 decides whether the limit binds; every
@@ -1146,9 +1315,12 @@ __global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lane
   const LaneDesc& L = lanes[blockIdx.y];
   GridLane& G = gl[blockIdx.y];
   if (G.stop) return;
-  unsigned long long none, all;
+  unsigned long long none, all, eps_frame;
   part_prefix(G.part[2], 0, s, &none, &all);
-  for (uint32_t i = threadIdx.x; i <= (uint32_t)kMaxLevels; i += kGT) G.nb[i] = 0;
+  part_prefix(G.part[3], 0, s, &none, &eps_frame);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < kGB; i += kGT) G.part[3][i] = 0;
+  for (uint32_t i = threadIdx.x; i <= (uint32_t)kMaxLevels; i += kGT) G.nb[i] = G.nbt[i] = 0;
   for (uint32_t i = threadIdx.x; i < (uint32_t)kHistBins; i += kGT) G.hist[i] = 0;
   if (threadIdx.x != 0) return;
   if (G.bad) {
@@ -1162,7 +1334,7 @@ __global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lane
   const uint64_t nE = (uint32_t)all;
   if (prm.flags & kFlagSparse) {
     // (counted only; the kept links are formed after the forward pass)
-    G.raw_total += nE + (prm.max_active > 0 ? all >> 32 : G.eps_frame >> 32);
+    G.raw_total += nE + (prm.max_active > 0 ? all >> 32 : eps_frame >> 32);
   } else {
     const uint64_t end = G.link_base + nE + (all >> 32);
     G.raw_total += end - G.link_base;
@@ -1189,8 +1361,7 @@ __global__ void __launch_bounds__(kGT) k_g_end(const LaneDesc* __restrict__ lane
   G.W = G.W_next;
   G.n_touched = 0;
   G.n_surv = 0;
-  G.eps_arcs += (uint32_t)G.eps_frame;
-  G.eps_frame = 0;
+  G.eps_arcs += (uint32_t)eps_frame;
   G.xmask = 0;
   G.best_key = 0xffffffffu;  // the next frame's expansion takes the minimum
   G.disp = 0;
@@ -1210,7 +1381,8 @@ __global__ void k_g_finish(const LaneDesc* __restrict__ lanes, GridLane* gl) {
   info->status = status;
   info->frames_done = (int32_t)G.frames;
   info->overflow = ovf;
-  const uint64_t eps = G.eps_arcs + (uint32_t)G.eps_frame;  // (with those of a frame that stopped)
+  uint64_t eps = G.eps_arcs;
+  for (uint32_t i = 0; G.status != 0 && i < kGB; ++i) eps += (uint32_t)G.part[3][i];  // (a frame that stopped)
   info->arcs_expanded = G.arcs + eps;
   info->eps_arcs = eps;
   info->tokens = G.tokens;
@@ -1508,7 +1680,9 @@ void grid_frames(const DevGraph& g, const LaneDesc* lanes, void* glv, int B, con
     if (t == 0) hipLaunchKernelGGL(k_g_begin, one, dim3(64), 0, st, g, lanes, gl);
     if (prm.flags & WD_FLAG_DYNAMIC_LB) hipLaunchKernelGGL(k_g_expand_dyn, all, blk, 0, st, g, lanes, gl, prm, t);
     else hipLaunchKernelGGL(k_g_expand, all, blk, 0, st, g, lanes, gl, prm, t);
-    for (uint32_t l = 0; l < g.nlevels; ++l) hipLaunchKernelGGL(k_g_level, all, blk, 0, st, g, lanes, gl, prm, l);
+    const uint32_t lp = path_level(g, prm);
+    for (uint32_t l = 0; l < lp; ++l) hipLaunchKernelGGL(k_g_level, all, blk, 0, st, g, lanes, gl, prm, l);
+    if (lp < g.nlevels) hipLaunchKernelGGL(k_g_paths, all, blk, 0, st, g, lanes, gl, prm);
     hipLaunchKernelGGL(k_g_count, all, blk, 0, st, g, lanes, gl, prm);
     if (prm.max_active > 0) {
       hipLaunchKernelGGL(k_g_select, one, blk, 0, st, gl, prm, 0);
