@@ -145,6 +145,7 @@ struct LaneInfo {
   uint64_t out_nodes;
   uint64_t nwords;
   uint64_t out_raw;            // raw links written to the debug output
+  uint64_t found;              // link records kept by the link count
   uint32_t start_node;
   uint32_t best_node;
   float best_cost;

@@ -14,7 +14,8 @@
 // frame t in state order, each token's epsilon arcs in order), exactly the
 // layout the lattice pass reads.  Three launches: per-frame counts, one
 // workgroup per utterance turning them into offsets (and checking the link
-// store's capacity), then the links, each frame by one workgroup.
+// store's capacity), then the links, each frame by one workgroup (of a small
+// frame from the records that the count has kept).
 #include "wd_block.h"
 #include "wd_host.h"
 #include "wd_sparse.h"
@@ -27,12 +28,21 @@ constexpr uint32_t kLinkBlocks = 256;  // workgroups per utterance (frames in tu
 constexpr uint32_t kSpBWin = 2048;     // sparse utterances: states of one frame held in LDS
 constexpr uint32_t kSpList = 2048;     // live nodes listed together
 
+// Links of a frame that the count keeps for the write: a frame of a hundred
+// tokens has about as many, and 8 KB of LDS leave the count its workgroups per CU.
+// Both passes are bound by gathers of arcs and log-likelihoods; with the records
+// only the count does them (one utterance of 1000 frames on 5M states: lattice
+// stage 1.53 ms before, 1.50 ms with them).
+constexpr uint32_t kFound = 512;
+
 struct LinkShared {
   BlockScratch bs;
   uint32_t pre[kLT];    // exclusive prefix of the tile's tokens' arc counts
   uint32_t beg[kLT];    // first arc of each token of the tile
   float cost[kLT];      // token cost
   uint32_t cls[kLT];    // token state's epsilon level (epsilon runs)
+  uint4 found[kFound];  // a frame's links, as the count finds them
+  unsigned long long base;
 };
 
 // The node of state s among one frame's nodes [n0, n1) (sorted by state), or
@@ -51,9 +61,12 @@ __device__ __forceinline__ uint64_t node_of(const LaneDesc& L, uint64_t n0, uint
 // frame t-1) or the epsilon links (sources: the nodes of frame t).  Counts
 // them (kWrite false: returns the count in every thread) or writes them from
 // link `at` on (returns the count, sets *xmask and *bad).
+// `found` (count mode, or null): the links' records {arc, source node,
+// destination state, x bits} go to LDS, up to kFound of them.
 template <bool kEps, bool kWrite>
 __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& L, LinkShared& sh, uint32_t& par,
-                                             int t, uint32_t cut, uint64_t at, uint32_t* xmask, uint32_t* bad) {
+                                             int t, uint32_t cut, uint64_t at, uint32_t* xmask, uint32_t* bad,
+                                             bool found = false) {
   const uint32_t tid = threadIdx.x;
   const uint64_t p0 = L.node_off[kEps ? t : t - 1], p1 = L.node_off[kEps ? t + 1 : t];
   const uint64_t d0 = L.node_off[t], d1 = L.node_off[t + 1];  // destinations: frame t
@@ -101,7 +114,7 @@ __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& 
         const uint32_t xk = cost_key(x);
         in = xk <= cut && xk < kInfKey;
       }
-      if (!kWrite) {
+      if (!kWrite && !found) {
         cnt += in ? 1u : 0u;
         continue;
       }
@@ -109,6 +122,11 @@ __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& 
       const uint32_t pos = n + block_excl_scan<kLWv>(in ? 1u : 0u, sh.bs, par, &nsub);
       n += nsub;
       if (!in) continue;
+      if (!kWrite) {
+        const uint32_t q = (uint32_t)at + pos;
+        if (q < kFound) sh.found[q] = make_uint4(r.w, (uint32_t)(q0 + j), r.x, xb);
+        continue;
+      }
       const uint64_t dn = node_of(L, d0, d1, r.x);
       if (dn == ~0ull) {
         *bad = 1;
@@ -126,7 +144,7 @@ __device__ __forceinline__ uint32_t link_run(const DevGraph& g, const LaneDesc& 
     }
     __syncthreads();  // every read of the tile's arrays done before the next tile
   }
-  if (!kWrite) {
+  if (!kWrite && !found) {
     uint32_t all;
     (void)block_excl_scan<kLWv>(cnt, sh.bs, par, &all);
     return all;
@@ -291,11 +309,26 @@ __global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc*
     }
     return;
   }
+  // The links found are kept for the write (in the output buffer, free until
+  // the final merge), so that it does not gather arcs and log-likelihoods again
+  // (a frame's hundred tokens touch most of its 24 KB row): a frame of more than
+  // kFound links, or beyond the buffer, is formed twice.
+  WD_GLOBAL uint4* const kept = (WD_GLOBAL uint4*)L.out_links;
+  const uint64_t cap = L.kept_cap * (sizeof(OutLink) / sizeof(uint4));
   for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
     const uint32_t cut = cost_key(L.cut[t]);
-    const uint32_t ne = t > 0 ? link_run<false, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr) : 0u;
-    const uint32_t nx = link_run<true, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr);
+    const uint32_t ne = t > 0 ? link_run<false, false>(g, L, sh, par, t, cut, 0, nullptr, nullptr, true) : 0u;
+    const uint32_t nx = link_run<true, false>(g, L, sh, par, t, cut, ne, nullptr, nullptr, true);
+    const uint32_t n = ne + nx;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      sh.base = n <= kFound ? atomicAdd((unsigned long long*)&L.info->found, (unsigned long long)n) : kEmpty;
+    __syncthreads();
+    const uint64_t base = sh.base;
+    const bool fits = n <= kFound && base + n <= cap;
+    for (uint32_t i = threadIdx.x; fits && i < n; i += kLT) kept[base + i] = sh.found[i];
     if (threadIdx.x == 0) {
+      L.kframe[2 * t] = fits ? base : kEmpty;
       L.link_xoff[t] = ne;
       L.link_end[t] = nx;
       // the step profile's frame record takes the frame's link count
@@ -361,11 +394,34 @@ __global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc*
     }
     return;
   }
+  const WD_GLOBAL uint4* const kept = (const WD_GLOBAL uint4*)L.out_links;
   for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
     const uint32_t cut = cost_key(L.cut[t]);
     uint32_t xmask = 0;
-    if (t > 0) (void)link_run<false, true>(g, L, sh, par, t, cut, L.link_off[t], &xmask, &bad);
-    (void)link_run<true, true>(g, L, sh, par, t, cut, L.link_xoff[t], &xmask, &bad);
+    const uint64_t base = L.kframe[2 * t], l0 = L.link_off[t];
+    if (base != kEmpty) {
+      // the count's records; the destinations found among the frame's nodes
+      const uint32_t n = (uint32_t)(L.link_end[t] - l0), ne = (uint32_t)(L.link_xoff[t] - l0);
+      const uint64_t d0 = L.node_off[t], d1 = L.node_off[t + 1];
+      for (uint32_t i = threadIdx.x; i < n; i += kLT) {
+        const uint4 r = kept[base + i];
+        const uint64_t dn = node_of(L, d0, d1, r.z);
+        if (dn == ~0ull) {
+          bad = 1;
+          continue;
+        }
+        L.links[l0 + i] = make_uint4(r.x, r.y, (uint32_t)dn, r.w);
+        if (i >= ne) {
+          const uint32_t cls = g.sclass[L.n_state[r.y]];
+          L.link_lvl[l0 + i] = (uint8_t)cls;
+          xmask |= 1u << (cls < 31u ? cls : 31u);
+        }
+        if (L.n_pack[dn] == pack_tok(cost_key(__uint_as_float(r.w)), r.x)) L.n_pred[dn] = r.y;
+      }
+    } else {
+      if (t > 0) (void)link_run<false, true>(g, L, sh, par, t, cut, l0, &xmask, &bad);
+      (void)link_run<true, true>(g, L, sh, par, t, cut, L.link_xoff[t], &xmask, &bad);
+    }
     const uint32_t all = block_or<kLWv>(xmask, sh.bs, par);
     if (threadIdx.x == 0) L.xmask[t] = all;
   }
