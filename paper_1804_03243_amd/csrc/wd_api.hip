@@ -80,9 +80,6 @@ struct Regions {
   LaneDesc* desc;
   LaneInfo* info;
   uint32_t* bad;
-  unsigned long long* slot;
-  uint32_t* bitmap;
-  uint32_t* used;
   void* grid;    // chip-wide: GridLanes
   void* ctl;     // the clusters' control blocks
   uint64_t grid_bytes;
@@ -157,9 +154,6 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   char* out_words = take(4 * c.words);
   char* prof = take(8 * c.prof);
   R.total = p;
-  R.slot = (unsigned long long*)slot;
-  R.bitmap = (uint32_t*)bitmap;
-  R.used = (uint32_t*)used;
   if (lanes) {
     for (int b = 0; b < B; ++b) {
       LaneDesc& L = lanes[b];
@@ -371,16 +365,7 @@ static wd_status run_setup(wd_stream* run, const wd_graph* g, int32_t B, const f
                       "lane upload")))
     return st;
   const uint64_t S = (uint64_t)g->S;
-  launch_fill_u32((uint32_t*)R.info, (uint64_t)B * sizeof(LaneInfo) / 4, 0u, s);
-  launch_fill_u32(R.bad, (uint64_t)B, 0u, s);
-  if (chip_wide_mode(p)) {
-    launch_fill_u64(R.slot, (uint64_t)B * S, kEmpty, s);
-    launch_fill_u32(R.bitmap, (uint64_t)B * R.bitmap_words, 0u, s);
-  } else {
-    // (the slots and the bitmap: by a decode's first large frame, if it has one)
-    launch_clear_clusters(R.desc, B, s);
-  }
-  launch_fill_u32(R.used, (uint64_t)B * R.used_words, 0u, s);
+  launch_setup(R.desc, B, R.bad, R.used_words, S, R.bitmap_words, chip_wide_mode(p), s);
   if (p->flags & WD_FLAG_TIMING)
     for (auto& e : run->ev)
       if ((st = hip_check(hipEventCreate(&e), "event"))) return st;
@@ -771,10 +756,7 @@ extern "C" wd_status wd_decode_noalloc(const wd_graph* g, const float* loglikes,
   // before writing is reset here, as for a caller's workspace
   if ((st = hip_check(hipMemcpyAsync(R.desc, &lane, sizeof(LaneDesc), hipMemcpyHostToDevice, s), "lane upload")))
     return st;
-  launch_fill_u32((uint32_t*)R.info, sizeof(LaneInfo) / 4, 0u, s);
-  launch_fill_u32(R.bad, 1, 0u, s);
-  launch_clear_clusters(R.desc, 1, s);
-  launch_fill_u32(R.used, R.used_words, 0u, s);
+  launch_setup(R.desc, 1, R.bad, R.used_words, (uint64_t)g->S, R.bitmap_words, false, s);
   const Params prm{p->beam, p->max_active, p->lattice_beam, p->flags};
   launch_check_loglikes(R.desc, 1, g->P, R.bad, s);
   launch_forward(g->dg, R.desc, 1, prm, R.bad, s);

@@ -55,11 +55,10 @@ void launch_pack_results(const LaneDesc* lanes, int B, void* dst, hipStream_t s)
 // Sets T, t0 and open of lanes[0..B) (streaming) from host values passed as
 // kernel arguments.
 void launch_set_frames(LaneDesc* lanes, int B, const int32_t* T, const int32_t* t0, int32_t open, hipStream_t s);
-// Resets the clusters' control blocks (one-workgroup mode, before a launch of
-// the forward pass; launch_set_frames does it for streams).
-void launch_clear_clusters(const LaneDesc* lanes, int B, hipStream_t s);
-void launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s);
-void launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
+// Resets what a decode reads before writing (launch_set_frames resets the
+// cluster headers again for a stream's advances).
+void launch_setup(const LaneDesc* lanes, int B, uint32_t* bad, uint64_t used_words, uint64_t S, uint64_t bitmap_words,
+                  bool chip, hipStream_t s);
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 

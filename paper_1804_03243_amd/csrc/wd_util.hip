@@ -1,5 +1,7 @@
 // Small per-decode kernels around the decoder: input checks, fills, the lane
 // frame ranges of a stream, and the packing of results for the host.
+#include <algorithm>
+
 #include "wd_cluster.h"
 #include "wd_host.h"
 
@@ -24,18 +26,6 @@ __global__ void k_check_loglikes(const LaneDesc* __restrict__ lanes, uint32_t P,
   }
   for (; i < n; i += stride) b |= bad_loglike(L.ll[i]);
   if (b) atomicOr(&bad[blockIdx.y], 1u);
-}
-
-__global__ void k_fill_u64(unsigned long long* p, uint64_t n, unsigned long long v) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = v;
 }
 
 // Results of every finished utterance (links, nodes, words) packed into one
@@ -98,12 +88,47 @@ __global__ void k_set_frames(LaneDesc* lanes, FrameSet f) {
   clear_cluster(L);
 }
 
-__global__ void k_clear_clusters(const LaneDesc* __restrict__ lanes) {
-  clear_cluster(lanes[blockIdx.x]);
+// Everything a decode reads before writing, in one launch: the utterance's
+// counters, its node bitmap and cluster headers; with `fill`, its slots and
+// state bitmap too.
+__global__ void __launch_bounds__(256) k_setup(const LaneDesc* __restrict__ lanes, uint32_t* bad, uint64_t used_words,
+                                               uint64_t S, uint64_t bitmap_words, bool fill) {
+  const LaneDesc& L = lanes[blockIdx.y];
+  const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+  const uint64_t sum_words = L.slot2 && fill ? (bitmap_words + 31) / 32 : 0;
+  for (uint64_t i = i0; i < used_words; i += step) L.used[i] = 0;
+  if (fill) {
+    for (uint64_t i = i0; i < S; i += step) {
+      L.slot[i] = kEmpty;
+      if (L.slot2) L.slot2[i] = kEmpty;
+    }
+    for (uint64_t i = i0; i < bitmap_words; i += step) L.bitmap[i] = 0;
+    // (the bitmap's summary, where it has room: large frames keep it there)
+    for (uint64_t i = i0; i < sum_words && i < L.frame_cap; i += step) L.surv_state[i] = 0;
+  }
+  if (blockIdx.x != 0) return;
+  WD_GLOBAL uint32_t* info = (WD_GLOBAL uint32_t*)L.info;
+  for (uint32_t i = threadIdx.x; i < sizeof(LaneInfo) / 4u; i += 256)
+    info[i] = i == offsetof(LaneInfo, slots_clean) / 4u && fill ? 1u : 0u;
+  if (threadIdx.x == 0) bad[blockIdx.y] = 0;
+  clear_cluster(L);
 }
 
-void launch_clear_clusters(const LaneDesc* lanes, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_clusters, dim3(B), dim3(128), 0, s, lanes);
+// One-workgroup mode empties an utterance's slots (16 bytes per state) here for
+// up to kFillLanes utterances, and otherwise in the utterance's first large
+// frame, if it has one.  The chip empties 4.5 TB/s, the frame's workgroup 90 GB/s
+// when no helper is up: one utterance on 30M states with three large frames
+// spent 5.6 of 20.6 ms on that and spends 0.11 ms here, while 256 utterances on
+// 5M states would spend 5 of 26 ms here.  The fill of some 50 utterances takes as long
+// as the frame's own emptying; the line lies where it costs a sixth of that.
+constexpr int kFillLanes = 8;
+
+void launch_setup(const LaneDesc* lanes, int B, uint32_t* bad, uint64_t used_words, uint64_t S, uint64_t bitmap_words,
+                  bool chip, hipStream_t s) {
+  const bool fill = chip || B <= kFillLanes;
+  const uint64_t n = fill ? std::max(used_words, S) : used_words;
+  const uint64_t gx = std::min<uint64_t>(std::max<uint64_t>((n + 1023) / 1024, 1), B >= 64 ? 16 : 2048 / B);
+  hipLaunchKernelGGL(k_setup, dim3((uint32_t)gx, B), dim3(256), 0, s, lanes, bad, used_words, S, bitmap_words, fill);
 }
 
 void launch_set_frames(LaneDesc* lanes, int B, const int32_t* T, const int32_t* t0, int32_t open, hipStream_t s) {
@@ -125,14 +150,6 @@ void launch_check_loglikes(const LaneDesc* lanes, int B, uint32_t P, uint32_t* b
   // ~2048 workgroups in all (at least 16 per utterance)
   const int gx = B >= 128 ? 16 : 2048 / B;
   hipLaunchKernelGGL(k_check_loglikes, dim3(gx, B), dim3(256), 0, s, lanes, P, bad);
-}
-
-void launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s) {
-  if (n) hipLaunchKernelGGL(k_fill_u64, dim3(1024), dim3(256), 0, s, p, n, v);
-}
-
-void launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
-  if (n) hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, s, p, n, v);
 }
 
 }  // namespace wd
