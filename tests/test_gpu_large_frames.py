@@ -156,3 +156,41 @@ def test_capacities(wf, oracle_mod, noisy):
             wf.decode_batch(graph, [x], *args, caps=caps, max_retries=0, mode="workgroup")
         assert e.value.status == wf.WD_ECAPACITY
         assert_same(wf.decode(graph, x, *args, caps=caps, mode="workgroup"), o)
+
+
+@pytest.mark.parametrize("ma", [120, 200, 320, 500])
+def test_link_records(wf, oracle_mod, noisy, ma):
+    """Frames with fewer and with more links than a workgroup keeps records of
+    (512), of both in one decode; and records beyond the output buffer."""
+    import torch
+    g, graph = noisy
+    L, args = flat(12, 200, 16), (12.0, ma, 6.0)
+    r = check(wf, oracle_mod, g, graph, L, args)
+    assert r.stats["max_tokens"] < 600
+    caps = wf.wd_caps(0, 0, 0, 0, 40, 0)
+    assert_same(wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, caps=caps, mode="workgroup"),
+                oracle_mod.decode(g, L, *args))
+
+
+@pytest.mark.parametrize("depth", [2, 3, 4, 9])
+@pytest.mark.parametrize("beam,ma", [(11.0, 0), (11.0, 1500)])
+def test_chip_wide_levels(wf, oracle_mod, depth, beam, ma):
+    """Epsilon levels on both sides of the one from which one launch takes them
+    all, and by levels throughout."""
+    g = graph_of(20_000, 60_000, 100, 0.3, depth, 30 + depth)
+    graph = wf.Graph(g, 100)
+    L, args = flat(9, 100, 17), (beam, ma, 6.0)
+    check(wf, oracle_mod, g, graph, L, args, "chip")
+    import torch
+    r = wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, mode="chip", flags=wf.WD_FLAG_EPS_LEVELS)
+    assert_same(r, oracle_mod.decode(g, L, *args))
+
+
+def test_held_results(wf, oracle_mod, noisy):
+    """Results stay as they are while later decodes download theirs."""
+    import torch
+    g, graph = noisy
+    Ls = [flat(5, 200, 40 + k) for k in range(6)]
+    rs = [wf.decode(graph, torch.from_numpy(x).to(graph.device), 11.0, 2500, 6.0) for x in Ls]
+    for x, r in zip(Ls, rs):
+        assert_same(r, oracle_mod.decode(g, x, 11.0, 2500, 6.0))
