@@ -15,8 +15,8 @@ size), reported only while the kernel sources hash to the ones the counters
 were taken on; `other_workloads` times the same utterance streamed in chunks
 of 32 and 8 frames, the host determinisation of its lattice, the
 64-utterance batch on the same graph (with its own roofline), and the
-chip-wide mode on the wide-beam 2M-state graph (with and without incremental
-lattice pruning, and with dynamic load balancing); `roofline.copy_ceiling_gbs`
+chip-wide mode on the wide-beam 2M-state graph (with the lattice pruned from
+live nodes, from a raw link store, and with dynamic load balancing); `roofline.copy_ceiling_gbs`
 is what a plain device copy reaches.  `--copy-kernel-bytes N` only runs a plain N-byte device copy
 (the counter calibration run) and exits.
 """

@@ -112,8 +112,10 @@ typedef struct {
 /* One-workgroup mode: take the epsilon closure level by level (one pass per
  * epsilon level, each a round of dependent memory reads) even when the graph
  * has an epsilon path table (wd_graph_eps_paths), where by default every
- * epsilon path of a state within the beam is relaxed at once.  The result is
- * identical; the flag exists for the A/B comparison. */
+ * epsilon path of a state within the beam is relaxed at once.  Chip-wide mode:
+ * all levels by levels, where by default those from the third on are taken by
+ * paths in one launch.  The result is identical; the flag exists for the A/B
+ * comparison. */
 #define WD_FLAG_EPS_LEVELS 128u
 /* Words per frame of wd_result_phases: WD_PHASE_STAMPS wall-clock stamps, at
  * (0) the frame's start, the end of (1) the emitting expansion and its best
@@ -125,7 +127,8 @@ typedef struct {
  * links << 32 (the links are formed after the forward pass, every frame at
  * once, and their count is filled in then), and word 11 = emitting work
  * items | LDS-table epsilon bucket entries << 32 (touched states with
- * epsilon arcs). */
+ * epsilon arcs; of a frame
+ * beyond that table the number of workgroups that ran it << 32). */
 #define WD_PHASE_STAMPS 10
 #define WD_PHASE_SLOTS 12
 /* Stamps of the lattice pass (wd_result_lattice_phases, WD_FLAG_PHASES): at

@@ -16,8 +16,9 @@
 // Nothing waits for a workgroup that may not be running: helpers register for
 // a run of frames while the leader holds the registration open for a few
 // microseconds, and the barriers count the registered ones only.  A helper
-// that is idle for kIdleTicks (and a quarter of the time it has worked) leaves, so the CUs of utterances that never have
-// a large frame are free for other work soon after the launch.
+// that is idle for kIdleTicks (and a quarter of the time it has worked) leaves,
+// so the CUs of utterances that never have a large frame are free for other
+// work soon after the launch.
 //
 // Per frame t, with the tokens of frame t - 1 as bits of a state bitmap (and
 // their packed tokens in the slot array of that frame's parity):

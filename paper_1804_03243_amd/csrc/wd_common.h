@@ -136,9 +136,8 @@ struct LaneInfo {
   uint64_t tokens;             // surviving tokens summed over frames (= nodes recorded)
   uint64_t max_tokens;
   uint64_t links;              // raw lattice links (all ever recorded)
-  uint64_t need_links;         // link store capacity the decode needed (peak; with
-                               // incremental pruning: the compacted region)
-  uint64_t need_window;        // incremental pruning: raw links of the largest window
+  uint64_t need_links;         // link store capacity the decode needed
+  uint64_t need_window;        // always 0 (reported for callers that size a window store by it)
   uint64_t need_frame_tokens;  // largest per-frame touched-state count
   uint64_t need_frame_arcs;    // largest per-frame emitting work
   uint64_t kept;               // kept lattice links

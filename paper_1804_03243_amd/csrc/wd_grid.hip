@@ -5,13 +5,15 @@
 // each a kernel over 1024 workgroups per utterance, launched frame by frame on
 // the caller's stream: emitting expansion with 64-bit atomicMin recombination
 // on the per-state slot array (Alg. 1) over the prefix-sum work space of
-// Sec. 3.3; one kernel per epsilon level; survivors of the beam cutoff with a
+// Sec. 3.3; one kernel per epsilon level, or for the upper ones together by
+// their paths; survivors of the beam cutoff with a
 // global radix histogram for max-active; compaction in state order through the
 // state bitmap; degree prefix sums; lattice links (Sec. 3.4).  Every position
 // (frontier, links) comes from a two-level scan: per-workgroup sums, one
 // workgroup scanning the sums, a per-workgroup rescan.  Frontier and link
 // order are therefore the same as in the one-workgroup pass and the result is
-// identical.  The backward pruning sweep of Sec. 3.5 has a chip-wide form too.
+// identical.  The lattice is pruned from live nodes after the last frame; with the
+// raw link store the backward pruning sweep of Sec. 3.5 has a chip-wide form too.
 // Every kernel reads the frame's sizes from device memory, so the host never
 // waits between frames; an utterance whose status is set skips the rest.
 #include "wd_block.h"
