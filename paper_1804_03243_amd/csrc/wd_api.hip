@@ -96,7 +96,9 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
     return at;
   };
   const uint64_t S = (uint64_t)g->S;
-  const uint64_t F1 = c.frame + 1;
+  // (frames in LDS are not held to the frame capacity: up to kRankMax tokens of
+  // one go to the workspace when a larger frame or a stream's next launch follows)
+  const uint64_t F1 = std::max<uint64_t>(c.frame, std::min<uint64_t>(S, kRankMax)) + 1;
   const uint64_t T2 = (uint64_t)max_T + 2;
   R.desc = (LaneDesc*)take(sizeof(LaneDesc));
   R.info = (LaneInfo*)take(sizeof(LaneInfo));

@@ -194,3 +194,23 @@ def test_held_results(wf, oracle_mod, noisy):
     rs = [wf.decode(graph, torch.from_numpy(x).to(graph.device), 11.0, 2500, 6.0) for x in Ls]
     for x, r in zip(Ls, rs):
         assert_same(r, oracle_mod.decode(g, x, 11.0, 2500, 6.0))
+
+
+@pytest.mark.parametrize("beam", [5.0, 9.0, 30.0])
+def test_small_frame_capacity(wf, oracle_mod, beam):
+    """Frames in LDS are not held to the frame capacity, so their frontiers
+    (here of up to 1500 tokens, between a stream's launches and from lane to
+    lane) must not reach the arrays behind the ones sized by it."""
+    import torch
+    g = graph_of(1500, 4200, 50, 0.2, 4, 60)
+    graph = wf.Graph(g, 50)
+    Ls = [flat(9, 50, 61 + b) for b in range(3)]
+    args = (beam, 0, 6.0)
+    print(f"\n[gpu case] small frame capacity, beam {beam}", flush=True)
+    s = wf.Stream(graph, 3, 16, *args, mode="workgroup", caps=wf.wd_caps(40, 0, 0, 0, 0, 0))
+    for a, b in ((0, 2), (2, 3), (3, 9)):
+        s.push([torch.from_numpy(x[a:b]).to(graph.device) for x in Ls])
+    for x, r in zip(Ls, s.end()):
+        o = oracle_mod.decode(g, x, *args)
+        assert_same(r, o)
+        assert beam < 30.0 or o.stats["max_tokens"] > 1024
