@@ -39,6 +39,7 @@
 #include <stddef.h>
 
 #include "wd_block.h"
+#include "wd_spin.h"
 
 namespace wd {
 
@@ -163,7 +164,7 @@ typedef WD_GLOBAL ClusterCtl::Frame CtlFrame;
 // Barrier over the run's N workgroups.  `gen` is the arrivals that complete
 // the last one, the same in every thread; the count runs on over the runs of a
 // launch, so that a workgroup still leaving a run's last barrier is not caught
-// by the next run.  A wait beyond kSpinTicks marks the run bad; the callers
+// by the next run.  A wait beyond its limit marks the run bad; the callers
 // stop at the next check.
 __device__ __forceinline__ void cl_barrier(Ctl* C, uint32_t N, uint32_t& gen) {
   gen += N;
@@ -173,9 +174,9 @@ __device__ __forceinline__ void cl_barrier(Ctl* C, uint32_t N, uint32_t& gen) {
     if (threadIdx.x == 0) {
       cl_add<uint32_t>(&C->bar, 1u);
       const uint32_t target = gen;
-      if (cl_load(&C->bar) < target) {
+      if (!arrived(cl_load(&C->bar), target)) {
         const uint64_t t0 = wall_clock64();
-        while (cl_load(&C->bar) < target)
+        while (!arrived(cl_load(&C->bar), target))
           if (wall_clock64() - t0 > kSpinTicks) {
             cl_store(&C->bad, 1u);
             break;
