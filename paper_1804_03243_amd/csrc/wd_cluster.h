@@ -50,7 +50,6 @@ constexpr uint32_t kClDigits = 3;          // radix digits of a 32-bit key (11, 
 constexpr uint64_t kIdleTicks = 30000;     // 300 µs of the 100 MHz clock
 constexpr uint64_t kJoinTicks = 400;       // a run waits for its helpers this long at most (4 µs)
 constexpr uint32_t kRegroupFrames = 4;     // frames after which a run takes in late helpers
-constexpr uint64_t kSpinTicks = 200000000; // a wait this long (2 s) is an error, not a hang
 // back to the LDS path once a frame is this small
 constexpr uint32_t kSmallTokens = 512;
 constexpr uint32_t kSmallTouched = 1400;
@@ -175,9 +174,9 @@ __device__ __forceinline__ void cl_barrier(Ctl* C, uint32_t N, uint32_t& gen) {
       cl_add<uint32_t>(&C->bar, 1u);
       const uint32_t target = gen;
       if (!arrived(cl_load(&C->bar), target)) {
-        const uint64_t t0 = wall_clock64();
+        SpinClock spin(wall_clock64());
         while (!arrived(cl_load(&C->bar), target))
-          if (wall_clock64() - t0 > kSpinTicks) {
+          if (spin.beyond(wall_clock64())) {
             cl_store(&C->bad, 1u);
             break;
           }
@@ -1023,9 +1022,9 @@ __device__ __forceinline__ uint32_t cl_wait(Ctl* C, uint32_t& go_lds, uint32_t& 
       // answer, and see whether the leader took it in
       seen = run;
       cl_store(&C->join[id], run);
-      const uint64_t t0 = wall_clock64();
+      SpinClock spin(wall_clock64());
       unsigned long long m = cl_load(&C->members);
-      while ((uint32_t)(m >> 32) != run && cl_load(&C->cmd) == run && wall_clock64() - t0 < kSpinTicks)
+      while ((uint32_t)(m >> 32) != run && cl_load(&C->cmd) == run && !spin.beyond(wall_clock64()))
         m = cl_load(&C->members);
       if ((uint32_t)(m >> 32) != run || !((m >> id) & 1u)) continue;
       const uint32_t mask = (uint32_t)m;

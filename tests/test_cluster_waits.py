@@ -9,6 +9,16 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = r"""
 #include "wd_spin.h"
 extern "C" int arrived(unsigned now, unsigned target) { return wd::arrived(now, target); }
+// ticks that looks `step` apart take until the wait is beyond its limit; one of them comes `pause` late
+extern "C" unsigned long long limit(unsigned long long step, unsigned long long pause) {
+  unsigned long long now = 1ull << 40;
+  wd::SpinClock c(now);
+  for (unsigned long long i = 0, run = 0;; ++i) {
+    now += step + (i == 1 ? pause : 0);
+    run += step;
+    if (c.beyond(now)) return run;
+  }
+}
 """
 
 
@@ -20,6 +30,8 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_1804_03243_amd", "csrc"),
                     "-o", out, str(d / "spin.cpp")], check=True)
     so = ctypes.CDLL(out)
+    so.limit.restype = ctypes.c_uint64
+    so.limit.argtypes = [ctypes.c_uint64] * 2
     return so
 
 
@@ -35,3 +47,14 @@ def test_barrier_count_runs_over(lib, base):
         for k in range(32):
             assert lib.arrived((target + k) % 2 ** 32, target % 2 ** 32), (gen, k)
         gen = target
+
+
+@pytest.mark.parametrize("step", [40, 100, 900])
+def test_limit_counts_running_time(lib, step):
+    """Two seconds of looks at the clock, however long the queue was off the
+    device between two of them."""
+    two, ten_us = 200_000_000, 1000
+    assert two <= lib.limit(step, 0) <= two + step
+    assert two - ten_us <= lib.limit(step, 0) - step <= two
+    for pause in (10 ** 6, 10 * two, 10 ** 12):
+        assert two - ten_us <= lib.limit(step, pause) <= two + step
