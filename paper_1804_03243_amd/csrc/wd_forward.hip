@@ -1035,8 +1035,9 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     info->tokens = sh.c_tokens;
     info->max_tokens = sh.c_max_tokens;
     // (the large frames' raw links; the link kernels count the other frames'
-    // after the forward pass, or all of them)
-    info->links = sh.c_links;
+    // after the forward pass, or all of them.  Of a decode that stopped: none, a
+    // run that stops does not wait for its helpers' counts)
+    info->links = status == 0 ? sh.c_links : 0ull;
     info->need_frame_tokens = sh.c_need_frame;
     info->need_frame_arcs = sh.c_need_arcs;
     info->last_tokens = n_prev;

@@ -214,3 +214,25 @@ def test_small_frame_capacity(wf, oracle_mod, beam):
         o = oracle_mod.decode(g, x, *args)
         assert_same(r, o)
         assert beam < 30.0 or o.stats["max_tokens"] > 1024
+
+
+@pytest.mark.parametrize("caps", [(2500, 0, 0), (0, 3000, 0), (0, 0, 4000)])
+def test_stopped_decode_stats(wf, noisy, caps):
+    """A decode that outgrows a capacity reports the same counters every time,
+    and no raw links."""
+    import torch
+    _, graph = noisy
+    x = torch.from_numpy(flat(8, 200, 12)).to(graph.device)
+    p = wf.wd_params(12.0, 3000, 6.0, wf.WD_FLAG_ONE_WORKGROUP)
+    nb, used = wf.wd_workspace_bytes(graph.handle, 1, 8, p, wf.wd_caps(*caps, 0, 0, 0))
+    ws = torch.empty(nb + 256, dtype=torch.uint8, device=graph.device)
+    seen = []
+    print(f"\n[gpu case] large frames, stopped at capacities {caps}", flush=True)
+    for _ in range(6):
+        st, r = wf.wd_decode(graph.handle, x.data_ptr(), 8, p, used, (ws.data_ptr() + 255) // 256 * 256, nb,
+                             torch.cuda.current_stream().cuda_stream)
+        assert st == wf.WD_ECAPACITY
+        out = wf.wd_result_read(r, False, False)
+        wf.wd_result_free(r)
+        seen.append((out.stats, out.needed))
+    assert seen[0][0]["raw_links"] == 0 and all(s == seen[0] for s in seen[1:]), seen
