@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "wd_host.h"
+#include "wd_pinned.h"
 
 namespace wd {
 
@@ -235,49 +236,29 @@ wd_status check_params(const wd_params* p) {
 
 namespace wd {
 
-// Pinned host memory that result downloads land in, a few blocks per device.
-// A decode leases a free block, the copy engine writes its packed results
-// there, and the results view them in place: the block goes back when the last
-// result of the call is freed.  (Copied into vectors, a batch's 25 MB of results
-// cost 6 ms of page faults and copies, a wide lattice's 70 MB 20 ms.)  At most
-// kPinnedBlocks blocks of at most kPinnedMax bytes; a call that finds none free
-// (in a program that keeps its results) downloads into ordinary memory.
-constexpr int kPinnedBlocks = 3;
-constexpr uint64_t kPinnedMax = 512ull << 20;
-
-struct PinnedBlock {
-  char* p = nullptr;
-  uint64_t cap = 0;
-  bool leased = false;
-};
-struct PinnedPool {
-  std::mutex mu;
-  PinnedBlock block[kPinnedBlocks];
-};
-
-// A leased block; gives it back when the last holder is gone.
-struct PinnedLease {
-  PinnedPool* pool;
-  PinnedBlock* block;
-  char* p;
-  ~PinnedLease() {
-    std::lock_guard<std::mutex> lk(pool->mu);
-    block->leased = false;
+struct HipHost {
+  static char* alloc(uint64_t bytes) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess) return (char*)p;
+    (void)hipGetLastError();  // (the caller goes on without it)
+    return nullptr;
   }
+  static void release(char* p) { (void)hipHostFree(p); }
 };
+typedef PinnedPool<HipHost> HipPinned;
 
 }  // namespace wd
 
 struct wd_result {
   wd_status status = WD_OK;
   float cost = 0.0f;
-  // words, links and nodes: in the lease's block, or in own
+  // words, links and nodes: in the lease's block, or in own memory
   const int32_t* words = nullptr;
   const wd_lat_arc* links = nullptr;
   const wd_lat_node* nodes = nullptr;
   int64_t n_words = 0, n_links = 0, n_nodes = 0;
-  std::shared_ptr<wd::PinnedLease> lease;
-  std::vector<char> own;
+  std::shared_ptr<wd::HipPinned::Lease> lease;
+  std::unique_ptr<char[]> own;
   std::vector<wd_lat_arc> raw;
   std::vector<wd_token> tokens;
   std::vector<float> best, cutb, cut;
@@ -433,38 +414,14 @@ static const char* status_message(wd_status st) {
                               : "decode failed";
 }
 
-// A block of at least `bytes` of the current device's pool in *out, or null
-// when none is free (or the size is beyond the pool's).
-static wd_status lease_pinned(uint64_t bytes, std::shared_ptr<PinnedLease>* out) {
-  static PinnedPool* pools = new PinnedPool[64];  // (kept until the process ends: results may outlive statics)
-  out->reset();
+// The current device's pinned memory.
+static wd_status pinned_of_current_device(HipPinned** out) {
+  static HipPinned* pools = new HipPinned[64];  // (kept until the process ends: results may outlive statics)
   int dev = 0;
   wd_status st = hip_check(hipGetDevice(&dev), "device");
   if (st != WD_OK) return st;
   if (dev < 0 || dev >= 64) return fail(WD_EINVAL, "pinned memory: device index out of range");
-  if (bytes > kPinnedMax) return WD_OK;
-  PinnedPool& pool = pools[dev];
-  std::lock_guard<std::mutex> lk(pool.mu);
-  PinnedBlock* best = nullptr;  // a free block, preferably the smallest that holds the bytes
-  for (PinnedBlock& b : pool.block) {
-    if (b.leased) continue;
-    if (!best || (b.cap >= bytes ? best->cap < bytes || b.cap < best->cap : best->cap < bytes && b.cap > best->cap))
-      best = &b;
-  }
-  if (!best) return WD_OK;
-  if (best->cap < bytes) {
-    if (best->p) (void)hipHostFree(best->p);
-    best->p = nullptr;
-    best->cap = 0;
-    const uint64_t want = std::max<uint64_t>(bytes + bytes / 4, 1ull << 20);
-    if ((st = hip_check(hipHostMalloc((void**)&best->p, want, hipHostMallocDefault), "pinned memory"))) {
-      best->p = nullptr;
-      return st;
-    }
-    best->cap = want;
-  }
-  best->leased = true;
-  out->reset(new PinnedLease{&pool, best, best->p});
+  *out = &pools[dev];
   return WD_OK;
 }
 
@@ -515,15 +472,28 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
   }
   const bool packed = !debug && poff[B] > 0 && poff[B] <= (uint64_t)B * run->c.arcs * 16;
   // they land in a leased block of pinned memory (a DMA straight into it)
-  // and stay there; with no block free, in ordinary memory of each result's own
-  std::shared_ptr<PinnedLease> lease;
-  std::vector<char> plain;
-  const char* host = nullptr;
+  // and stay there; small ones, and those for which no block is free, are
+  // copied from the block that is not leased into memory of each result's own
+  std::shared_ptr<HipPinned::Lease> lease;
+  std::unique_lock<std::mutex> staging;
+  std::unique_ptr<char[]> plain;
+  char* dst = nullptr;
+  if (!debug && poff[B] > 0) {
+    HipPinned* pool = nullptr;
+    if ((st = pinned_of_current_device(&pool))) return st;
+    if (poff[B] > kPinnedSmall) lease = pool->lease(poff[B]);
+    if (lease) {
+      dst = lease->data();
+    } else if (packed) {
+      staging = std::unique_lock<std::mutex>(pool->stage_lock());
+      if (!(dst = pool->stage(poff[B]))) {
+        staging.unlock();
+        plain.reset(new char[poff[B]]);
+        dst = plain.get();
+      }
+    }
+  }
   if (packed) {
-    if ((st = lease_pinned(poff[B], &lease))) return st;
-    if (!lease) plain.resize(poff[B]);
-    char* dst = lease ? lease->p : plain.data();
-    host = dst;
     launch_pack_results(R.desc, B, run->lanes[0].cand, s);
     if ((st = hip_check(hipGetLastError(), "launch")) ||
         (st = hip_check(hipMemcpyAsync(dst, run->lanes[0].cand, poff[B], hipMemcpyDeviceToHost, s),
@@ -550,14 +520,15 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
     // links, nodes, words, one after another: where the packed results are, or
     // in memory of the result's own
     const uint64_t lbytes = sizeof(OutLink) * I.kept, nbytes = sizeof(OutNode) * I.out_nodes;
-    const char* at = nullptr;
-    if (packed && lease) {
+    const uint64_t bytes = lbytes + nbytes + 4 * I.nwords;
+    char* at = nullptr;
+    if (lease) {
       r->lease = lease;
-      at = host + poff[b];
+      at = dst + poff[b];
     } else {
-      r->own.resize(lbytes + nbytes + 4 * I.nwords);
-      if (packed) std::memcpy(r->own.data(), host + poff[b], r->own.size());
-      at = r->own.data();
+      r->own.reset(new char[bytes]);
+      at = r->own.get();
+      if (packed) std::memcpy(at, dst + poff[b], bytes);
     }
     r->links = (const wd_lat_arc*)at;
     r->nodes = (const wd_lat_node*)(at + lbytes);
@@ -576,8 +547,8 @@ static wd_status run_finish(wd_stream* run, wd_result** out) {
       r->tick_hz = 1e3 * khz;
     }
     if (packed) continue;
-    if ((st = d2h(r->own.data(), L.out_links, lbytes)) || (st = d2h(r->own.data() + lbytes, L.out_nodes, nbytes)) ||
-        (st = d2h(r->own.data() + lbytes + nbytes, L.out_words, 4 * I.nwords)))
+    if ((st = d2h(at, L.out_links, lbytes)) || (st = d2h(at + lbytes, L.out_nodes, nbytes)) ||
+        (st = d2h(at + lbytes + nbytes, L.out_words, 4 * I.nwords)))
       return st;
     if (debug) {
       const uint64_t nn = I.tokens;

@@ -196,6 +196,29 @@ def test_held_results(wf, oracle_mod, noisy):
         assert_same(r, oracle_mod.decode(g, x, 11.0, 2500, 6.0))
 
 
+def test_held_results_beyond_the_pool(wf, oracle_mod, noisy):
+    """Results of some size kept over more calls than there are pinned blocks
+    (leased blocks, then the one they are copied from), small ones among them,
+    then batches whose results share a block."""
+    import torch
+    g, graph = noisy
+    lbs = (2.0, 60.0, 60.0, 2.0, 60.0, 60.0, 60.0, 2.0)
+    Ls = [flat(6, 200, 70 + k) for k in range(len(lbs))]
+    xs = [torch.from_numpy(x).to(graph.device) for x in Ls]
+    print("\n[gpu case] held results", flush=True)
+    for _ in range(2):  # (the second time on the blocks of the first)
+        rs = [wf.decode(graph, x, 11.0, 2500, lb) for x, lb in zip(xs, lbs)]
+        sizes = [r.links.nbytes + r.nodes.nbytes + r.words.nbytes for r in rs]
+        assert min(sizes) < 64 << 10 < max(sizes) and sorted(sizes)[3] > 64 << 10, sizes
+        batches = [wf.decode_batch(graph, xs[k:k + 3], 11.0, 2500, 60.0) for k in range(5)]
+        for x, lb, r in zip(Ls, lbs, rs):
+            assert_same(r, oracle_mod.decode(g, x, 11.0, 2500, lb))
+        for k, b in enumerate(batches):
+            for x, r in zip(Ls[k:k + 3], b):
+                assert_same(r, oracle_mod.decode(g, x, 11.0, 2500, 60.0))
+
+
+
 @pytest.mark.parametrize("beam", [5.0, 9.0, 30.0])
 def test_small_frame_capacity(wf, oracle_mod, beam):
     """Frames in LDS are not held to the frame capacity, so their frontiers
