@@ -21,6 +21,13 @@
 // source lookup, its token, minimum), so a cluster of workgroups on one XCD
 // runs it (wd_cluster.h), each with the states of three frames in LDS: all of
 // them, or every 2^k-th when a frame has more than kSpWin.
+//
+// A generation's nodes are shared out whole, so the in-arcs of a state that many
+// arcs end in (the back-off states of a language model have 10^5 and more) would
+// fall to one workgroup, and may be far more than the arcs out of the frame's
+// tokens, which alone can be links.  Such hubs are left to a second step, all
+// workgroups together: over shares of their in-arcs, or, where these are more,
+// over the tokens' out-arcs into them.
 #include "wd_cluster.h"
 #include "wd_host.h"
 #include "wd_sparse.h"
@@ -34,6 +41,13 @@ constexpr uint64_t kSpGather = 300;            // helpers have 3 µs to come up,
 constexpr uint64_t kSpGatherWide = 10000;      // 100 µs where frames average more than
 constexpr uint64_t kSpWide = 30000;            // this many tokens
 constexpr uint32_t kSpHelpers = 28;            // (an XCD's CUs, but for a few)
+// A node is a hub from kSpHubMin in-arcs on where there are as many nodes as the
+// frame's tokens, and from kSpHubMax on in any case (two rounds of a workgroup; the
+// second step costs a barrier and a tile, about 5 µs).  Between the two the nodes'
+// in-arcs together stay within the tokens' out-arcs, taken as kSpOut per token
+// (with its own offsets to read).
+constexpr uint32_t kSpHubMin = 32, kSpHubMax = 2048, kSpOut = 3;
+constexpr uint32_t kSpHubs = 4096;             // hubs listed; more are left to the out-arcs
 
 struct SpShared {
   BlockScratch bs;
@@ -48,12 +62,17 @@ struct SpCounters {
   WD_GLOBAL uint32_t* e;    // [3] nodes of the frame before, pushed by a frame
   WD_GLOBAL uint32_t* any;  // a final state was reached
   WD_GLOBAL unsigned long long* best;  // inverted (final cost key, node offset) of the best end token
+  WD_GLOBAL uint32_t* h;    // [3] hubs among a generation's nodes
+  WD_GLOBAL unsigned long long* ha;  // [3] their in-arcs
+  WD_GLOBAL uint32_t* hubs;  // [kSpHubs] of this generation
 };
 __device__ __forceinline__ SpCounters sp_counters(const LaneDesc& L) {
   WD_GLOBAL uint32_t* h = &((Ctl*)L.ctl)->hist[0][0];
-  return SpCounters{h, h + 32, h + 64, (WD_GLOBAL unsigned long long*)(h + 96)};
+  return SpCounters{h, h + 32, h + 64, (WD_GLOBAL unsigned long long*)(h + 96),
+                    h + 128, (WD_GLOBAL unsigned long long*)(h + 160), h + 256};
 }
-constexpr uint32_t kSpCounterWords = 128;
+constexpr uint32_t kSpCounterWords = 192;
+static_assert(256 + kSpHubs <= kClDigits * kHistBins, "the hubs' list behind the counters");
 
 // Appends v to list[] for every lane with `on`: one add per wavefront.  Whole
 // wavefronts.  Entries beyond the capacity are dropped; the count tells.
@@ -159,6 +178,7 @@ __device__ __forceinline__ void sp_sweep(const DevGraph& g, const LaneDesc& L, S
   cl_barrier(C, N, gen);
 
   uint32_t gi = 0;
+  uint32_t n_e = cl_load(&cn.e[(T + 1) % 3]);  // nodes of the next frame to walk, pushed by this one
   for (int t = T; t >= 0; --t) {
     const uint32_t* const win0 = S.win[t % 3];
     const uint32_t* const win1 = S.win[(t + 2) % 3];  // frame t - 1
@@ -173,20 +193,35 @@ __device__ __forceinline__ void sp_sweep(const DevGraph& g, const LaneDesc& L, S
     const uint32_t cut = cost_key(L.cut[t]);
     const float* row = (const float*)L.ll + (size_t)(t > 0 ? t - 1 : 0) * g.P;
     if (w == 0 && tid == 0) cl_store(&cn.e[(t + 2) % 3], 0u);  // (frame t - 1's)
-    bool first = true;
-    while (true) {
-      // this generation's nodes: the frame's list, or what the last
-      // generation pushed (all live nodes of the frame, if that overflowed)
-      uint32_t n_list = first ? cl_load(&cn.e[(t + 1) % 3]) : cl_load(&cn.x[(gi + 2) % 3]);
-      if (!first && n_list == 0) break;
-      const WD_GLOBAL uint32_t* list = first ? we + (size_t)((t + 1) & 1) * cap : wx + (size_t)((gi + 1) & 1) * cap;
-      const bool all = n_list > cap;
-      if (all) n_list = f0.n;
-      if (w == 0 && tid == 0) cl_store(&cn.x[(gi + 1) % 3], 0u);
-      const uint32_t i0 = (uint32_t)((uint64_t)n_list * w / N), i1 = (uint32_t)((uint64_t)n_list * (w + 1) / N);
+    // A link out of node src, of cost x, into node `node` (cost key, predecessor
+    // arc and extra cost given): whether src is to be walked (again) in this
+    // frame (epsilon links), in the frame before.
+    auto relax = [&](bool eps, uint32_t src, float x, uint32_t arc_id, uint32_t node, uint32_t key, uint32_t arc,
+                     uint32_t ex, bool& push_x, bool& push_e) {
+      const uint32_t xk = cost_key(x);
+      if (xk > cut || xk >= kInfKey) return;
+      // the link that made the destination's token names its predecessor
+      if (xk == key && arc_id == arc) L.n_pred[node] = src;
+      const uint32_t le = cost_key(key_cost(ex) + (x - key_cost(key)));
+      if (le > lb_key) return;
+      const uint32_t old = __hip_atomic_fetch_min(&L.extra_key[src], le, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool fresh = old > lb_key;
+      if (fresh)
+        (void)__hip_atomic_fetch_or(&L.used[src >> 5], 1u << (src & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      push_x = eps && le < old;
+      push_e = !eps && fresh;
+    };
+    auto push = [&](bool push_x, bool push_e, uint32_t src) {
+      sp_push(push_x, src, wx + (size_t)(gi & 1) * cap, cap, &cn.x[gi % 3]);
+      sp_push(push_e, src, we + (size_t)(t & 1) * cap, cap, &cn.e[t % 3]);
+    };
+    // In-arcs of nodes i0 .. i1 of a list (`all`: of the frame): all of those
+    // with up to `lim`; or (`shared`) this workgroup's part of each node's.
+    auto walk = [&](const WD_GLOBAL uint32_t* list, bool all, uint32_t i0, uint32_t i1, uint32_t lim, bool shared) {
       for (uint32_t tb = i0; tb < i1; tb += kSpTok) {
         const uint32_t mm = i1 - tb < kSpTok ? i1 - tb : kSpTok;
         uint32_t deg = 0, beg = 0, key = 0, arc = 0, ex = kInfKey, v = 0;
+        bool hub = false;
         if (tid < mm) {
           v = all ? (uint32_t)(f0.n0 + tb + tid) : cl_load(&list[tb + tid]);
           const uint32_t s = L.n_state[v];
@@ -197,6 +232,20 @@ __device__ __forceinline__ void sp_sweep(const DevGraph& g, const LaneDesc& L, S
           arc = (uint32_t)pk;
           beg = r0;
           deg = ex <= lb_key ? r1 - r0 : 0u;
+          if (shared) {
+            const uint32_t d = deg;
+            beg += (uint32_t)((uint64_t)d * w / N);
+            deg = (uint32_t)((uint64_t)d * (w + 1) / N) - (uint32_t)((uint64_t)d * w / N);
+          } else {
+            hub = deg > lim;
+          }
+        }
+        if (!shared) {
+          if (hub) {
+            cl_add<unsigned long long>(&cn.ha[gi % 3], (unsigned long long)deg);
+            deg = 0;
+          }
+          sp_push(hub, v, cn.hubs, kSpHubs, &cn.h[gi % 3]);
         }
         uint32_t tot;
         S.pre[tid] = block_excl_scan(deg, S.bs, par, &tot);
@@ -220,33 +269,105 @@ __device__ __forceinline__ void sp_sweep(const DevGraph& g, const LaneDesc& L, S
               float x = key_cost((uint32_t)(L.n_pack[src] >> 32));
               if (!eps) x = x + -row[r.z - 1u];
               x = canon(x + __uint_as_float(r.y));
-              const uint32_t xk = cost_key(x);
-              if (xk <= cut && xk < kInfKey) {
-                // the link that made the destination's token names its predecessor
-                if (xk == S.key[j] && r.w == S.arc[j]) L.n_pred[S.node[j]] = src;
-                const uint32_t le = cost_key(key_cost(S.ex[j]) + (x - key_cost(S.key[j])));
-                if (le <= lb_key) {
-                  const uint32_t old = __hip_atomic_fetch_min(&L.extra_key[src], le, __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT);
-                  const bool fresh = old > lb_key;
-                  if (fresh)
-                    (void)__hip_atomic_fetch_or(&L.used[src >> 5], 1u << (src & 31u), __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-                  push_x = eps && le < old;
-                  push_e = !eps && fresh;
-                }
-              }
+              relax(eps, src, x, r.w, S.node[j], S.key[j], S.arc[j], S.ex[j], push_x, push_e);
             }
           }
-          sp_push(push_x, src, wx + (size_t)(gi & 1) * cap, cap, &cn.x[gi % 3]);
-          sp_push(push_e, src, we + (size_t)(t & 1) * cap, cap, &cn.e[t % 3]);
+          push(push_x, push_e, src);
         }
         __syncthreads();
       }
+    };
+    // The out-arcs of this workgroup's share of the source frame's tokens into
+    // live nodes of more than `lim` in-arcs.
+    auto from_tokens = [&](bool eps, uint32_t lim) {
+      const SpFrame& f = eps ? f0 : f1;
+      const uint32_t i1 = (uint32_t)((uint64_t)f.n * (w + 1) / N);
+      for (uint32_t tb = (uint32_t)((uint64_t)f.n * w / N); tb < i1; tb += kSpTok) {
+        const uint32_t mm = i1 - tb < kSpTok ? i1 - tb : kSpTok;
+        uint32_t deg = 0, beg = 0, key = 0;
+        const uint32_t v = (uint32_t)(f.n0 + tb + tid);
+        if (tid < mm) {
+          const uint32_t s = L.n_state[v];
+          const uint4 o0 = g.off[s], o1 = g.off[s + 1];
+          key = (uint32_t)(L.n_pack[v] >> 32);
+          beg = eps ? o0.y : o0.x;
+          deg = eps ? o1.y - o0.y : o1.x - o0.x;
+        }
+        uint32_t tot;
+        S.pre[tid] = block_excl_scan(deg, S.bs, par, &tot);
+        S.beg[tid] = beg;
+        S.key[tid] = key;
+        S.node[tid] = v;
+        __syncthreads();
+        for (uint64_t b = 0; b < tot; b += kThreads) {
+          const uint64_t it = b + tid;
+          bool push_x = false, push_e = false;
+          uint32_t src = ~0u;
+          if (it < tot) {
+            const uint32_t j = cl_find(S.pre, mm, (uint32_t)it);
+            const uint32_t a = S.beg[j] + ((uint32_t)it - S.pre[j]);
+            const uint4 r = eps ? g.xarc[a] : g.earc[a];  // {destination, weight, ilabel | level, arc}
+            const uint32_t dn = g.roff[r.x + 1] - g.roff[r.x] > lim ? sp_lookup<kSpWin>(L, f0, win0, r.x) : ~0u;
+            if (dn != ~0u) {
+              const uint32_t ex = cl_load(&L.extra_key[dn]);
+              if (ex <= lb_key) {
+                src = S.node[j];
+                float x = key_cost(S.key[j]);
+                if (!eps) x = x + -row[(r.z & 0xffffffu) - 1u];
+                x = canon(x + __uint_as_float(r.y));
+                const unsigned long long pk = L.n_pack[dn];
+                relax(eps, src, x, r.w, dn, (uint32_t)(pk >> 32), (uint32_t)pk, ex, push_x, push_e);
+              }
+            }
+          }
+          push(push_x, push_e, src);
+        }
+        __syncthreads();
+      }
+    };
+    bool first = true;
+    uint32_t n_list = n_e;
+    while (true) {
+      // this generation's nodes: the frame's list, or what the last
+      // generation pushed (all live nodes of the frame, if that overflowed)
+      const WD_GLOBAL uint32_t* list = first ? we + (size_t)((t + 1) & 1) * cap : wx + (size_t)((gi + 1) & 1) * cap;
+      const bool all = n_list > cap;
+      if (all) n_list = f0.n;
+      if (w == 0 && tid == 0) {
+        cl_store(&cn.x[(gi + 1) % 3], 0u);
+        cl_store(&cn.h[(gi + 1) % 3], 0u);
+        cl_store<unsigned long long>(&cn.ha[(gi + 1) % 3], 0ull);
+      }
+      const uint64_t out = (uint64_t)kSpOut * ((uint64_t)f0.n + f1.n);
+      uint32_t lim = kSpHubMax;
+      if (out / kSpHubMax < n_list) {
+        lim = (uint32_t)((float)out / (float)n_list);
+        lim = lim > kSpHubMin ? lim : kSpHubMin;
+      }
+      walk(list, all, (uint32_t)((uint64_t)n_list * w / N), (uint32_t)((uint64_t)n_list * (w + 1) / N), lim, false);
       cl_barrier(C, N, gen);
-      if (cl_load(&C->bad)) return;
+      // (every word the next steps depend on in one round of loads)
+      const uint32_t n_hub = cl_load(&cn.h[gi % 3]);
+      uint32_t bad = cl_load(&C->bad), n_x = cl_load(&cn.x[gi % 3]);
+      n_e = cl_load(&cn.e[t % 3]);
+      if (bad) return;
+      if (n_hub) {
+        if (n_hub <= kSpHubs && cl_load(&cn.ha[gi % 3]) <= out) {
+          walk(cn.hubs, false, 0, n_hub, 0, true);
+        } else {
+          if (t > 0) from_tokens(false, lim);
+          from_tokens(true, lim);
+        }
+        cl_barrier(C, N, gen);
+        bad = cl_load(&C->bad);
+        n_x = cl_load(&cn.x[gi % 3]);
+        n_e = cl_load(&cn.e[t % 3]);
+        if (bad) return;
+      }
       first = false;
       ++gi;
+      if (n_x == 0) break;
+      n_list = n_x;
     }
     // frame t - 2 takes the place of frame t + 1 (whose window nobody reads
     // any more)

@@ -259,3 +259,61 @@ def test_stopped_decode_stats(wf, noisy, caps):
         wf.wd_result_free(r)
         seen.append((out.stats, out.needed))
     assert seen[0][0]["raw_links"] == 0 and all(s == seen[0] for s in seen[1:]), seen
+
+
+def hub_graph(S, A, P, hubs, seed):
+    """Random arcs; for each (in-degree, share of epsilon arcs) of `hubs` that
+    many states' last arcs end in one state (1, 2, ...) instead."""
+    rng = np.random.default_rng(seed)
+    deg = np.full(S, A // S)
+    deg[0] = 64
+    row = np.zeros(S + 1, np.int64)
+    np.cumsum(deg, out=row[1:])
+    n = int(row[-1])
+    dst = rng.integers(len(hubs) + 1, S, n)
+    il = rng.integers(1, P + 1, n)
+    w = rng.exponential(3.0, n).astype(np.float32)
+    at = rng.permutation(np.arange(len(hubs) + 1, S))
+    for k, (din, eps) in enumerate(hubs):
+        a, at = row[at[:din] + 1] - 1, at[din:]
+        dst[a] = 1 + k
+        il[a[rng.random(a.size) < eps]] = 0
+    return synth._pack(dict(row_ptr=row, dst=dst, ilabel=il, olabel=rng.integers(0, 9, n), weight=w), S)
+
+
+# in-degrees below and above the tokens' out-arcs (the second step's two ways),
+# around its smallest (2048 and one more), none; by emitting, by epsilon arcs, by both
+@pytest.mark.parametrize("mode", ["workgroup", "chip"])
+@pytest.mark.parametrize("hubs,ma", [([(20_000, 0.0)], 2000), ([(20_000, 1.0)], 2000), ([(4000, 0.0), (5000, 1.0)], 3000),
+                                     ([(2048, 0.5), (2049, 0.5), (9000, 0.5)], 1500), ([(12_000, 0.5)], 0)])
+def test_hubs(wf, oracle_mod, hubs, ma, mode):
+    """States that a large share of the graph's arcs end in."""
+    g = hub_graph(30_000, 90_000, 60, hubs, 80)
+    graph = wf.Graph(g, 60)
+    for lb in (6.0, 40.0):
+        check(wf, oracle_mod, g, graph, flat(8, 60, 81), (16.0, ma, lb), mode)
+
+
+def test_many_hubs(wf, oracle_mod):
+    """Every live node above the smallest in-degree of a hub, more of them than
+    are listed."""
+    g = hub_graph(6000, 360_000, 40, [], 82)
+    graph = wf.Graph(g, 40)
+    for mode in ("workgroup", "chip"):
+        check(wf, oracle_mod, g, graph, flat(5, 40, 83), (30.0, 0, 60.0), mode)
+
+
+@pytest.mark.parametrize("eps", [0.0, 1.0])
+def test_hub_time(wf, eps):
+    """The pruning of a graph with a state of 400 thousand in-arcs stays within a
+    few times that of the raw links (measured 13 times with the in-arcs walked by
+    the node)."""
+    import torch
+    graph = wf.Graph(hub_graph(500_000, 2_000_000, 300, [(400_000, eps)], 84), 300)
+    x = torch.from_numpy(flat(30, 300, 85)).to(graph.device)
+    print(f"\n[gpu case] hub of 400k in-arcs, eps {eps}", flush=True)
+    ms = {}
+    for fl in (0, wf.WD_FLAG_NO_INCREMENTAL_PRUNE):
+        ms[fl] = min(wf.decode(graph, x, 12.0, 0, 8.0, timing=True, mode="chip", flags=fl).stats["lattice_ms"]
+                     for _ in range(4))
+    assert ms[0] < 4 * ms[wf.WD_FLAG_NO_INCREMENTAL_PRUNE] + 0.5, ms
