@@ -139,6 +139,7 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   char* link_off = take(8 * T2);
   char* link_xoff = take(8 * T2);
   char* link_end = take(8 * T2);
+  char* slice = c.chip ? take(sizeof(uint2) * kSlices * T2) : nullptr;
   char* xmask = take(4 * T2);
   char* best = take(4 * T2);
   char* cutb = take(4 * T2);
@@ -195,6 +196,7 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
       L.link_off = (decltype(L.link_off))at(link_off, 8 * T2);
       L.link_xoff = (decltype(L.link_xoff))at(link_xoff, 8 * T2);
       L.link_end = (decltype(L.link_end))at(link_end, 8 * T2);
+      L.slice = c.chip ? (decltype(L.slice))at(slice, sizeof(uint2) * kSlices * T2) : nullptr;
       L.xmask = (decltype(L.xmask))at(xmask, 4 * T2);
       L.best = (decltype(L.best))at(best, 4 * T2);
       L.cutb = (decltype(L.cutb))at(cutb, 4 * T2);

@@ -26,6 +26,7 @@ constexpr int kHashMax = 2048;              // LDS token table entries before a 
 constexpr int kFrontCap = 1024;             // frontier tokens held in LDS
 constexpr int kHistBins = 2048;             // 11-bit radix digits for max-active
 constexpr uint32_t kInfKey = 0xff800000u;   // key of +inf
+constexpr uint32_t kSlices = 32;            // parts of a wide frame whose links are formed apart
 constexpr uint32_t kPathMaxLen = 16;        // epsilon paths longer than this: no path table
 constexpr uint64_t kPathMax = 1ull << 27;   // more epsilon paths than this: no path table
 constexpr int kProfStamps = 10;             // step boundaries stamped per frame (WD_FLAG_PHASES)
@@ -241,6 +242,7 @@ struct LaneDesc {
   WD_GLOBAL uint64_t* link_off;          // [T+2] first link of frame t (emitting run)
   WD_GLOBAL uint64_t* link_xoff;         // [T+2] first epsilon link of frame t
   WD_GLOBAL uint64_t* link_end;          // [T+2] one past the last link of frame t
+  WD_GLOBAL uint2* slice;                // [(T+2) * kSlices] chip-wide: emitting, epsilon links of a frame's slices
   WD_GLOBAL uint32_t* xmask;             // [T+2] levels of the epsilon links of frame t (bit 31: 31 or more)
   WD_GLOBAL float* best;                 // [T+1]
   WD_GLOBAL float* cutb;                 // [T+1]

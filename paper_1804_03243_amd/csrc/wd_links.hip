@@ -25,6 +25,7 @@ namespace wd {
 constexpr int kLT = 256;              // threads per workgroup
 constexpr int kLWv = kLT / 64;        // wavefronts
 constexpr uint32_t kLinkBlocks = 256;  // workgroups per utterance (frames in turn)
+constexpr uint32_t kSliceBlocks = 1024;  // chip-wide: workgroups per utterance (slices in turn)
 constexpr uint32_t kSpBWin = 2048;     // sparse utterances: states of one frame held in LDS
 constexpr uint32_t kSpList = 2048;     // live nodes listed together
 
@@ -163,14 +164,34 @@ struct SpLinkShared {
   uint32_t cls[kLT];
 };
 
+// Slices of an utterance's frames: a frame's links are formed by this many
+// workgroups, each out of an equal part of the source frame's nodes.  With one
+// workgroup a frame, the last frames of a wide decode (every token of the very
+// last one within the beam ends a path) took as long as all the others: of 60
+// frames of up to 650 thousand tokens, 604 thousand links kept, 9.8 ms each
+// for count and write.  A slice costs some 10 µs however few live nodes it has,
+// so frames of the one-workgroup mode are one slice.
+constexpr uint32_t kSliceNodes = 8192;
+__device__ __forceinline__ uint32_t slices_of(const LaneDesc& L, uint32_t flags) {
+  if (!(flags & kFlagSwept)) return 1u;
+  const uint64_t n = L.info->max_tokens / kSliceNodes;
+  return n < 1 ? 1u : n < kSlices ? (uint32_t)n : kSlices;
+}
+
 // The kept emitting links into frame t out of frame t - 1's live nodes (kEps
-// false), or the kept epsilon links of frame t: counted, or written from link
-// `at` on, in the order of their sources' states and arcs.
+// false), or the kept epsilon links of frame t, those of slice k of ns: counted,
+// or written from link `at` on, in the order of their sources' states and arcs.
 template <bool kEps, bool kWrite>
 __device__ __forceinline__ uint32_t sp_run(const DevGraph& g, const LaneDesc& L, SpLinkShared& sh, uint32_t& par, int t,
-                                           const SpFrame& df, uint32_t lb_key, uint64_t at, uint32_t* xmask) {
+                                           uint32_t k, uint32_t ns, const SpFrame& df, uint32_t lb_key, uint64_t at,
+                                           uint32_t* xmask) {
   const uint32_t tid = threadIdx.x;
-  const uint64_t p0 = L.node_off[kEps ? t : t - 1], p1 = L.node_off[kEps ? t + 1 : t];
+  uint64_t p0 = L.node_off[kEps ? t : t - 1], p1 = L.node_off[kEps ? t + 1 : t];
+  if (ns > 1) {  // (cut at words of the live nodes' bitmap)
+    const uint64_t w0 = p0 >> 5, n = ((p1 + 31) >> 5) - w0, a = 32 * (w0 + n * k / ns), b = 32 * (w0 + n * (k + 1) / ns);
+    if (a > p0) p0 = a;
+    if (b < p1) p1 = b;
+  }
   const float* row = (const float*)L.ll + (size_t)(t > 0 ? t - 1 : 0) * g.P;
   const uint32_t cut = cost_key(L.cut[t]);
   uint32_t n = 0;
@@ -287,8 +308,10 @@ __global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc*
   if (!links_wanted(L)) return;
   uint32_t par = 0;
   if (sparse_lane(L, prm.flags)) {
-    const uint32_t lb_key = cost_key(prm.lattice_beam);
-    for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
+    const uint32_t lb_key = cost_key(prm.lattice_beam), ns = slices_of(L, prm.flags);
+    for (uint32_t u = blockIdx.x; u < ((uint32_t)L.T + 1u) * ns; u += gridDim.x) {
+      const int t = (int)(u / ns);
+      const uint32_t k = u % ns;
       uint64_t raw = 0;
       if (!(prm.flags & kFlagSwept) && L.xmask[t] == 0) {
         // a frame whose raw links the forward pass has not counted
@@ -298,12 +321,16 @@ __global__ void __launch_bounds__(kLT) k_links_count(DevGraph g, const LaneDesc*
         __syncthreads();
       }
       const SpFrame f = sp_dest(L, lds.sparse, t);
-      const uint32_t ne = t > 0 ? sp_run<false, false>(g, L, lds.sparse, par, t, f, lb_key, 0, nullptr) : 0u;
-      const uint32_t nx = sp_run<true, false>(g, L, lds.sparse, par, t, f, lb_key, 0, nullptr);
+      const uint32_t ne = t > 0 ? sp_run<false, false>(g, L, lds.sparse, par, t, k, ns, f, lb_key, 0, nullptr) : 0u;
+      const uint32_t nx = sp_run<true, false>(g, L, lds.sparse, par, t, k, ns, f, lb_key, 0, nullptr);
       __syncthreads();
       if (threadIdx.x == 0) {
-        L.link_xoff[t] = ne;
-        L.link_end[t] = nx;
+        if (ns > 1) {
+          L.slice[(size_t)t * kSlices + k] = make_uint2(ne, nx);
+        } else {
+          L.link_xoff[t] = ne;
+          L.link_end[t] = nx;
+        }
         if (raw) atomicAdd((unsigned long long*)&L.info->links, (unsigned long long)raw);
       }
     }
@@ -351,6 +378,21 @@ __global__ void __launch_bounds__(kLT) k_links_offsets(const LaneDesc* __restric
   const uint32_t f0 = threadIdx.x * per < T1 ? threadIdx.x * per : T1;
   const uint32_t f1 = f0 + per < T1 ? f0 + per : T1;
   uint64_t sum = 0;
+  const uint32_t ns = sparse_lane(L, prm.flags) ? slices_of(L, prm.flags) : 1u;
+  if (ns > 1)
+    // (a slice's counts become what lies before it in its frame's two runs)
+    for (uint32_t t = f0; t < f1; ++t) {
+      uint2 n = make_uint2(0, 0);
+      for (uint32_t k = 0; k < ns; ++k) {
+        const uint2 c = L.slice[(size_t)t * kSlices + k];
+        L.slice[(size_t)t * kSlices + k] = n;
+        n.x += c.x;
+        n.y += c.y;
+      }
+      L.link_xoff[t] = n.x;
+      L.link_end[t] = n.y;
+      L.xmask[t] = 0;
+    }
   for (uint32_t t = f0; t < f1; ++t) sum += L.link_xoff[t] + L.link_end[t];
   uint32_t par = 0;
   uint64_t total;
@@ -383,14 +425,20 @@ __global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc*
   if (!links_wanted(L)) return;
   uint32_t par = 0, bad = 0;
   if (sparse_lane(L, prm.flags)) {
-    const uint32_t lb_key = cost_key(prm.lattice_beam);
-    for (int t = (int)blockIdx.x; t <= L.T; t += (int)gridDim.x) {
+    const uint32_t lb_key = cost_key(prm.lattice_beam), ns = slices_of(L, prm.flags);
+    for (uint32_t u = blockIdx.x; u < ((uint32_t)L.T + 1u) * ns; u += gridDim.x) {
+      const int t = (int)(u / ns);
+      const uint32_t k = u % ns;
       const SpFrame f = sp_dest(L, lds.sparse, t);
+      const uint2 before = ns > 1 ? (uint2)L.slice[(size_t)t * kSlices + k] : make_uint2(0, 0);
       uint32_t xmask = 0;
-      if (t > 0) (void)sp_run<false, true>(g, L, lds.sparse, par, t, f, lb_key, L.link_off[t], &xmask);
-      (void)sp_run<true, true>(g, L, lds.sparse, par, t, f, lb_key, L.link_xoff[t], &xmask);
+      if (t > 0) (void)sp_run<false, true>(g, L, lds.sparse, par, t, k, ns, f, lb_key, L.link_off[t] + before.x, &xmask);
+      (void)sp_run<true, true>(g, L, lds.sparse, par, t, k, ns, f, lb_key, L.link_xoff[t] + before.y, &xmask);
       const uint32_t all = block_or<kLWv>(xmask, lds.sparse.bs, par);
-      if (threadIdx.x == 0) L.xmask[t] = all;
+      if (threadIdx.x == 0) {
+        if (ns == 1) L.xmask[t] = all;
+        else if (all) (void)atomicOr((uint32_t*)&L.xmask[t], all);
+      }
     }
     return;
   }
@@ -429,9 +477,10 @@ __global__ void __launch_bounds__(kLT) k_links_write(DevGraph g, const LaneDesc*
 }
 
 void launch_links(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm, hipStream_t s) {
-  hipLaunchKernelGGL(k_links_count, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes, prm);
+  const uint32_t blocks = prm.flags & kFlagSwept ? kSliceBlocks : kLinkBlocks;
+  hipLaunchKernelGGL(k_links_count, dim3(blocks, B), dim3(kLT), 0, s, g, lanes, prm);
   hipLaunchKernelGGL(k_links_offsets, dim3(B), dim3(kLT), 0, s, lanes, prm);
-  hipLaunchKernelGGL(k_links_write, dim3(kLinkBlocks, B), dim3(kLT), 0, s, g, lanes, prm);
+  hipLaunchKernelGGL(k_links_write, dim3(blocks, B), dim3(kLT), 0, s, g, lanes, prm);
 }
 
 }  // namespace wd

@@ -317,3 +317,28 @@ def test_hub_time(wf, eps):
         ms[fl] = min(wf.decode(graph, x, 12.0, 0, 8.0, timing=True, mode="chip", flags=fl).stats["lattice_ms"]
                      for _ in range(4))
     assert ms[0] < 4 * ms[wf.WD_FLAG_NO_INCREMENTAL_PRUNE] + 0.5, ms
+
+
+@pytest.mark.parametrize("lb", [8.0, 16.0, float("inf")])
+def test_wide_lattice_beam_chip(wf, oracle_mod, noisy, lb):
+    """Frames whose links are formed in several slices, from a few live nodes
+    to all of them."""
+    g, graph = noisy
+    for T in (3, 11):
+        r = check(wf, oracle_mod, g, graph, flat(T, 200, 90), (18.0, 0, lb), "chip")
+    assert r.stats["max_tokens"] > 5 * 8192
+
+
+def test_wide_lattice_time(wf):
+    """Where the lattice beam keeps most of a wide decode's last frames, pruning
+    from live nodes stays near the raw links' time (measured 2.5 to 3.6 times
+    with a frame's links formed by one workgroup)."""
+    import torch
+    graph = wf.Graph(graph_of(1_000_000, 3_000_000, 300, 0.3, 6, 91), 300)
+    x = torch.from_numpy(flat(20, 300, 92)).to(graph.device)
+    print("\n[gpu case] wide lattice beam", flush=True)
+    ms = {}
+    for fl in (0, wf.WD_FLAG_NO_INCREMENTAL_PRUNE):
+        ms[fl] = min(wf.decode(graph, x, 20.0, 0, 16.0, timing=True, mode="chip", flags=fl).stats["lattice_ms"]
+                     for _ in range(4))
+    assert ms[0] < 2.4 * ms[wf.WD_FLAG_NO_INCREMENTAL_PRUNE], ms
