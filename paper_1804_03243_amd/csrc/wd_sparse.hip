@@ -389,7 +389,13 @@ __global__ void __launch_bounds__(kThreads) k_sp_sweep(DevGraph g, const LaneDes
   uint32_t lane_no = blockIdx.x;
   if (!lead && !helper_lane(B, &lane_no)) return;
   const LaneDesc& L = lanes[lane_no];
-  if (!sparse_lane(L, prm.flags)) return;
+  // (one thread looks for all: a helper may come up as late as the leader's last
+  // store, which can be to the status)
+  if (threadIdx.x == 0) S.go = sparse_lane(L, prm.flags) ? 1u : 0u;
+  __syncthreads();
+  const bool wanted = S.go != 0;
+  __syncthreads();
+  if (!wanted) return;
   Ctl* const C = (Ctl*)((WD_GLOBAL char*)L.ctl + sizeof(ClusterCtl));  // (its header only)
   uint32_t w = 0, N = 1;
   if (lead) {
