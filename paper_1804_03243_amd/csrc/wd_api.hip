@@ -371,15 +371,16 @@ static wd_status run_frames(wd_stream* run, bool update) {
   if (update) launch_set_frames(R.desc, B, run->T.data(), run->next.data(), run->open ? 1 : 0, s);
   launch_check_loglikes(R.desc, B, run->g->P, R.bad, s);
   wd_status st = WD_OK;
+  int lo = run->max_T + 1, hi = -1, most = 0;
+  for (int b = 0; b < B; ++b) {
+    lo = std::min(lo, run->next[b]);
+    hi = std::max(hi, run->T[b]);
+    most = std::max(most, run->T[b] + 1 - run->next[b]);
+  }
   if (run->chip) {
-    int lo = run->max_T + 1, hi = -1;
-    for (int b = 0; b < B; ++b) {
-      lo = std::min(lo, run->next[b]);
-      hi = std::max(hi, run->T[b]);
-    }
     grid_frames(run->g->dg, R.desc, R.grid, B, run->prm, R.bad, lo, hi, s);
   } else {
-    launch_forward(run->g->dg, R.desc, B, run->prm, R.bad, s);
+    launch_forward(run->g->dg, R.desc, B, most, run->prm, R.bad, s);
   }
   for (int b = 0; b < B; ++b) run->next[b] = run->T[b] + 1;
   if (st == WD_OK) st = hip_check(hipGetLastError(), "launch");
@@ -734,7 +735,7 @@ extern "C" wd_status wd_decode_noalloc(const wd_graph* g, const float* loglikes,
   launch_setup(R.desc, 1, R.bad, R.used_words, (uint64_t)g->S, R.bitmap_words, false, s);
   const Params prm{p->beam, p->max_active, p->lattice_beam, p->flags};
   launch_check_loglikes(R.desc, 1, g->P, R.bad, s);
-  launch_forward(g->dg, R.desc, 1, prm, R.bad, s);
+  launch_forward(g->dg, R.desc, 1, T + 1, prm, R.bad, s);
   launch_sweep(g->dg, R.desc, 1, prm, s);
   launch_links(g->dg, R.desc, 1, prm, s);
   launch_lattice(g->dg, R.desc, 1, prm, s);

@@ -18,7 +18,8 @@
 // microseconds, and the barriers count the registered ones only.  A helper
 // that is idle for kIdleTicks (and a quarter of the time it has worked) leaves,
 // so the CUs of utterances that never have a large frame are free for other
-// work soon after the launch.
+// work soon after the launch; in a launch that resumes parked utterances, which
+// have such frames, it stays for kIdleResumed.
 //
 // Per frame t, with the tokens of frame t - 1 as bits of a state bitmap (and
 // their packed tokens in the slot array of that frame's parity):
@@ -48,6 +49,8 @@ constexpr uint32_t kClMax = 32;            // workgroups of a cluster (an XCD ha
 constexpr uint32_t kCoarse = 2048;         // state ranges counted for the shares of phase A
 constexpr uint32_t kClDigits = 3;          // radix digits of a 32-bit key (11, 11, 10)
 constexpr uint64_t kIdleTicks = 30000;     // 300 µs of the 100 MHz clock
+// helpers of utterances known to have large frames: 2 ms, some 250 small frames
+constexpr uint64_t kIdleResumed = 200000;
 constexpr uint64_t kJoinTicks = 400;       // a run waits for its helpers this long at most (4 µs)
 constexpr uint32_t kRegroupFrames = 4;     // frames after which a run takes in late helpers
 // back to the LDS path once a frame is this small

@@ -152,6 +152,8 @@ struct LaneInfo {
   uint32_t tb_fail;            // traceback met an inconsistent predecessor
   uint32_t last_tokens;        // surviving tokens of the last decoded frame
   uint32_t slots_clean;        // one-workgroup mode: the slot arrays and the bitmap have been emptied
+  uint32_t parked;             // the first launch ended at a large frame (frames_done), for the second to go on with
+  uint32_t pad0;
   double Z;                    // total cost of the kept lattice (-log of its path sum)
 };
 

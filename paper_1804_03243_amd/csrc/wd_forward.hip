@@ -16,7 +16,8 @@
 // the survivor scan are LDS operations.  A frame that touches more states than
 // the table holds starts again from the same frontier as a large frame, which
 // the workgroup runs together with the launch's helper workgroups on its XCD
-// (wd_cluster.h); its inputs are unchanged, so the result is identical.  The
+// (wd_cluster.h; in a launch that has none the utterance is parked for the next
+// one); its inputs are unchanged, so the result is identical.  The
 // frontier itself is kept in LDS when it fits.
 #include "../../include/wfstdec.h"
 #include "wd_cluster.h"
@@ -246,16 +247,29 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 
 // kProf: the step-profile copy (WD_FLAG_PHASES), which stores the device
 // wall clock at each step boundary of every frame (thread 0).
-// Workgroups 0 .. B-1 lead an utterance each; the others help (one that finds
-// its lane's leader on another XCD leaves at once).
-template <bool kProf>
+// kCluster: workgroups 0 .. B-1 lead an utterance each; the others help (one
+// that finds its lane's leader on another XCD leaves at once).  Without it there
+// are leaders only, and an utterance that comes to a large frame is parked there:
+// its state is left as an open stream's, for a launch with kCluster and `resume`,
+// which goes on with the parked utterances only.
+template <bool kProf, bool kCluster>
 __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, const LaneDesc* __restrict__ lanes,
-                                             const Params& prm, const uint32_t* __restrict__ bad, uint32_t B) {
+                                             const Params& prm, const uint32_t* __restrict__ bad, uint32_t B,
+                                             bool resume) {
   const uint32_t tid = threadIdx.x;
-  const bool lead = blockIdx.x < B;
+  const bool lead = !kCluster || blockIdx.x < B;
   uint32_t lane_no = blockIdx.x;
   if (!lead && !helper_lane(B, &lane_no)) return;
   const LaneDesc& L = lanes[lane_no];
+  if (resume) {
+    // (one thread looks for all: the leader clears the word at its end, and a
+    // helper may come up that late)
+    if (tid == 0) sh.spill = L.info->parked;
+    __syncthreads();
+    const bool parked = sh.spill != 0;
+    __syncthreads();
+    if (!parked) return;
+  }
   Ctl* const C = (Ctl*)L.ctl;
   ClusterShared& cs = *reinterpret_cast<ClusterShared*>(sh.hist);
   static_assert(sizeof(ClusterShared) + offsetof(FwdShared, hist) <= sizeof(FwdShared), "a large frame's LDS");
@@ -264,11 +278,11 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   if (bad[lane_no]) {
     if (lead && tid == 0) {
       L.info->status = 1;  // WD_EINVAL
-      cl_store(&C->quit, 1u);
+      if (kCluster) cl_store(&C->quit, 1u);
     }
     return;
   }
-  if (lead && tid == 0) cl_store(&C->xcc, cl_xcc() + 1u);
+  if (kCluster && lead && tid == 0) cl_store(&C->xcc, cl_xcc() + 1u);
   const int T = L.T;
   const uint32_t P = g.P;
 
@@ -294,7 +308,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   bool clean = false;     // the slot arrays and the bitmap are empty (large frames)
   uint32_t runs = 0;      // runs of large frames opened (leader), seen (helper)
   uint32_t id = kClMax;   // helper: its number among the lane's helpers
-  bool again = false;     // the next frame is a large one (its run was only interrupted)
+  bool again = resume;    // the next frame is a large one (its run was only interrupted)
   uint64_t busy = 0;      // helper: time spent in runs
   if (tid == 0) {
     sh.c_arcs = 0;
@@ -308,7 +322,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   uint32_t warm_bad = 0;  // a warming load returned the sentinel payload (never)
   float warm_prev = 0.0f;  // the previous frame's warming values (read a frame late)
   uint32_t par = 0;     // scratch buffer parity of the workgroup collectives
-  int t = L.t0;
+  int t = resume ? L.info->frames_done : L.t0;
   // step profile: slot k < kProfStamps of frame t gets the wall clock when
   // thread 0 passes step boundary k; the last two slots describe the frame
   auto stamp = [&](int k) {
@@ -333,7 +347,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     const bool go_on = I.status == 4 && (I.overflow & (kOvfFrame | kOvfArcs)) == 0;
     status = __builtin_amdgcn_readfirstlane(go_on ? 0 : I.status);
     if (status != 0) {
-      if (lead && tid == 0) cl_store(&C->quit, 1u);
+      if (kCluster && tid == 0) cl_store(&C->quit, 1u);
       return;
     }
     ovf = __builtin_amdgcn_readfirstlane(I.overflow);
@@ -363,6 +377,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
       L.f_ebeg[i] = sh.f_ebeg[i];
     }
   };
+  bool parked = false;
   while (true) {  // frames in LDS, then a run of large ones
     uint32_t w = 0, N = 1;
     if (lead) {
@@ -978,47 +993,53 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
         stamp(9);
       }
       if (!large) break;
+      if (!kCluster) {
+        parked = true;
+        break;
+      }
       if (front_lds) front_out();
       w = 0;
       N = cl_open(C, cs.go, t, n_prev, node_base, hist_ok, !clean, ++runs);
     } else {
-      const uint32_t go = cl_wait(C, cs.go, runs, id, kIdleTicks + busy / 4);
+      const uint32_t go = cl_wait(C, cs.go, runs, id, (resume ? kIdleResumed : kIdleTicks) + busy / 4);
       if (go == 0) return;
       w = go >> 8;
       N = go & 0xffu;
     }
-    const uint64_t t0 = wall_clock64();
-    cl_run(g, L, prm, cs, C, w, N, paths);
-    busy += wall_clock64() - t0;
-    if (!lead) continue;
-    // the run's outcome; the LDS tables start afresh
-    const ClusterState& o = cs.out;
-    t = __builtin_amdgcn_readfirstlane(o.t);
-    status = __builtin_amdgcn_readfirstlane(o.status);
-    ovf |= __builtin_amdgcn_readfirstlane(o.ovf);
-    n_prev = __builtin_amdgcn_readfirstlane(o.n_prev);
-    W = __builtin_amdgcn_readfirstlane(o.W);
-    hist_ok = __builtin_amdgcn_readfirstlane(o.hist_ok) != 0;
-    node_base = uniform64(o.node_base);
-    again = __builtin_amdgcn_readfirstlane(o.again) != 0;
-    front_lds = false;
-    front_own = false;
-    clean = true;
-    if (tid == 0) {
-      my_eps += o.eps;
-      sh.c_arcs += o.arcs;
-      sh.c_links += o.links;
-      sh.c_tokens += o.tokens;
-      if (o.max_tokens > sh.c_max_tokens) sh.c_max_tokens = o.max_tokens;
-      if (o.need_frame > sh.c_need_frame) sh.c_need_frame = o.need_frame;
-      if (o.need_arcs > sh.c_need_arcs) sh.c_need_arcs = o.need_arcs;
+    if constexpr (kCluster) {
+      const uint64_t t0 = wall_clock64();
+      cl_run(g, L, prm, cs, C, w, N, paths);
+      busy += wall_clock64() - t0;
+      if (!lead) continue;
+      // the run's outcome; the LDS tables start afresh
+      const ClusterState& o = cs.out;
+      t = __builtin_amdgcn_readfirstlane(o.t);
+      status = __builtin_amdgcn_readfirstlane(o.status);
+      ovf |= __builtin_amdgcn_readfirstlane(o.ovf);
+      n_prev = __builtin_amdgcn_readfirstlane(o.n_prev);
+      W = __builtin_amdgcn_readfirstlane(o.W);
+      hist_ok = __builtin_amdgcn_readfirstlane(o.hist_ok) != 0;
+      node_base = uniform64(o.node_base);
+      again = __builtin_amdgcn_readfirstlane(o.again) != 0;
+      front_lds = false;
+      front_own = false;
+      clean = true;
+      if (tid == 0) {
+        my_eps += o.eps;
+        sh.c_arcs += o.arcs;
+        sh.c_links += o.links;
+        sh.c_tokens += o.tokens;
+        if (o.max_tokens > sh.c_max_tokens) sh.c_max_tokens = o.max_tokens;
+        if (o.need_frame > sh.c_need_frame) sh.c_need_frame = o.need_frame;
+        if (o.need_arcs > sh.c_need_arcs) sh.c_need_arcs = o.need_arcs;
+      }
+      __syncthreads();
+      empty_tables();
+      if (status != 0) break;
     }
-    __syncthreads();
-    empty_tables();
-    if (status != 0) break;
   }
 
-  if (L.open && front_lds) front_out();  // an open stream resumes from the workspace frontier
+  if ((L.open || parked) && front_lds) front_out();  // the next launch resumes from the workspace frontier
   warm_bad |= __float_as_uint(warm_prev) == 0x7fc00001u ? 1u : 0u;
   const uint32_t wb = block_or(warm_bad, sh.bs, par);
   const uint64_t eps = block_sum64(my_eps, sh.bs, par);
@@ -1042,22 +1063,22 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     info->need_frame_arcs = sh.c_need_arcs;
     info->last_tokens = n_prev;
     info->slots_clean = clean ? 1u : 0u;
-    cl_store(&C->quit, 1u);
+    info->parked = parked ? 1u : 0u;
+    if (kCluster) cl_store(&C->quit, 1u);
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_forward(DevGraph g, const LaneDesc* __restrict__ lanes,
-                                                      Params prm, const uint32_t* __restrict__ bad, uint32_t B) {
-  __shared__ FwdShared sh;
-  forward_body<false>(sh, g, lanes, prm, bad, B);
-}
-
-__global__ void __launch_bounds__(kThreads) k_forward_phases(DevGraph g, const LaneDesc* __restrict__ lanes,
-                                                             Params prm, const uint32_t* __restrict__ bad,
-                                                             uint32_t B) {
-  __shared__ FwdShared sh;
-  forward_body<true>(sh, g, lanes, prm, bad, B);
-}
+#define WD_FORWARD(NAME, PROF, CLUSTER)                                                                        \
+  __global__ void __launch_bounds__(kThreads) NAME(DevGraph g, const LaneDesc* __restrict__ lanes, Params prm, \
+                                                   const uint32_t* __restrict__ bad, uint32_t B, bool resume) { \
+    __shared__ FwdShared sh;                                                                                   \
+    forward_body<PROF, CLUSTER>(sh, g, lanes, prm, bad, B, CLUSTER && resume);                                 \
+  }
+WD_FORWARD(k_forward, false, false)
+WD_FORWARD(k_forward_phases, true, false)
+WD_FORWARD(k_forward_cluster, false, true)
+WD_FORWARD(k_forward_cluster_phases, true, true)
+#undef WD_FORWARD
 
 int cluster_grid(int B) {
   int dev = 0, cus = 0;
@@ -1067,15 +1088,29 @@ int cluster_grid(int B) {
   return B < cus ? cus : B;
 }
 
-// A batch that leaves CUs idle brings helpers for large frames: one workgroup
-// per CU in all (they leave within 300 µs when no frame needs them).
-void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm,
+// One utterance, or a few frames of several (a stream's chunk): leaders only,
+// then a launch with helpers for those that came to a large frame.  Clean
+// utterances keep no CU but their own (helpers hold one each, for 300 µs at
+// least: of four threads that decode commands of 60 frames on streams of their
+// own, each call took 1.25 ms with helpers in its launch and takes 0.73 ms, and
+// one thread's 0.738 and 0.713 ms), and a large frame finds helpers whenever it
+// comes (100 clean frames and then 233 of 7000 tokens: 76.2 and 15.9 ms).  The
+// kernel without the large frames' code spills nothing: 1000 frames of a hundred
+// tokens 8.9 and 8.3 ms.
+// A longer batch brings its helpers at once, one workgroup per CU in all, which
+// leave within 300 µs when no frame needs them: parked, an utterance whose second
+// frame is a large one would wait for the longest one's last.  There an utterance
+// whose large frames come later runs them alone, 0.3 ms each of 7000 tokens.
+constexpr int kSplitFrames = 64;
+
+void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, int frames, const Params& prm,
                     const uint32_t* bad, hipStream_t s) {
-  const int grid = cluster_grid(B);
-  if (prm.flags & WD_FLAG_PHASES)
-    hipLaunchKernelGGL(k_forward_phases, dim3(grid), dim3(kThreads), 0, s, g, lanes, prm, bad, (uint32_t)B);
-  else
-    hipLaunchKernelGGL(k_forward, dim3(grid), dim3(kThreads), 0, s, g, lanes, prm, bad, (uint32_t)B);
+  const bool prof = (prm.flags & WD_FLAG_PHASES) != 0, split = B == 1 || frames <= kSplitFrames;
+  if (split)
+    hipLaunchKernelGGL(prof ? k_forward_phases : k_forward, dim3(B), dim3(kThreads), 0, s, g, lanes, prm, bad,
+                       (uint32_t)B, false);
+  hipLaunchKernelGGL(prof ? k_forward_cluster_phases : k_forward_cluster, dim3(cluster_grid(B)), dim3(kThreads), 0, s,
+                     g, lanes, prm, bad, (uint32_t)B, split);
 }
 
 size_t cluster_ctl_bytes() { return kCtlBytes; }

@@ -24,7 +24,8 @@ void set_error(const std::string& msg);
 wd_status fail(wd_status st, const std::string& msg);
 wd_status hip_check(hipError_t e, const char* what);
 
-void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, const Params& prm,
+// The frames received and not decoded yet, of at most `frames` each.
+void launch_forward(const DevGraph& g, const LaneDesc* lanes, int B, int frames, const Params& prm,
                     const uint32_t* bad, hipStream_t s);
 // Lattice links of one-workgroup decodes, from the node store, after the
 // forward pass (all frames at once); before launch_lattice.

@@ -331,8 +331,8 @@ def test_wide_lattice_beam_chip(wf, oracle_mod, noisy, lb):
 
 def test_wide_lattice_time(wf):
     """Where the lattice beam keeps most of a wide decode's last frames, pruning
-    from live nodes stays near the raw links' time (measured 2.5 to 3.6 times
-    with a frame's links formed by one workgroup)."""
+    from live nodes stays near the raw links' time (measured 5.6 times it with a
+    frame's links formed by one workgroup, 1.6 times now)."""
     import torch
     graph = wf.Graph(graph_of(1_000_000, 3_000_000, 300, 0.3, 6, 91), 300)
     x = torch.from_numpy(flat(20, 300, 92)).to(graph.device)
@@ -342,3 +342,116 @@ def test_wide_lattice_time(wf):
         ms[fl] = min(wf.decode(graph, x, 20.0, 0, 16.0, timing=True, mode="chip", flags=fl).stats["lattice_ms"]
                      for _ in range(4))
     assert ms[0] < 2.4 * ms[wf.WD_FLAG_NO_INCREMENTAL_PRUNE], ms
+
+
+def cluster_sizes(r):
+    """Workgroups that ran each large frame, by frame (WD_FLAG_PHASES)."""
+    large = (r.phases[:, 10] & 1) == 0
+    return {int(t): int(r.phases[t, 11] >> 32) for t in np.flatnonzero(large)}
+
+
+def peaked(T, P, seed):
+    L = flat(T, P, seed) - 20.0
+    rng = np.random.default_rng(seed)
+    for t in range(T):
+        L[t, rng.choice(P, 3, replace=False)] = -1.0
+    return L.astype(np.float32)
+
+
+@pytest.mark.parametrize("B,T", [(1, 60), (3, 40), (3, 90), (12, 90)])
+def test_cluster_runs_the_frames(wf, oracle_mod, noisy, B, T):
+    """Large frames are run by several workgroups: of one utterance, and of
+    batches of few and of many frames.  The first run opens while helpers come
+    up, so later frames have more of them."""
+    import torch
+    g, graph = noisy
+    Ls, args = [flat(T, 200, 100 + b) for b in range(B)], (11.0, 2500, 6.0)
+    print(f"\n[gpu case] cluster sizes, {B} x {T}", flush=True)
+    rs = wf.decode_batch(graph, [torch.from_numpy(x).to(graph.device) for x in Ls], *args, mode="workgroup",
+                         flags=wf.WD_FLAG_PHASES)
+    for x, r in zip(Ls, rs):
+        n = cluster_sizes(r)
+        print(list(n.items())[:12], max(n.values()))
+        assert len(n) > T // 2
+        assert max(n.values()) >= (16 if B == 1 else 4), n
+        assert max(list(n.values())[8:]) >= list(n.values())[0], n
+    assert_same(rs[0], oracle_mod.decode(g, Ls[0], *args))
+
+
+def test_cluster_for_late_frames(wf, oracle_mod, noisy):
+    """Large frames that come after a thousand small ones, and again after a
+    hundred, find helpers."""
+    import torch
+    g, graph = noisy
+    L = np.concatenate([peaked(1000, 200, 110), flat(40, 200, 111), peaked(100, 200, 112), flat(40, 200, 113)])
+    args = (11.0, 2500, 6.0)
+    print("\n[gpu case] late large frames", flush=True)
+    r = wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, mode="workgroup", flags=wf.WD_FLAG_PHASES)
+    assert_same(r, oracle_mod.decode(g, L, *args))
+    n = cluster_sizes(r)
+    print(n)
+    assert not [t for t in n if t <= 1000], n
+    for a in (1000, 1140):
+        assert max([v for t, v in n.items() if a < t <= a + 40], default=0) >= 16, n
+
+
+def test_leaders_alone(wf, oracle_mod, noisy):
+    """A batch with an utterance for every compute unit has no helpers: each
+    leader runs its large frames alone."""
+    import torch
+    g, graph = noisy
+    B, args = torch.cuda.get_device_properties(0).multi_processor_count, (11.0, 1200, 6.0)
+    Ls = [flat(5, 200, 120 + b % 7) for b in range(B)]
+    xs = {b: torch.from_numpy(Ls[b]).to(graph.device) for b in range(7)}
+    print(f"\n[gpu case] {B} utterances", flush=True)
+    rs = wf.decode_batch(graph, [xs[b % 7] for b in range(B)], *args, mode="workgroup", flags=wf.WD_FLAG_PHASES)
+    want = [oracle_mod.decode(g, Ls[b], *args) for b in range(7)]
+    for b, r in enumerate(rs):
+        n = cluster_sizes(r)
+        assert n and set(n.values()) == {1}, (b, n)
+        assert_same(r, want[b % 7])
+
+
+def test_concurrent_decodes(wf, oracle_mod, noisy):
+    """Utterances on streams and threads of their own, with and without large
+    frames.  Helpers of one decode come up late where another's hold the compute
+    units, so that runs of large frames open with few and take in more (how often
+    is printed: nothing makes sure of it)."""
+    import threading
+    import torch
+    g, graph = noisy
+    args = (11.0, 2500, 6.0)
+    Ls = [peaked(50, 200, 130), flat(60, 200, 131), flat(60, 200, 132),
+          np.concatenate([peaked(30, 200, 133), flat(40, 200, 134)])]
+    p = wf.wd_params(*args, wf.WD_FLAG_ONE_WORKGROUP | wf.WD_FLAG_PHASES)
+    caps = wf.wd_caps(0, 0, 400_000, 800_000, 400_000, 0)
+    got, xs = [[] for _ in Ls], [torch.from_numpy(x).to(graph.device) for x in Ls]
+    print("\n[gpu case] concurrent decodes", flush=True)
+    want = [oracle_mod.decode(g, x, *args) for x in Ls]
+
+    def run(i):
+        T = Ls[i].shape[0]
+        nb, used = wf.wd_workspace_bytes(graph.handle, 1, T, p, caps)
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ws = torch.empty(nb + 256, dtype=torch.uint8, device=graph.device)
+            for _ in range(8):
+                st, r = wf.wd_decode(graph.handle, xs[i].data_ptr(), T, p, used, (ws.data_ptr() + 255) // 256 * 256, nb,
+                                     s.cuda_stream)
+                got[i].append((st, wf.wd_result_read(r, False, True) if r else None))
+                if r:
+                    wf.wd_result_free(r)
+
+    torch.cuda.synchronize()
+    th = [threading.Thread(target=run, args=(i,)) for i in range(len(Ls))]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for o, rs in zip(want, got):
+        for st, r in rs:
+            assert st == wf.WD_OK
+            assert_same(r, o)
+    sizes = [list(cluster_sizes(r).values()) for rs in got for _, r in rs]
+    print("decodes with large frames", sum(map(bool, sizes)), "whose cluster grew",
+          sum(any(b > a for a, b in zip(n, n[1:])) for n in sizes))
