@@ -245,6 +245,17 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
 }
 
+// x, through an empty asm on its address: what is read of it afterwards is
+// read there, and not held in registers from an earlier read on.
+// (Through the constant address space: x does not change while the kernel runs.)
+template <class T>
+__device__ __forceinline__ const T& again_read(const T& x) {
+  typedef const __attribute__((address_space(4))) T* Const;
+  Const p = (Const)&x;
+  asm volatile("" : "+s"(p));
+  return *(const T*)p;
+}
+
 // kProf: the step-profile copy (WD_FLAG_PHASES), which stores the device
 // wall clock at each step boundary of every frame (thread 0).
 // kCluster: workgroups 0 .. B-1 lead an utterance each; the others help (one
@@ -378,7 +389,11 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     }
   };
   bool parked = false;
+  const DevGraph& g_all = g;
+  const LaneDesc& L_all = L;
   while (true) {  // frames in LDS, then a run of large ones
+    const DevGraph& g = again_read(g_all);
+    const LaneDesc& L = again_read(L_all);
     uint32_t w = 0, N = 1;
     if (lead) {
       bool large = false;
@@ -1008,7 +1023,7 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
     }
     if constexpr (kCluster) {
       const uint64_t t0 = wall_clock64();
-      cl_run(g, L, prm, cs, C, w, N, paths);
+      cl_run(again_read(g_all), again_read(L_all), prm, cs, C, w, N, paths);
       busy += wall_clock64() - t0;
       if (!lead) continue;
       // the run's outcome; the LDS tables start afresh
@@ -1072,7 +1087,10 @@ __device__ __forceinline__ void forward_body(FwdShared& sh, const DevGraph& g, c
   __global__ void __launch_bounds__(kThreads) NAME(DevGraph g, const LaneDesc* __restrict__ lanes, Params prm, \
                                                    const uint32_t* __restrict__ bad, uint32_t B, bool resume) { \
     __shared__ FwdShared sh;                                                                                   \
-    forward_body<PROF, CLUSTER>(sh, g, lanes, prm, bad, B, CLUSTER && resume);                                 \
+    /* (the graph where the arguments are: a reference to g would be to a copy) */                             \
+    typedef const __attribute__((address_space(4))) DevGraph KernArg;                                          \
+    const DevGraph& gk = *(const DevGraph*)(KernArg*)__builtin_amdgcn_kernarg_segment_ptr();                   \
+    forward_body<PROF, CLUSTER>(sh, gk, lanes, prm, bad, B, CLUSTER && resume);                                 \
   }
 WD_FORWARD(k_forward, false, false)
 WD_FORWARD(k_forward_phases, true, false)
