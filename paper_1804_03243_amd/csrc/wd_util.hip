@@ -120,8 +120,11 @@ __global__ void __launch_bounds__(256) k_setup(const LaneDesc* __restrict__ lane
 // when no helper is up: one utterance on 30M states with three large frames
 // spent 5.6 of 20.6 ms on that and spends 0.11 ms here, while 256 utterances on
 // 5M states would spend 5 of 26 ms here.  The fill of some 50 utterances takes as long
-// as the frame's own emptying; the line lies where it costs a sixth of that.
-constexpr int kFillLanes = 8;
+// as a frame's own emptying; the line lies where it costs half of that, since in a
+// batch of long utterances some frame usually is large, after the helpers have left
+// (16 clean utterances of 500 frames on 5M states: 6.6 ms emptied by the frame,
+// 5.8 ms here).
+constexpr int kFillLanes = 24;
 
 void launch_setup(const LaneDesc* lanes, int B, uint32_t* bad, uint64_t used_words, uint64_t S, uint64_t bitmap_words,
                   bool chip, hipStream_t s) {
