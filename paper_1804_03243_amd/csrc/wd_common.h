@@ -110,6 +110,7 @@ struct DevGraph {
   const uint4* rarc;
   uint64_t npaths;
   uint32_t pstride;
+  uint32_t path_level;         // first epsilon level that chip-wide frames take by paths
   uint32_t S;
   uint32_t start;
   uint32_t nlevels;

@@ -32,6 +32,7 @@ struct Prepared {
   std::vector<uint4> phead;
   std::vector<float> ptail;
   uint32_t pstride = 0;
+  uint32_t path_level = 0;
 };
 
 struct Layout {
@@ -193,6 +194,28 @@ void eps_paths(const wd_graph_desc* d, const std::vector<uint32_t>& topo, Prepar
   }
 }
 
+// The first epsilon level that chip-wide frames take by the paths out of its and
+// the upper levels' states, in one launch, instead of a launch per level.  Paths
+// beyond the arcs are extra work, and each level by paths saves a launch (9-11 µs),
+// in which the chip relaxes about half a million paths: with 8 levels of 50 thousand
+// states of two epsilon arcs each, 5.2 million extra paths from level 2 on, 41
+// frames took 9.8 ms by paths from level 2 and 8.3 ms by levels; on the wide-beam
+// graph, 0.27 million extra, paths take 18 of the 65 µs that its six upper levels
+// did.  Not below level 2: levels 0 and 1 hold three quarters of the states there, and
+// relaxing their paths costs more than the two launches.
+constexpr uint32_t kPathLevelMin = 2;
+constexpr uint64_t kPathsPerLaunch = 500000;
+
+uint32_t path_level_of(const Prepared& p, int64_t S) {
+  std::vector<uint64_t> extra(p.nlevels + 1, 0);  // paths beyond the arcs, of levels l and up
+  for (int64_t s = 0; s < S; ++s)
+    if (p.sclass[s] != kNoEps) extra[p.sclass[s]] += (p.off[s + 1].z - p.off[s].z) - (p.off[s + 1].y - p.off[s].y);
+  for (uint32_t l = p.nlevels; l-- > 0;) extra[l] += extra[l + 1];
+  uint32_t l = kPathLevelMin;
+  while (l + 1 < p.nlevels && extra[l] > kPathsPerLaunch * (p.nlevels - 1 - l)) ++l;
+  return l;
+}
+
 wd_status prepare(const wd_graph_desc* d, Prepared& p, uint64_t* Ae_out, uint64_t* Ax_out) {
   wd_status st = validate(d);
   if (st != WD_OK) return st;
@@ -244,6 +267,7 @@ wd_status prepare(const wd_graph_desc* d, Prepared& p, uint64_t* Ae_out, uint64_
     p.xnext[j] = make_uint2(p.off[v].y, p.off[v + 1].y);
   }
   eps_paths(d, topo, p);
+  if (p.paths) p.path_level = path_level_of(p, S);
   (void)A;
   *Ae_out = Ae;
   *Ax_out = Ax;
@@ -393,6 +417,7 @@ extern "C" wd_status wd_graph_load(const wd_graph_desc* d, void* dev_buf, size_t
   dg.rarc = (const uint4*)(base + l.rarc);
   dg.npaths = npaths;
   dg.pstride = p.pstride;
+  dg.path_level = p.path_level;
   dg.S = (uint32_t)S;
   dg.start = (uint32_t)d->start_state;
   dg.nlevels = p.nlevels;

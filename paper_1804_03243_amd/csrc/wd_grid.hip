@@ -574,19 +574,15 @@ __global__ void __launch_bounds__(kGT) k_g_level(DevGraph g, const LaneDesc* __r
 }
 
 // The upper epsilon levels in one launch: the states bucketed on levels from
-// kPathLevel on relax every epsilon path out of them (the graph's path table),
-// as the one-workgroup closure does for all levels: a path's cost adds its
+// the graph's path level on relax every epsilon path out of them (the graph's path
+// table), as the one-workgroup closure does for all levels: a path's cost adds its
 // arcs' weights in path order, so the minimum over the paths into a state is
-// what one pass per level gives it, arc ids included.  A level holds half the
-// states of the one below and its launch costs 9-11 µs however few they are,
-// while the paths out of the upper levels are few (all paths are 3.2 times the
-// arcs on the wide-beam graph, and relaxing those of level 0 costs more than
-// its launch).  What the states' epsilon arcs add to the counts is taken from
-// their final costs by the survivor kernel.
-constexpr uint32_t kPathLevel = 2;
-
+// what one pass per level gives it, arc ids included.  A level's launch costs
+// 9-11 µs however few states it has, while the paths out of the upper levels
+// usually are few (path_level_of has the line).  What the states' epsilon arcs add
+// to the counts is taken from their final costs by the survivor kernel.
 __host__ __device__ inline uint32_t path_level(const DevGraph& g, const Params& prm) {
-  return g.npaths != 0 && g.nlevels > kPathLevel + 1u && !(prm.flags & WD_FLAG_EPS_LEVELS) ? kPathLevel : g.nlevels;
+  return g.npaths != 0 && g.nlevels > g.path_level + 1u && !(prm.flags & WD_FLAG_EPS_LEVELS) ? g.path_level : g.nlevels;
 }
 
 __global__ void __launch_bounds__(kGT) k_g_paths(DevGraph g, const LaneDesc* __restrict__ lanes, GridLane* gl,
@@ -598,7 +594,7 @@ __global__ void __launch_bounds__(kGT) k_g_paths(DevGraph g, const LaneDesc* __r
   GridLane& G = gl[blockIdx.y];
   if (G.stop || G.best_key >= kInfKey) return;
   // the levels' entries as one list
-  const uint32_t l0 = kPathLevel;
+  const uint32_t l0 = g.path_level;
   if (threadIdx.x == 0) {
     uint32_t n = 0;
     for (uint32_t l = l0; l < g.nlevels; ++l) {

@@ -455,3 +455,34 @@ def test_concurrent_decodes(wf, oracle_mod, noisy):
     sizes = [list(cluster_sizes(r).values()) for rs in got for _, r in rs]
     print("decodes with large frames", sum(map(bool, sizes)), "whose cluster grew",
           sum(any(b > a for a, b in zip(n, n[1:])) for n in sizes))
+
+
+@pytest.mark.parametrize("fan,levels", [(2, 9), (3, 8), (1, 9)])
+def test_chip_wide_many_paths(wf, oracle_mod, fan, levels):
+    """Graphs with many epsilon paths out of their upper levels (taken by
+    levels up to a higher one) and with few."""
+    import torch
+    S, P = 60_000, 100
+    rng = np.random.default_rng(140)
+    lvl = rng.integers(0, levels, S)
+    lvl[0] = 0
+    deg = np.where(lvl < levels - 1, 2 + fan, 2)
+    deg[0] = 64 + fan
+    row = np.zeros(S + 1, np.int64)
+    np.cumsum(deg, out=row[1:])
+    n = int(row[-1])
+    src = np.repeat(np.arange(S), deg)
+    eps = (lvl[src] < levels - 1) & (np.arange(n) - row[src] >= deg[src] - fan)
+    dst, il = rng.integers(1, S, n), rng.integers(1, P + 1, n)
+    il[eps] = 0
+    for l in range(levels - 1):
+        k = np.flatnonzero(eps & (lvl[src] == l))
+        dst[k] = rng.choice(np.flatnonzero(lvl == l + 1), k.size)
+    w = rng.exponential(3.0, n).astype(np.float32)
+    g = synth._pack(dict(row_ptr=row, dst=dst, ilabel=il, olabel=rng.integers(0, 9, n), weight=w), S)
+    graph = wf.Graph(g, P)
+    L = flat(9, P, 141)
+    for args in ((13.0, 0, 6.0), (13.0, 6000, 6.0)):
+        check(wf, oracle_mod, g, graph, L, args, "chip")
+        r = wf.decode(graph, torch.from_numpy(L).to(graph.device), *args, mode="chip", flags=wf.WD_FLAG_EPS_LEVELS)
+        assert_same(r, oracle_mod.decode(g, L, *args))
