@@ -104,7 +104,7 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   R.desc = (LaneDesc*)take(sizeof(LaneDesc));
   R.info = (LaneInfo*)take(sizeof(LaneInfo));
   R.bad = (uint32_t*)take(sizeof(uint32_t));
-  // (one size, so that a workspace does not depend on the mode)
+  // (one region: chip-wide decodes keep their state there, the others their clusters' control blocks)
   R.grid_bytes = align_up(std::max(grid_lane_bytes(), cluster_ctl_bytes()), 256);
   R.grid = take(R.grid_bytes);
   R.ctl = c.chip ? take(align_up(cluster_ctl_bytes(), 256)) : R.grid;  // (one workgroup: nothing else there)
@@ -122,12 +122,12 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
   char* surv_pack = take(8 * c.frame);
   char* f_state = take(4 * F1);
   char* f_key = take(4 * F1);
-  char* f_arc = take(4 * F1);
+  char* f_arc = c.chip ? take(4 * F1) : nullptr;
   char* f_edeg = take(4 * F1);
   char* f_xdeg = take(4 * F1);
   char* f_ebeg = take(4 * F1);
   char* f_xbeg = take(4 * F1);
-  char* f_cls = take(F1);
+  char* f_cls = c.chip ? take(F1) : nullptr;
   char* cand = take(16 * c.arcs);
   char* n_state = take(4 * c.nodes);
   char* n_pack = take(8 * c.nodes);
@@ -180,12 +180,12 @@ Regions carve(const wd_graph* g, int B, int32_t max_T, const Caps& c, char* base
       L.surv_pack = (decltype(L.surv_pack))at(surv_pack, 8 * c.frame);
       L.f_state = (decltype(L.f_state))at(f_state, 4 * F1);
       L.f_key = (decltype(L.f_key))at(f_key, 4 * F1);
-      L.f_arc = (decltype(L.f_arc))at(f_arc, 4 * F1);
+      L.f_arc = c.chip ? (decltype(L.f_arc))at(f_arc, 4 * F1) : nullptr;
       L.f_edeg = (decltype(L.f_edeg))at(f_edeg, 4 * F1);
       L.f_xdeg = (decltype(L.f_xdeg))at(f_xdeg, 4 * F1);
       L.f_ebeg = (decltype(L.f_ebeg))at(f_ebeg, 4 * F1);
       L.f_xbeg = (decltype(L.f_xbeg))at(f_xbeg, 4 * F1);
-      L.f_cls = (decltype(L.f_cls))at(f_cls, F1);
+      L.f_cls = c.chip ? (decltype(L.f_cls))at(f_cls, F1) : nullptr;
       L.cand = (decltype(L.cand))at(cand, 16 * c.arcs);
       L.n_state = (decltype(L.n_state))at(n_state, 4 * c.nodes);
       L.n_pack = (decltype(L.n_pack))at(n_pack, 8 * c.nodes);

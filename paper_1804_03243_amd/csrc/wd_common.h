@@ -214,7 +214,7 @@ struct LaneDesc {
   // per-frame scratch
   WD_GLOBAL unsigned long long* slot;    // [S] packed (cost key, arc id); kEmpty between frames
   // one-workgroup mode: the slots of odd frames (large frames only; both slot
-  // arrays and the bitmap are emptied when a decode has its first large frame)
+  // arrays and the bitmap are emptied before the decode or in its first large frame)
   WD_GLOBAL unsigned long long* slot2;   // [S]
   WD_GLOBAL struct ClusterCtl* ctl;      // control block of the utterance's workgroup cluster
   // chip-wide mode
@@ -228,12 +228,12 @@ struct LaneDesc {
   // (used when a frame has more survivors than the LDS frontier holds)
   WD_GLOBAL uint32_t* f_state;
   WD_GLOBAL uint32_t* f_key;             // cost key
-  WD_GLOBAL uint32_t* f_arc;             // predecessor arc
+  WD_GLOBAL uint32_t* f_arc;             // predecessor arc (chip-wide mode)
   WD_GLOBAL uint32_t* f_edeg;            // exclusive prefix of emitting out-degree (+ total)
   WD_GLOBAL uint32_t* f_xdeg;            // exclusive prefix of epsilon out-degree (+ total)
   WD_GLOBAL uint32_t* f_ebeg;            // first emitting arc of the state
   WD_GLOBAL uint32_t* f_xbeg;            // first epsilon arc of the state
-  WD_GLOBAL uint8_t* f_cls;
+  WD_GLOBAL uint8_t* f_cls;              // (chip-wide mode)
   WD_GLOBAL uint4* cand;                 // [cand_cap] emitting candidates {arc, src node, dst, x bits}
   // history
   WD_GLOBAL uint32_t* n_state;           // [node_cap]
