@@ -211,10 +211,10 @@ def test_stream_capacity_fallback(wf, oracle_mod, tiny10k, mode):
 
 
 def test_concurrent_chip_decodes(wf, oracle_mod, tiny10k):
-    """Chip-wide decodes from two host threads on two HIP streams share the
-    library's pruning stream (each decode orders it with its own events):
-    every result equals the oracle's.  Each thread has its own Graph (a
-    Graph's workspace serves one decode at a time)."""
+    """Chip-wide decodes from two host threads on two HIP streams, each with
+    a pruning sweep whose helpers want the same compute units: every result
+    equals the oracle's.  Each thread has its own Graph (a Graph's workspace
+    serves one decode at a time)."""
     import threading
     import torch
     cfg, g, L, _ = tiny10k

@@ -105,19 +105,18 @@ def wide_golden(request, wf):
 def test_wide_2m_golden(wf, wide_golden, mode):
     """The first 200 frames of the wide-beam workload (650k tokens and 1.1M
     candidate links per frame once it has ramped up, epsilon chains of depth
-    8), decoded as a whole utterance without the debug flag, so that in
-    chip-wide mode the lattice is pruned in 32-frame windows on the second
-    stream while decoding goes on (windows 0-5, each 8 frames after its end;
-    the last, partial window is gathered for the final pruning): words, cost, statistics and every lattice link and node must match
-    the oracle's stored result bit for bit (per-frame digests written by
-    tests/golden/make_wide_2m.py from an oracle run), posteriors within 1e-4."""
+    8), decoded as a whole utterance without the debug flag, so that the
+    lattice is pruned from live nodes without a raw one: words, cost, statistics
+    and every lattice link and node must match the oracle's stored result bit
+    for bit (per-frame digests written by tests/golden/make_wide_2m.py from an
+    oracle run), posteriors within 1e-4."""
     gm, name, cfg, graph, x, meta, post = wide_golden
     print(f"\n[gpu case] {name} golden first {GOLDEN_T} frames mode={mode}", flush=True)
     r = wf.decode(graph, x, cfg["beam"], cfg["max_active"], cfg["lattice_beam"], mode=mode)
     gm.compare(meta, post, r.words, r.cost, r.links, r.nodes, r.stats)
-    if mode.startswith("chip"):
-        # incremental pruning ran: the link store held far fewer than the raw links
-        assert r.needed["links"] + 2 * r.needed["window_links"] < r.stats["raw_links"]
+    # the link store held the kept links and nothing else
+    assert r.needed["links"] == r.stats["kept_links"] < r.stats["raw_links"] // 100
+    assert r.needed["window_links"] == 0
 
 
 @pytest.mark.parametrize("name,mode", [("wide_2m", "chip"), ("wide_2m_dyadic", "chip"), ("wide_2m", "chip_dyn")])
@@ -136,7 +135,7 @@ def test_wide_2m_full(wf, name, mode):
     r = wf.decode(graph, torch.from_numpy(L).to(graph.device), cfg["beam"], cfg["max_active"],
                   cfg["lattice_beam"], mode=mode)
     assert r.stats["max_tokens"] > 500000 and r.stats["raw_links"] > 500_000_000
-    # incremental pruning keeps the link store far below the raw lattice
-    assert r.needed["links"] < r.stats["raw_links"] // 2
+    # the link store held the kept links and nothing else
+    assert r.needed["links"] == r.stats["kept_links"]
     unique = lattice_props.check(g, L, cfg["lattice_beam"], r)
     assert unique or name.endswith("dyadic")
