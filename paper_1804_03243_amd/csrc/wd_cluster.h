@@ -178,8 +178,8 @@ __device__ __forceinline__ void cl_barrier(Ctl* C, uint32_t N, uint32_t& gen) {
       const uint32_t target = gen;
       if (!arrived(cl_load(&C->bar), target)) {
         SpinClock spin(wall_clock64());
-        while (!arrived(cl_load(&C->bar), target))
-          if (spin.beyond(wall_clock64())) {
+        for (uint32_t n = 1; !arrived(cl_load(&C->bar), target); ++n)
+          if (n % kSpinLooks == 0 && spin.beyond(wall_clock64())) {
             cl_store(&C->bad, 1u);
             break;
           }

@@ -13,7 +13,8 @@
 namespace wd {
 
 constexpr uint64_t kSpinTicks = 200000000; // a wait that has run this long (2 s of the 100 MHz clock) is an error, not a hang
-constexpr uint64_t kSpinGap = 1000;        // longest time between two looks that counts (10 µs; a look takes about 1 µs)
+constexpr uint64_t kSpinGap = 1000;        // longest time between two looks at the clock that counts (10 µs)
+constexpr uint32_t kSpinLooks = 8;         // looks at the arrivals (about 0.7 µs each) for one at the clock
 
 // Whether a count of arrivals has come to `target`.  The count goes on over a
 // whole launch, modulo 2^32 (254 epsilon levels of 32 workgroups are 16 thousand
