@@ -49,16 +49,17 @@ BYTES_TOKEN = 8 + 12 + 12
 BYTES_LINK = 16
 
 
-# HBM traffic of one k_forward launch on this workload, from rocprofv3 --pmc
+# HBM traffic of one forward pass on this workload (k_forward, and 32 KB by the
+# k_forward_cluster launch behind it, which finds no large frame), from rocprofv3 --pmc
 # runs of this script (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch), each
 # divided by the counter's reading per byte of a plain device copy of known
 # size (bench.py --copy-kernel-bytes).  Valid while k_forward's sources hash to this.
-TRAFFIC = {"sources_sha256": "939d545fec9ffe3ba92d01c1a49c7271ec731bb32f90926100672b7b1ed07a56",
-           "bytes_per_launch": 65999327}
+TRAFFIC = {"sources_sha256": "7fda6090dc60197eef97df6c835af2060d0c3ae625688c4d49806014893dad88",
+           "bytes_per_launch": 58319565}
 
 
 # what k_forward is built from, and the device graph layout it reads
-FORWARD_SOURCES = ("wd_block.h", "wd_common.h", "wd_forward.hip", "wd_graph.hip")
+FORWARD_SOURCES = ("wd_block.h", "wd_cluster.h", "wd_common.h", "wd_forward.hip", "wd_graph.hip", "wd_spin.h")
 
 
 def sources_sha256() -> str:
